@@ -6,7 +6,8 @@ import sys
 PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 LIB = os.path.join(PKG, "libeife.so")
-SOURCES = [os.path.join(PKG, "csrc", "eife.hip"), os.path.join(PKG, "csrc", "eife_corr.hip")]
+CSRC = os.path.join(PKG, "csrc")
+SOURCES = ["eife.hip", "eife_fold.hip", "eife_corr.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",
@@ -32,8 +33,8 @@ def build(verbose=False):
     The sources are compiled to objects in parallel, then linked."""
     objs, procs = [], []
     for src in SOURCES:
-        obj = os.path.join(PKG, os.path.basename(src) + ".o")
-        cmd = [hipcc()] + [f for f in HIPCC_FLAGS if f != "-shared"] + ["-c", "-o", obj, src]
+        obj = os.path.join(PKG, src + ".o")
+        cmd = [hipcc()] + [f for f in HIPCC_FLAGS if f != "-shared"] + ["-c", "-o", obj, os.path.join(CSRC, src)]
         if verbose:
             print(" ".join(cmd), flush=True)
         procs.append(subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True))

@@ -39,6 +39,7 @@ static_assert(sizeof(eife::RowGeom) + sizeof(eife::Forcing) + 8 * sizeof(void*) 
 static_assert(sizeof(eife::ColGeom) + sizeof(eife::Diag) + 8 * sizeof(void*) <= 1024, "column pass arguments");
 static_assert(sizeof(eife::NormGeom) + 8 * sizeof(void*) <= 1024, "norm pass arguments");
 #include "eife_long.hpp"
+#include "eife_fold.hpp"
 
 using namespace eife;
 
@@ -663,6 +664,21 @@ void col_fast_launch(int var, int mode, int pitch, int outer, int count, hipStre
   }
 }
 
+// FP32 lines of 256 intervals on 3D grids take the folded passes
+// (eife_fold.hpp) where the launch fills the chip: from two 16-pair column tiles
+// or 16 wavefronts of eight rows per compute unit.  Smaller launches last as
+// long as one wavefront's work, and the folded wavefront holds four line pairs
+// against one (255^2: x pass 9 against 4 us, stage passes 14 against 6.5 us; at
+// 255^3: x pass 39 against 43 us, stage passes 61-66 against 72-78 us).
+template <typename T>
+bool fold_cols(const eife_grid_s* g, int axis, int outer) {
+  return sizeof(T) == 4 && g->d == 3 && g->N[axis] == 256 && (g->pitch / 32) * int64_t(outer) >= 2 * g_cus;
+}
+template <typename T>
+bool fold_rows(const eife_grid_s* g) {
+  return sizeof(T) == 4 && g->d == 3 && g->N[0] == 256 && g->nlines_total() >= 16 * 8 * g_cus;
+}
+
 // Periodic lines with wave-local kernels: N = L = 128, 256, 512 (single grids).
 inline bool per_fast_len(int N) { return N == 128 || N == 256 || N == 512; }
 
@@ -815,6 +831,12 @@ bool try_row_fast(const eife_grid_s* g, int var, int mode, int count, hipStream_
       row_long_launch<T, 8192>(mode, rg.nrows, s, src, dst, dst2, rg, tw, F);
     return true;
   }
+  if constexpr (sizeof(T) == 4) {
+    if (mode == ROW_PHYS && !ri && fold_rows<T>(g)) {
+      fold::row_launch(rg.nrows, s, dst, rg, tw, F);
+      return true;
+    }
+  }
   if (!fast_len<T>(g->N[0])) return false;
   switch (g->N[0]) {
     case 64: row_fast_launch<T, 128>(var, mode, rg.nrows, count, s, src, dst, dst2, rg, tw, F, ri); return true;
@@ -846,6 +868,12 @@ bool try_col_fast(const eife_grid_s* g, int var, int axis, int mode, int outer, 
     else
       col_long_launch<T, 8192>(mode, g->pitch, outer, s, W, H, cg, tw, dg);
     return true;
+  }
+  if constexpr (sizeof(T) == 4) {
+    if (!ci && fold_cols<T>(g, axis, outer)) {
+      fold::col_launch(g_cus, mode, g->pitch, outer, s, W, H, cg, tw, dg);
+      return true;
+    }
   }
   if (!fast_len<T>(g->N[axis])) return false;
   switch (g->N[axis]) {

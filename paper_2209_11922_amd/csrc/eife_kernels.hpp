@@ -503,7 +503,7 @@ struct Forcing {
 
 // sin(pi (a + (i + 1) h)) for i < n: the per-axis factors of the manufactured
 // solution and of Example 5.1's forcing.
-__global__ void sinpi_table(double* __restrict__ out, int n, double a, double h) {
+static __global__ void sinpi_table(double* __restrict__ out, int n, double a, double h) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) out[i] = sinpi(a + (i + 1) * h);
 }
@@ -1438,7 +1438,7 @@ __global__ void __launch_bounds__(kNwThreads) norm_waves(const T* __restrict__ u
 // Second level: 256 threads stride over the block partials, then a fixed-order
 // tree in LDS (deterministic); accumulator 2 is a maximum, the others sums.
 constexpr int kNormFinalThreads = 256;
-__global__ void __launch_bounds__(kNormFinalThreads) norm_final(const double* __restrict__ partials, int nblocks,
+static __global__ void __launch_bounds__(kNormFinalThreads) norm_final(const double* __restrict__ partials, int nblocks,
                                                                 double* __restrict__ out5) {
   __shared__ double red[kNormAcc][kNormFinalThreads];
   const int t = threadIdx.x;
@@ -1465,7 +1465,7 @@ __global__ void __launch_bounds__(kNormFinalThreads) norm_final(const double* __
 // norm_final's reduction followed by the finishing arithmetic of eife_norms on
 // the device: out4 = (||e||_0, ||e||_1, max|e|, energy) with ||e||_0^2 = e^T M e,
 // ||e||_1^2 = e^T M e + e^T K_1 e and energy = (D/2) u^T K_1 u + cellvol sum F(u_i).
-__global__ void __launch_bounds__(kNormFinalThreads) norm_finish(const double* __restrict__ partials, int nblocks,
+static __global__ void __launch_bounds__(kNormFinalThreads) norm_finish(const double* __restrict__ partials, int nblocks,
                                                                  double D, double cellvol, double* __restrict__ out4) {
   __shared__ double red[kNormAcc][kNormFinalThreads];
   const int t = threadIdx.x;
