@@ -38,8 +38,7 @@
 static_assert(sizeof(eife::RowGeom) + sizeof(eife::Forcing) + 8 * sizeof(void*) <= 1024, "row pass arguments");
 static_assert(sizeof(eife::ColGeom) + sizeof(eife::Diag) + 8 * sizeof(void*) <= 1024, "column pass arguments");
 static_assert(sizeof(eife::NormGeom) + 8 * sizeof(void*) <= 1024, "norm pass arguments");
-#include "eife_long.hpp"
-#include "eife_fold.hpp"
+#include "eife_grid.hpp"
 
 using namespace eife;
 
@@ -63,136 +62,17 @@ int fail(int code, const char* fmt, ...) {
     if (_e != hipSuccess) return fail(EIFE_EHIP, "%s: %s", #expr, hipGetErrorString(_e)); \
   } while (0)
 
-constexpr int kThreads = 256;
-// Generic FP64 passes over lines of at least kLongLine FFT points (one or two
-// lines fill a block's LDS) run kLongThreads threads per block: more waves per
-// compute unit and 8 instead of 32 values per thread.
-constexpr int kLongLine = 4096;
-constexpr int kLongThreads = 1024;
-// FP64 only: FP32 long lines measured slower with the larger blocks (two
-// 256-thread blocks of one FP32 line each share a compute unit instead).
-template <typename T>
-bool long_lines(int L) {
-  return sizeof(T) == 8 && L >= kLongLine;
-}
-constexpr size_t kLdsBudget = 80 * 1024;  // per block, two blocks per CU fit in 160 KB
 constexpr int kNormBlocksMax = 8192;
 constexpr int kTabArrays = 8;  // lam, w, M, Q, Mc, R, Mc3, Qc3 per axis
-constexpr int kPipeBlocksPerCu = 4;  // resident blocks of the pipelined column pass (LDS permitting)
-constexpr int kStagePipeMinTiles = 2;  // tiles per resident block from which the stage pass is pipelined
-int g_cus = 256;                     // compute units of the device (set at grid creation)
-
-bool factor_plan(int L, FftPlan* pl) {
-  pl->L = L;
-  pl->n8 = pl->n4 = pl->n2 = pl->n3 = pl->n5 = pl->n7 = pl->nd = 0;
-  pl->dr[0] = pl->dr[1] = pl->dr[2] = 0;
-  int r = L;
-  while (r % 8 == 0) {
-    r /= 8;
-    pl->n8++;
-  }
-  while (r % 4 == 0) {
-    r /= 4;
-    pl->n4++;
-  }
-  while (r % 2 == 0) {
-    r /= 2;
-    pl->n2++;
-  }
-  while (r % 3 == 0) {
-    r /= 3;
-    pl->n3++;
-  }
-  while (r % 5 == 0) {
-    r /= 5;
-    pl->n5++;
-  }
-  while (r % 7 == 0) {
-    r /= 7;
-    pl->n7++;
-  }
-  // the remaining prime factors (all above 7) run as direct-DFT stages
-  for (int p = 11; p <= r; p += 2) {
-    while (r % p == 0) {
-      if (pl->nd == 3) return false;
-      pl->dr[pl->nd++] = p;
-      r /= p;
-    }
-  }
-  return r == 1;
-}
 
 }  // namespace
 
-struct eife_grid_s {
-  int d = 0;
-  int N[3] = {2, 2, 2};
-  int n[3] = {1, 1, 1};  // unknowns per axis: N - 1 (Dirichlet), N (periodic); virtual axes: 1
-  bool per[3] = {false, false, false};  // periodic axis (real axes of a periodic grid)
-  double h[3] = {1, 1, 1};
-  double a[3] = {0, 0, 0};
-  double D = 1;
-  int dtype = EIFE_F64;
-  size_t esz = 8;
-  int pitch = 0;  // row pitch of W and H (elements)
-  // scheme
-  double tau = 0;
-  int stages = 0;
-  double c2 = 0.5;
-  double c2_3 = 1.0 / 3.0, c3_3 = 2.0 / 3.0;  // nodes of the three-stage scheme
-  void* X = nullptr;  // extra spectral state of the three-stage scheme (allocated on first use)
-  int load = EIFE_LOAD_LUMPED;
-  double c0 = 0, c1 = 0;
-  bool phi_ready = false;
-  int device = 0;
-  size_t max_lds = 65536;
-  // device memory
-  void* W = nullptr;
-  void* H = nullptr;
-  void* tw[3] = {nullptr, nullptr, nullptr};
-  double* tab[3] = {nullptr, nullptr, nullptr};  // kTabArrays arrays per axis
-  double* sinpi_ax[3] = {nullptr, nullptr, nullptr};  // sin(pi x) at the interior nodes of each axis
-  int tablen[3] = {0, 0, 0};
-  double* partials = nullptr;
-  double* out5 = nullptr;
-  double* host5 = nullptr;  // pinned
-  // per-step phi tables of variable-step runs (eife_step_variable): a chunk of
-  // steps at a time, each step 3 arrays (M, Q, Mc) per axis
-  // (two chunk buffers, filled alternately)
-  double* vtab = nullptr;
-  double* vhost = nullptr;  // pinned staging copies
-  hipEvent_t vev[2] = {nullptr, nullptr};  // copy of the buffer's last chunk done
-  int64_t vchunk = 0;       // steps per chunk (0: not allocated)
-  std::vector<double> hlam[3];  // host copy of the lambda table of each axis
-  // launch shapes
-  FftPlan plan[3];
-  int transform = EIFE_TX_FFT;
-  void* smat[3] = {nullptr, nullptr, nullptr};  // split-BF16 sine matrices (hi then lo, kp x kp each)
-  int kp[3] = {0, 0, 0};
-  int prow = 1;     // pairs per block, row pass
-  int pcol[3] = {1, 1, 1};  // pairs per block, column pass along axis 1, 2
-  int nlines_total() const { return n[1] * n[2]; }
-  // per-pass timing (eife_profile)
-  bool prof_on = false;
-  struct ProfRec {
-    int kind;
-    hipEvent_t a, b;
-  };
-  std::vector<ProfRec> prof_pending;
-  std::vector<hipEvent_t> ev_pool;
-  double prof_ms[EIFE_PASS_COUNT] = {0};
-  int64_t prof_n[EIFE_PASS_COUNT] = {0};
-};
+namespace eife {
+int g_cus = 256;
+thread_local const char* g_bad_launch = nullptr;
+}  // namespace eife
 
 namespace {
-
-size_t lds_bytes(const eife_grid_s* g, int P, int L) { return size_t(P) * size_t(L + 1) * 2 * g->esz; }
-
-int pick_pairs(const eife_grid_s* g, int L, int cap) {
-  int P = cap;
-  while (P > 1 && (lds_bytes(g, P, L) > kLdsBudget || size_t(P) * L > size_t(kMaxElems) * kThreads)) P--;
-  return P;
-}
 
 template <typename T>
 void fill_twiddles(std::vector<Cx<T>>& v, int L) {
@@ -378,27 +258,6 @@ int upload_sinpi(eife_grid_s* g) {
   return EIFE_OK;
 }
 
-template <typename T, bool BAT>
-int set_lds_attrs_v(int b) {
-  const void* fns[] = {reinterpret_cast<const void*>(&row_pass<T, ROW_PHYS, BAT>),
-                       reinterpret_cast<const void*>(&row_pass<T, ROW_FWD_USER, BAT>),
-                       reinterpret_cast<const void*>(&row_pass<T, ROW_INV_USER, BAT>),
-                       reinterpret_cast<const void*>(&col_pass<T, COL_PLAIN, BAT>),
-                       reinterpret_cast<const void*>(&col_pass<T, COL_STAGE_A, BAT>),
-                       reinterpret_cast<const void*>(&col_pass<T, COL_STAGE_B, BAT>),
-                       reinterpret_cast<const void*>(&col_pass<T, COL_ETD1, BAT>)};
-  for (const void* f : fns) HIP_TRY(hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, b));
-  return EIFE_OK;
-}
-
-template <typename T>
-int set_lds_attrs(size_t bytes) {
-  if (bytes <= 65536) return EIFE_OK;
-  const int r = set_lds_attrs_v<T, false>(int(bytes));
-  if (r != EIFE_OK) return r;
-  return set_lds_attrs_v<T, true>(int(bytes));
-}
-
 hipEvent_t take_event(eife_grid_s* g) {
   if (!g->ev_pool.empty()) {
     hipEvent_t e = g->ev_pool.back();
@@ -444,524 +303,6 @@ int prof_collect(eife_grid_s* g) {
 // class (a batch): `count` instances, per-instance pointers and tables in
 // the device tables `rinst` / `cinst` (null for a single grid).  `var`
 // selects a launch shape (pairs per block) among the tuned variants.
-
-// Pairs per block of the specialised kernels: the largest power of two whose
-// LDS regions fit the budget (64 KB rows, 80 KB columns = two blocks per CU),
-// capped so row blocks stay within 512 threads and column tiles at 128-byte
-// row segments.  Variant 1 halves it.
-template <typename T, int L>
-constexpr int pb_fit(int budget, int cap) {
-  int pb = 1;
-  while (pb < cap && size_t(2 * pb) * fast::Line<T, L>::BUF * sizeof(Cx<T>) <= size_t(budget)) pb *= 2;
-  return pb;
-}
-template <typename T, int L>
-constexpr int row_pb(int var) {
-  constexpr int cap = std::min(16, 512 / fast::Line<T, L>::LP);
-  constexpr int pb = pb_fit<T, L>(65536, cap);
-  return var == 0 ? pb : std::max(1, pb / 2);
-}
-template <typename T, int L>
-constexpr int col_pb(int var) {
-  constexpr int pb = pb_fit<T, L>(81920, int(128 / (2 * sizeof(T))));
-  return var == 0 ? pb : std::max(1, pb / 2);
-}
-
-template <typename T, int L, int PB>
-constexpr int col_ppw() {
-  return (PB * fast::Line<T, L>::LP > 512) ? PB * fast::Line<T, L>::LP / 512 : 1;
-}
-
-// Line lengths with specialised kernels (the three-subsequence form of
-// N = 384 needs more registers than double data allows without spilling).
-template <typename T>
-bool fast_len(int N) {
-  return N == 64 || N == 128 || N == 256 || N == 512 || N == 192 || (N == 384 && sizeof(T) == 4);
-}
-
-// Host-side checks of a specialised launch: the argument blocks fit the
-// kernel-argument segment, block sizes are within the limits (a block may be a
-// fraction of a wavefront: one 16-lane line pair), static LDS fits a workgroup
-// (160 KB on gfx950), and the grid is non-empty and within range.  A failed
-// check skips the launch and is reported by launch_row / launch_col.
-static_assert(3 * sizeof(void*) + sizeof(RowGeom) + sizeof(void*) + sizeof(Forcing) + sizeof(void*) <= 1024,
-              "row pass arguments");
-static_assert(2 * sizeof(void*) + sizeof(ColGeom) + sizeof(void*) + sizeof(Diag) + sizeof(void*) <= 1024,
-              "column pass arguments");
-thread_local const char* g_bad_launch = nullptr;
-
-bool launch_shape_ok(dim3 grid, int threads, size_t lds_static) {
-  const bool ok = grid.x >= 1 && grid.y >= 1 && grid.z >= 1 && grid.x <= 0x7fffffffu && grid.y <= 65535u &&
-                  grid.z <= 65535u && threads >= 1 && threads <= 1024 && lds_static <= 160 * 1024;
-  if (!ok) g_bad_launch = "specialised pass launch shape out of range";
-  return ok;
-}
-
-template <typename T, int L, int PB, bool BAT>
-void row_fast_go(int mode, int nrows, int count, hipStream_t s, const T* src, T* dst, T* dst2, const RowGeom& rg,
-                 const Cx<T>* tw, const Forcing& F, const RowInst<T>* ri) {
-  constexpr int NT = PB * fast::Line<T, L>::LP;
-  dim3 grid((nrows + 2 * PB - 1) / (2 * PB), count);
-  if (!launch_shape_ok(grid, NT, size_t(PB) * fast::Line<T, L>::BUF * sizeof(Cx<T>))) return;
-  if (mode == ROW_PHYS) {
-    if (F.kind == FK_AC)
-      hipLaunchKernelGGL((fast::row_fast<T, L, PB, ROW_PHYS, fast::RK_AC, BAT>), grid, dim3(NT), 0, s, src, dst,
-                         dst2, rg, tw, F, ri);
-    else
-      hipLaunchKernelGGL((fast::row_fast<T, L, PB, ROW_PHYS, fast::RK_GENERIC, BAT>), grid, dim3(NT), 0, s, src,
-                         dst, dst2, rg, tw, F, ri);
-  } else if (mode == ROW_FWD_PHYS) {
-    if (F.kind == FK_AC)
-      hipLaunchKernelGGL((fast::row_fast<T, L, PB, ROW_FWD_PHYS, fast::RK_AC, BAT>), grid, dim3(NT), 0, s, src, dst,
-                         dst2, rg, tw, F, ri);
-    else
-      hipLaunchKernelGGL((fast::row_fast<T, L, PB, ROW_FWD_PHYS, fast::RK_GENERIC, BAT>), grid, dim3(NT), 0, s, src,
-                         dst, dst2, rg, tw, F, ri);
-  } else if (mode == ROW_FWD_USER) {
-    hipLaunchKernelGGL((fast::row_fast<T, L, PB, ROW_FWD_USER, fast::RK_GENERIC, BAT>), grid, dim3(NT), 0, s, src,
-                       dst, dst2, rg, tw, F, ri);
-  } else if (mode == ROW_INV_CHG) {
-    if constexpr (fast::Line<T, L>::LP == 64 && !BAT)
-      hipLaunchKernelGGL((fast::row_fast<T, L, PB, ROW_INV_CHG, fast::RK_GENERIC, BAT>), grid, dim3(NT), 0, s, src,
-                         dst, dst2, rg, tw, F, ri);
-  } else {
-    hipLaunchKernelGGL((fast::row_fast<T, L, PB, ROW_INV_USER, fast::RK_GENERIC, BAT>), grid, dim3(NT), 0, s, src,
-                       dst, dst2, rg, tw, F, ri);
-  }
-}
-
-template <typename T, int L>
-void row_fast_launch(int var, int mode, int nrows, int count, hipStream_t s, const T* src, T* dst, T* dst2,
-                     const RowGeom& rg, const Cx<T>* tw, const Forcing& F, const RowInst<T>* ri) {
-  if (ri) {
-    if (var == 0)
-      row_fast_go<T, L, row_pb<T, L>(0), true>(mode, nrows, count, s, src, dst, dst2, rg, tw, F, ri);
-    else
-      row_fast_go<T, L, row_pb<T, L>(1), true>(mode, nrows, count, s, src, dst, dst2, rg, tw, F, ri);
-  } else {
-    // a single grid with few rows (2D grids up to N = 512): fewer pairs per
-    // block so that the launch spreads over the compute units
-    constexpr int pb0 = row_pb<T, L>(0);
-    constexpr int pbs = std::max(1, pb0 / 4);
-    if ((nrows + 2 * pb0 - 1) / (2 * pb0) < g_cus)
-      row_fast_go<T, L, pbs, false>(mode, nrows, count, s, src, dst, dst2, rg, tw, F, ri);
-    else
-      row_fast_go<T, L, pb0, false>(mode, nrows, count, s, src, dst, dst2, rg, tw, F, ri);
-  }
-}
-
-template <typename T, int L, int PB, bool BAT>
-void col_fast_go(int mode, int pitch, int outer, int count, bool pipe, hipStream_t s, T* W, T* H, const ColGeom& cg,
-                 const Cx<T>* tw, const Diag& dg, const ColInst<T>* ci) {
-  constexpr int PPW = col_ppw<T, L, PB>();
-  constexpr int NT = PB / PPW * fast::Line<T, L>::LP;
-  dim3 grid(pitch / (2 * PB), outer, count);
-  if (!launch_shape_ok(grid, NT, size_t(PB) * fast::Line<T, L>::BUF * sizeof(Cx<T>))) return;
-  if (mode == COL_PLAIN) {
-    // FP32: the persistent pass that prefetches each next tile; FP64 one tile
-    // per block (the prefetch registers would leave three waves per SIMD, one
-    // block per CU, where one tile per block fits two blocks: measured faster)
-    if (pipe && !ci && sizeof(T) == 4) {
-      const int ntx = pitch / (2 * PB);
-      const int ntiles = ntx * outer;
-      constexpr int lds = PB * fast::Line<T, L>::BUF * int(sizeof(Cx<T>));
-      constexpr int per_cu = std::max(1, std::min(kPipeBlocksPerCu, 160 * 1024 / lds));
-      const int nblk = std::min(ntiles, g_cus * per_cu);
-      hipLaunchKernelGGL((fast::col_pipe<T, L, PB, PPW>), dim3(nblk), dim3(NT), 0, s, W, cg, tw, ntx, ntiles);
-    } else {
-      hipLaunchKernelGGL((fast::col_fast<T, L, PB, PPW, COL_PLAIN, BAT>), grid, dim3(NT), 0, s, W, H, cg, tw, dg, ci);
-    }
-    return;
-  }
-  // FP32 power-of-two lines up to 512 points: the persistent pipelined stage
-  // pass fits 4 waves per SIMD without spilling; longer, radix-3 or FP64 lines
-  // keep one tile per block
-  if constexpr (!BAT && sizeof(T) == 4 && fast::IsPow2<L>::value && L <= 512) {
-    // many tiles per resident block: the persistent pipelined stage pass
-    const int ntx = pitch / (2 * PB);
-    const int ntiles = ntx * outer;
-    constexpr int lds = PB * fast::Line<T, L>::BUF * int(sizeof(Cx<T>));
-    constexpr int per_cu = std::max(1, std::min(kPipeBlocksPerCu, 160 * 1024 / lds));
-    const int nblk = g_cus * per_cu;
-    if (pipe && ntiles >= kStagePipeMinTiles * nblk && mode < COL_S3_1) {
-      if (mode == COL_STAGE_A)
-        hipLaunchKernelGGL((fast::col_stage_pipe<T, L, PB, PPW, COL_STAGE_A>), dim3(nblk), dim3(NT), 0, s, W, H, cg,
-                           tw, dg, ntx, ntiles, (const ColInst<T>*)nullptr, 0);
-      else if (mode == COL_STAGE_B)
-        hipLaunchKernelGGL((fast::col_stage_pipe<T, L, PB, PPW, COL_STAGE_B>), dim3(nblk), dim3(NT), 0, s, W, H, cg,
-                           tw, dg, ntx, ntiles, (const ColInst<T>*)nullptr, 0);
-      else
-        hipLaunchKernelGGL((fast::col_stage_pipe<T, L, PB, PPW, COL_ETD1>), dim3(nblk), dim3(NT), 0, s, W, H, cg,
-                           tw, dg, ntx, ntiles, (const ColInst<T>*)nullptr, 0);
-      return;
-    }
-  }
-  // batched FP32 classes, column variant 2: the pipelined stage pass over
-  // every tile of every instance (faster for 1024-point lines, where one
-  // 8-wave block fills a CU; slower for 768-point lines: the autotuner decides)
-  if constexpr (BAT && sizeof(T) == 4) {
-    if (pipe && ci && (mode == COL_STAGE_A || mode == COL_STAGE_B || mode == COL_ETD1)) {
-      const int ntx = pitch / (2 * PB);
-      const int tpi = ntx * outer;
-      const int ntiles = tpi * count;
-      auto go = [&](auto kern) {
-        static int per_cu = 0;
-        if (per_cu == 0 &&
-            hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, reinterpret_cast<const void*>(kern), NT, 0) !=
-                hipSuccess)
-          per_cu = 1;
-        const int nblk = std::min(ntiles, g_cus * std::max(1, per_cu));
-        if (!launch_shape_ok(dim3(nblk), NT, size_t(PB) * fast::Line<T, L>::BUF * sizeof(Cx<T>))) return;
-        hipLaunchKernelGGL(kern, dim3(nblk), dim3(NT), 0, s, W, H, cg, tw, dg, ntx, ntiles, ci, tpi);
-      };
-      if (mode == COL_STAGE_A)
-        go(fast::col_stage_pipe<T, L, PB, PPW, COL_STAGE_A, true>);
-      else if (mode == COL_STAGE_B)
-        go(fast::col_stage_pipe<T, L, PB, PPW, COL_STAGE_B, true>);
-      else
-        go(fast::col_stage_pipe<T, L, PB, PPW, COL_ETD1, true>);
-      return;
-    }
-  }
-  if constexpr (!BAT) {
-    if (mode == COL_S3_1 || mode == COL_S3_2 || mode == COL_S3_3) {
-      if (mode == COL_S3_1)
-        hipLaunchKernelGGL((fast::col_fast<T, L, PB, PPW, COL_S3_1, false>), grid, dim3(NT), 0, s, W, H, cg, tw, dg, ci);
-      else if (mode == COL_S3_2)
-        hipLaunchKernelGGL((fast::col_fast<T, L, PB, PPW, COL_S3_2, false>), grid, dim3(NT), 0, s, W, H, cg, tw, dg, ci);
-      else
-        hipLaunchKernelGGL((fast::col_fast<T, L, PB, PPW, COL_S3_3, false>), grid, dim3(NT), 0, s, W, H, cg, tw, dg, ci);
-      return;
-    }
-  }
-  if (mode == COL_STAGE_A) {
-    hipLaunchKernelGGL((fast::col_fast<T, L, PB, PPW, COL_STAGE_A, BAT>), grid, dim3(NT), 0, s, W, H, cg, tw, dg, ci);
-  } else if (mode == COL_STAGE_B) {
-    hipLaunchKernelGGL((fast::col_fast<T, L, PB, PPW, COL_STAGE_B, BAT>), grid, dim3(NT), 0, s, W, H, cg, tw, dg, ci);
-  } else {
-    hipLaunchKernelGGL((fast::col_fast<T, L, PB, PPW, COL_ETD1, BAT>), grid, dim3(NT), 0, s, W, H, cg, tw, dg, ci);
-  }
-}
-
-template <typename T, int L>
-void col_fast_launch(int var, int mode, int pitch, int outer, int count, hipStream_t s, T* W, T* H,
-                     const ColGeom& cg, const Cx<T>* tw, const Diag& dg, const ColInst<T>* ci) {
-  if (ci) {
-    // batched variants: 0 / 1 the two tile widths (one tile per block), 2 / 3
-    // the same widths in the persistent pipelined stage pass
-    if (var == 1 || var == 3)
-      col_fast_go<T, L, col_pb<T, L>(1), true>(mode, pitch, outer, count, var == 3, s, W, H, cg, tw, dg, ci);
-    else
-      col_fast_go<T, L, col_pb<T, L>(0), true>(mode, pitch, outer, count, var == 2, s, W, H, cg, tw, dg, ci);
-  } else {
-    // a single grid with few column tiles (2D grids): narrower tiles
-    constexpr int pb0 = col_pb<T, L>(0);
-    constexpr int pbs = std::max(1, pb0 / 8);
-    if ((pitch / (2 * pb0)) * outer < g_cus)
-      col_fast_go<T, L, pbs, false>(mode, pitch, outer, count, true, s, W, H, cg, tw, dg, ci);
-    else
-      col_fast_go<T, L, pb0, false>(mode, pitch, outer, count, true, s, W, H, cg, tw, dg, ci);
-  }
-}
-
-// FP32 lines of 256 intervals on 3D grids take the folded passes
-// (eife_fold.hpp) where the launch fills the chip: from two 16-pair column tiles
-// or 16 wavefronts of eight rows per compute unit.  Smaller launches last as
-// long as one wavefront's work, and the folded wavefront holds four line pairs
-// against one (255^2: x pass 9 against 4 us, stage passes 14 against 6.5 us; at
-// 255^3: x pass 39 against 43 us, stage passes 61-66 against 72-78 us).
-template <typename T>
-bool fold_cols(const eife_grid_s* g, int axis, int outer) {
-  return sizeof(T) == 4 && g->d == 3 && g->N[axis] == 256 && (g->pitch / 32) * int64_t(outer) >= 2 * g_cus;
-}
-template <typename T>
-bool fold_rows(const eife_grid_s* g) {
-  return sizeof(T) == 4 && g->d == 3 && g->N[0] == 256 && g->nlines_total() >= 16 * 8 * g_cus;
-}
-
-// Periodic lines with wave-local kernels: N = L = 128, 256, 512 (single grids).
-inline bool per_fast_len(int N) { return N == 128 || N == 256 || N == 512; }
-
-template <typename T, int L>
-void row_per_launch(int mode, int nrows, hipStream_t s, const T* src, T* dst, T* dst2, const RowGeom& rg,
-                    const Cx<T>* tw, const Forcing& F) {
-  constexpr int pb0 = row_pb<T, L>(0);
-  constexpr int pbs = std::max(1, pb0 / 4);
-  const bool few = (nrows + 2 * pb0 - 1) / (2 * pb0) < g_cus;
-  auto go = [&](auto pbc) {
-    constexpr int PB = decltype(pbc)::value;
-    constexpr int NT = PB * fast::FftShape<L>::LP;
-    dim3 grid((nrows + 2 * PB - 1) / (2 * PB));
-    if (mode == ROW_PHYS)
-      hipLaunchKernelGGL((fast::row_fast_per<T, L, PB, ROW_PHYS>), grid, dim3(NT), 0, s, src, dst, dst2, rg, tw, F);
-    else if (mode == ROW_FWD_USER)
-      hipLaunchKernelGGL((fast::row_fast_per<T, L, PB, ROW_FWD_USER>), grid, dim3(NT), 0, s, src, dst, dst2, rg, tw, F);
-    else
-      hipLaunchKernelGGL((fast::row_fast_per<T, L, PB, ROW_INV_USER>), grid, dim3(NT), 0, s, src, dst, dst2, rg, tw, F);
-  };
-  if (few)
-    go(std::integral_constant<int, pbs>());
-  else
-    go(std::integral_constant<int, pb0>());
-}
-
-template <typename T>
-bool try_row_fast_per(const eife_grid_s* g, int mode, int count, hipStream_t s, const T* src, T* dst, T* dst2,
-                      const RowGeom& rg, const Cx<T>* tw, const Forcing& F, const RowInst<T>* ri) {
-  if (g->transform != EIFE_TX_FFT || ri || count != 1 || !per_fast_len(g->N[0])) return false;
-  if (mode != ROW_PHYS && mode != ROW_FWD_USER && mode != ROW_INV_USER) return false;
-  switch (g->N[0]) {
-    case 128: row_per_launch<T, 128>(mode, rg.nrows, s, src, dst, dst2, rg, tw, F); return true;
-    case 256: row_per_launch<T, 256>(mode, rg.nrows, s, src, dst, dst2, rg, tw, F); return true;
-    case 512: row_per_launch<T, 512>(mode, rg.nrows, s, src, dst, dst2, rg, tw, F); return true;
-  }
-  return false;
-}
-
-template <typename T, int L>
-void col_per_launch(int mode, int pitch, int outer, hipStream_t s, T* W, T* H, const ColGeom& cg, const Cx<T>* tw,
-                    const Diag& dg) {
-  constexpr int pb0 = col_pb<T, L>(0);
-  constexpr int pbs = std::max(1, pb0 / 8);
-  const bool few = (pitch / (2 * pb0)) * outer < g_cus;
-  auto go = [&](auto pbc) {
-    constexpr int PB = decltype(pbc)::value;
-    constexpr int PPW = col_ppw<T, L, PB>();
-    constexpr int NT = PB / PPW * fast::FftShape<L>::LP;
-    dim3 grid(pitch / (2 * PB), outer);
-    if (mode == COL_PLAIN)
-      hipLaunchKernelGGL((fast::col_fast_per<T, L, PB, PPW, COL_PLAIN>), grid, dim3(NT), 0, s, W, H, cg, tw, dg);
-    else if (mode == COL_PLAIN_INV)
-      hipLaunchKernelGGL((fast::col_fast_per<T, L, PB, PPW, COL_PLAIN_INV>), grid, dim3(NT), 0, s, W, H, cg, tw, dg);
-    else if (mode == COL_STAGE_A)
-      hipLaunchKernelGGL((fast::col_fast_per<T, L, PB, PPW, COL_STAGE_A>), grid, dim3(NT), 0, s, W, H, cg, tw, dg);
-    else if (mode == COL_STAGE_B)
-      hipLaunchKernelGGL((fast::col_fast_per<T, L, PB, PPW, COL_STAGE_B>), grid, dim3(NT), 0, s, W, H, cg, tw, dg);
-    else
-      hipLaunchKernelGGL((fast::col_fast_per<T, L, PB, PPW, COL_ETD1>), grid, dim3(NT), 0, s, W, H, cg, tw, dg);
-  };
-  if (few)
-    go(std::integral_constant<int, pbs>());
-  else
-    go(std::integral_constant<int, pb0>());
-}
-
-template <typename T>
-bool try_col_fast_per(const eife_grid_s* g, int axis, int mode, int outer, int count, hipStream_t s, T* W, T* H,
-                      const ColGeom& cg, const Cx<T>* tw, const Diag& dg, const ColInst<T>* ci) {
-  if (g->transform != EIFE_TX_FFT || ci || count != 1 || !per_fast_len(g->N[axis]) || mode >= COL_S3_1) return false;
-  switch (g->N[axis]) {
-    case 128: col_per_launch<T, 128>(mode, g->pitch, outer, s, W, H, cg, tw, dg); return true;
-    case 256: col_per_launch<T, 256>(mode, g->pitch, outer, s, W, H, cg, tw, dg); return true;
-    case 512: col_per_launch<T, 512>(mode, g->pitch, outer, s, W, H, cg, tw, dg); return true;
-  }
-  return false;
-}
-
-// Lines of 1024, 2048 and 4096 intervals (2048-, 4096- and 8192-point odd
-// extensions): one line pair per block (eife_long.hpp); single grids,
-// non-periodic.
-inline bool long_len(int N) { return N == 1024 || N == 2048 || N == 4096; }
-
-template <typename T, int L>
-void row_long_launch(int mode, int nrows, hipStream_t s, const T* src, T* dst, T* dst2, const RowGeom& rg,
-                     const Cx<T>* tw, const Forcing& F) {
-  constexpr int NT = lng::Shape<L>::NT;
-  const dim3 grid((nrows + 1) / 2);
-  if (!launch_shape_ok(grid, NT, lng::Shape<L>::BUF * sizeof(Cx<T>))) return;
-  if (mode == ROW_PHYS) {
-    if (F.kind == FK_AC)
-      hipLaunchKernelGGL((lng::row_long<T, L, ROW_PHYS, fast::RK_AC>), grid, dim3(NT), 0, s, src, dst, dst2, rg, tw, F);
-    else
-      hipLaunchKernelGGL((lng::row_long<T, L, ROW_PHYS, fast::RK_GENERIC>), grid, dim3(NT), 0, s, src, dst, dst2, rg, tw,
-                         F);
-  } else if (mode == ROW_FWD_USER) {
-    hipLaunchKernelGGL((lng::row_long<T, L, ROW_FWD_USER, fast::RK_GENERIC>), grid, dim3(NT), 0, s, src, dst, dst2, rg,
-                       tw, F);
-  } else {
-    hipLaunchKernelGGL((lng::row_long<T, L, ROW_INV_USER, fast::RK_GENERIC>), grid, dim3(NT), 0, s, src, dst, dst2, rg,
-                       tw, F);
-  }
-}
-
-template <typename T, int L>
-void col_long_launch(int mode, int pitch, int outer, hipStream_t s, T* W, T* H, const ColGeom& cg, const Cx<T>* tw,
-                     const Diag& dg) {
-  constexpr int NT = lng::Shape<L>::NT;
-  if constexpr (2 * lng::Shape<L>::BUF * sizeof(Cx<T>) <= 160 * 1024) {
-    // two column pairs (a 16- or 32-byte row piece) per block of 2 NT threads (FP32, and FP64 up to
-    // 4096 points); the pitch is a multiple of 32
-    const dim3 grid(pitch / 4, outer);
-    if (!launch_shape_ok(grid, 2 * NT, 2 * lng::Shape<L>::BUF * sizeof(Cx<T>))) return;
-    if (mode == COL_PLAIN)
-      hipLaunchKernelGGL((lng::col_long4<T, L, COL_PLAIN>), grid, dim3(2 * NT), 0, s, W, H, cg, tw, dg);
-    else if (mode == COL_STAGE_A)
-      hipLaunchKernelGGL((lng::col_long4<T, L, COL_STAGE_A>), grid, dim3(2 * NT), 0, s, W, H, cg, tw, dg);
-    else if (mode == COL_STAGE_B)
-      hipLaunchKernelGGL((lng::col_long4<T, L, COL_STAGE_B>), grid, dim3(2 * NT), 0, s, W, H, cg, tw, dg);
-    else
-      hipLaunchKernelGGL((lng::col_long4<T, L, COL_ETD1>), grid, dim3(2 * NT), 0, s, W, H, cg, tw, dg);
-  } else {
-    const dim3 grid(pitch / 2, outer);
-    if (!launch_shape_ok(grid, NT, lng::Shape<L>::BUF * sizeof(Cx<T>))) return;
-    if (mode == COL_PLAIN)
-      hipLaunchKernelGGL((lng::col_long<T, L, COL_PLAIN>), grid, dim3(NT), 0, s, W, H, cg, tw, dg);
-    else if (mode == COL_STAGE_A)
-      hipLaunchKernelGGL((lng::col_long<T, L, COL_STAGE_A>), grid, dim3(NT), 0, s, W, H, cg, tw, dg);
-    else if (mode == COL_STAGE_B)
-      hipLaunchKernelGGL((lng::col_long<T, L, COL_STAGE_B>), grid, dim3(NT), 0, s, W, H, cg, tw, dg);
-    else
-      hipLaunchKernelGGL((lng::col_long<T, L, COL_ETD1>), grid, dim3(NT), 0, s, W, H, cg, tw, dg);
-  }
-}
-
-template <typename T>
-bool try_row_fast(const eife_grid_s* g, int var, int mode, int count, hipStream_t s, const T* src, T* dst, T* dst2,
-                  const RowGeom& rg, const Cx<T>* tw, const Forcing& F, const RowInst<T>* ri) {
-  if (g->per[0]) return try_row_fast_per<T>(g, mode, count, s, src, dst, dst2, rg, tw, F, ri);
-  // the traveling wave's boundary code runs in the generic row pass only
-  if (g->transform != EIFE_TX_FFT || F.kind == FK_EX52) return false;
-  if (long_len(g->N[0])) {
-    if (count != 1 || ri || (mode != ROW_PHYS && mode != ROW_FWD_USER && mode != ROW_INV_USER)) return false;
-    if (g->N[0] == 1024)
-      row_long_launch<T, 2048>(mode, rg.nrows, s, src, dst, dst2, rg, tw, F);
-    else if (g->N[0] == 2048)
-      row_long_launch<T, 4096>(mode, rg.nrows, s, src, dst, dst2, rg, tw, F);
-    else
-      row_long_launch<T, 8192>(mode, rg.nrows, s, src, dst, dst2, rg, tw, F);
-    return true;
-  }
-  if constexpr (sizeof(T) == 4) {
-    if (mode == ROW_PHYS && !ri && fold_rows<T>(g)) {
-      fold::row_launch(rg.nrows, s, dst, rg, tw, F);
-      return true;
-    }
-  }
-  if (!fast_len<T>(g->N[0])) return false;
-  switch (g->N[0]) {
-    case 64: row_fast_launch<T, 128>(var, mode, rg.nrows, count, s, src, dst, dst2, rg, tw, F, ri); return true;
-    case 128: row_fast_launch<T, 256>(var, mode, rg.nrows, count, s, src, dst, dst2, rg, tw, F, ri); return true;
-    case 256: row_fast_launch<T, 512>(var, mode, rg.nrows, count, s, src, dst, dst2, rg, tw, F, ri); return true;
-    case 512: row_fast_launch<T, 1024>(var, mode, rg.nrows, count, s, src, dst, dst2, rg, tw, F, ri); return true;
-    case 192: row_fast_launch<T, 384>(var, mode, rg.nrows, count, s, src, dst, dst2, rg, tw, F, ri); return true;
-    case 384:
-      if constexpr (sizeof(T) == 4) {
-        row_fast_launch<T, 768>(var, mode, rg.nrows, count, s, src, dst, dst2, rg, tw, F, ri);
-        return true;
-      }
-      return false;
-  }
-  return false;
-}
-
-template <typename T>
-bool try_col_fast(const eife_grid_s* g, int var, int axis, int mode, int outer, int count, hipStream_t s, T* W, T* H,
-                  const ColGeom& cg, const Cx<T>* tw, const Diag& dg, const ColInst<T>* ci) {
-  if (g->per[axis]) return try_col_fast_per<T>(g, axis, mode, outer, count, s, W, H, cg, tw, dg, ci);
-  if (g->transform != EIFE_TX_FFT) return false;
-  if (long_len(g->N[axis])) {
-    if (count != 1 || ci || mode > COL_ETD1) return false;
-    if (g->N[axis] == 1024)
-      col_long_launch<T, 2048>(mode, g->pitch, outer, s, W, H, cg, tw, dg);
-    else if (g->N[axis] == 2048)
-      col_long_launch<T, 4096>(mode, g->pitch, outer, s, W, H, cg, tw, dg);
-    else
-      col_long_launch<T, 8192>(mode, g->pitch, outer, s, W, H, cg, tw, dg);
-    return true;
-  }
-  if constexpr (sizeof(T) == 4) {
-    if (!ci && fold_cols<T>(g, axis, outer)) {
-      fold::col_launch(g_cus, mode, g->pitch, outer, s, W, H, cg, tw, dg);
-      return true;
-    }
-  }
-  if (!fast_len<T>(g->N[axis])) return false;
-  switch (g->N[axis]) {
-    case 64: col_fast_launch<T, 128>(var, mode, g->pitch, outer, count, s, W, H, cg, tw, dg, ci); return true;
-    case 128: col_fast_launch<T, 256>(var, mode, g->pitch, outer, count, s, W, H, cg, tw, dg, ci); return true;
-    case 256: col_fast_launch<T, 512>(var, mode, g->pitch, outer, count, s, W, H, cg, tw, dg, ci); return true;
-    case 512: col_fast_launch<T, 1024>(var, mode, g->pitch, outer, count, s, W, H, cg, tw, dg, ci); return true;
-    case 192: col_fast_launch<T, 384>(var, mode, g->pitch, outer, count, s, W, H, cg, tw, dg, ci); return true;
-    case 384:
-      if constexpr (sizeof(T) == 4) {
-        col_fast_launch<T, 768>(var, mode, g->pitch, outer, count, s, W, H, cg, tw, dg, ci);
-        return true;
-      }
-      return false;
-  }
-  return false;
-}
-
-template <typename T, bool BATR, int NT = kThreads>
-void row_generic_go(int mode, dim3 grid, size_t shm, hipStream_t s, const T* src, T* dst, T* dst2, const RowGeom& rg,
-                    const Cx<T>* tw, const Forcing& F, const RowInst<T>* ri) {
-  if (mode == ROW_PHYS)
-    hipLaunchKernelGGL((row_pass<T, ROW_PHYS, BATR, NT>), grid, dim3(NT), shm, s, src, dst, dst2, rg, tw, F, ri);
-  else if (mode == ROW_FWD_USER)
-    hipLaunchKernelGGL((row_pass<T, ROW_FWD_USER, BATR, NT>), grid, dim3(NT), shm, s, src, dst, dst2, rg, tw, F, ri);
-  else
-    hipLaunchKernelGGL((row_pass<T, ROW_INV_USER, BATR, NT>), grid, dim3(NT), shm, s, src, dst, dst2, rg, tw, F, ri);
-}
-
-template <typename T, bool BATC, int NT = kThreads>
-void col_generic_go(int mode, dim3 grid, size_t shm, hipStream_t s, T* W, T* H, const ColGeom& cg, const Cx<T>* tw,
-                    const Diag& dg, const ColInst<T>* ci) {
-  if constexpr (!BATC) {
-    if (mode == COL_S3_1) {
-      hipLaunchKernelGGL((col_pass<T, COL_S3_1, false, NT>), grid, dim3(NT), shm, s, W, H, cg, tw, dg, ci);
-      return;
-    }
-    if (mode == COL_S3_2) {
-      hipLaunchKernelGGL((col_pass<T, COL_S3_2, false, NT>), grid, dim3(NT), shm, s, W, H, cg, tw, dg, ci);
-      return;
-    }
-    if (mode == COL_S3_3) {
-      hipLaunchKernelGGL((col_pass<T, COL_S3_3, false, NT>), grid, dim3(NT), shm, s, W, H, cg, tw, dg, ci);
-      return;
-    }
-  }
-  if (mode == COL_PLAIN)
-    hipLaunchKernelGGL((col_pass<T, COL_PLAIN, BATC, NT>), grid, dim3(NT), shm, s, W, H, cg, tw, dg, ci);
-  else if (mode == COL_STAGE_A)
-    hipLaunchKernelGGL((col_pass<T, COL_STAGE_A, BATC, NT>), grid, dim3(NT), shm, s, W, H, cg, tw, dg, ci);
-  else if (mode == COL_STAGE_B)
-    hipLaunchKernelGGL((col_pass<T, COL_STAGE_B, BATC, NT>), grid, dim3(NT), shm, s, W, H, cg, tw, dg, ci);
-  else
-    hipLaunchKernelGGL((col_pass<T, COL_ETD1, BATC, NT>), grid, dim3(NT), shm, s, W, H, cg, tw, dg, ci);
-}
-
-// Periodic lines (generic passes only).
-template <typename T, int NT = kThreads>
-void row_periodic_go(int mode, dim3 grid, size_t shm, hipStream_t s, const T* src, T* dst, T* dst2,
-                     const RowGeom& rg, const Cx<T>* tw, const Forcing& F) {
-  if (mode == ROW_PHYS)
-    hipLaunchKernelGGL((row_pass_per<T, ROW_PHYS, NT>), grid, dim3(NT), shm, s, src, dst, dst2, rg, tw, F);
-  else if (mode == ROW_FWD_USER)
-    hipLaunchKernelGGL((row_pass_per<T, ROW_FWD_USER, NT>), grid, dim3(NT), shm, s, src, dst, dst2, rg, tw, F);
-  else
-    hipLaunchKernelGGL((row_pass_per<T, ROW_INV_USER, NT>), grid, dim3(NT), shm, s, src, dst, dst2, rg, tw, F);
-}
-
-template <typename T, int NT = kThreads>
-void col_periodic_go(int mode, dim3 grid, size_t shm, hipStream_t s, T* W, T* H, const ColGeom& cg,
-                     const Cx<T>* tw, const Diag& dg) {
-  if (mode == COL_PLAIN)
-    hipLaunchKernelGGL((col_pass_per<T, COL_PLAIN, NT>), grid, dim3(NT), shm, s, W, H, cg, tw, dg);
-  else if (mode == COL_PLAIN_INV)
-    hipLaunchKernelGGL((col_pass_per<T, COL_PLAIN_INV, NT>), grid, dim3(NT), shm, s, W, H, cg, tw, dg);
-  else if (mode == COL_STAGE_A)
-    hipLaunchKernelGGL((col_pass_per<T, COL_STAGE_A, NT>), grid, dim3(NT), shm, s, W, H, cg, tw, dg);
-  else if (mode == COL_STAGE_B)
-    hipLaunchKernelGGL((col_pass_per<T, COL_STAGE_B, NT>), grid, dim3(NT), shm, s, W, H, cg, tw, dg);
-  else if (mode == COL_S3_1)
-    hipLaunchKernelGGL((col_pass_per<T, COL_S3_1, NT>), grid, dim3(NT), shm, s, W, H, cg, tw, dg);
-  else if (mode == COL_S3_2)
-    hipLaunchKernelGGL((col_pass_per<T, COL_S3_2, NT>), grid, dim3(NT), shm, s, W, H, cg, tw, dg);
-  else if (mode == COL_S3_3)
-    hipLaunchKernelGGL((col_pass_per<T, COL_S3_3, NT>), grid, dim3(NT), shm, s, W, H, cg, tw, dg);
-  else
-    hipLaunchKernelGGL((col_pass_per<T, COL_ETD1, NT>), grid, dim3(NT), shm, s, W, H, cg, tw, dg);
-}
 
 // ---------------------------------------------------------------------------
 // Split-BF16 matrix-core transform (single grids, FP32).
@@ -1140,8 +481,22 @@ struct Batchlet {
   const void* rinst = nullptr;  // RowInst<T>[count] (device) or null
   const void* cinst = nullptr;  // ColInst<T>[count] (device) or null
   int var_row = 0, var_col = 0;  // tuned launch variants
-  int prow = 0, pcol = 0;        // generic-kernel pairs per block (0 = the grid's default)
+  int prow = 0, pcol = 0;        // mixed-radix passes: pairs per block (0 = the grid's default)
 };
+
+// Pairs per block (log2) of a mixed-radix launch: the tuned number, else the grid's
+// widest block, halved while the launch has fewer blocks than compute units (blocks(q)
+// for 2^q pairs); the results do not depend on it.
+template <typename F>
+int mix_lp(int tuned, int widest, F blocks) {
+  int lp = widest;
+  if (tuned > 0) {
+    for (lp = 0; (2 << lp) <= tuned;) ++lp;
+    return lp;
+  }
+  while (lp > 0 && blocks(lp) < g_cus) --lp;
+  return lp;
+}
 
 template <typename T>
 int launch_row(eife_grid_s* g, int mode, const T* src, int64_t ld_src, T* dst, int64_t ld_dst, T* dst2,
@@ -1155,9 +510,6 @@ int launch_row(eife_grid_s* g, int mode, const T* src, int64_t ld_src, T* dst, i
   rg.ny = g->n[1];
   rg.ld_src = ld_src;
   rg.ld_dst = ld_dst;
-  rg.pl = g->plan[0];
-  rg.P = B.prow > 0 ? B.prow : g->prow;
-  rg.ls = rg.pl.L + 1;
   const RowInst<T>* ri = static_cast<const RowInst<T>*>(B.rinst);
   const Cx<T>* tw = reinterpret_cast<const Cx<T>*>(g->tw[0]);
   const int pidx = prof_begin(g, mode == ROW_PHYS ? EIFE_PASS_ROW_PHYS
@@ -1167,21 +519,10 @@ int launch_row(eife_grid_s* g, int mode, const T* src, int64_t ld_src, T* dst, i
   g_bad_launch = nullptr;
   if (!(B.count == 1 && !ri && try_row_gemm<T>(g, mode, s, src, dst, dst2, rg, F)) &&
       !try_row_fast<T>(g, B.var_row, mode, B.count, s, src, dst, dst2, rg, tw, F, ri)) {
-    const size_t shm = lds_bytes(g, rg.P, rg.pl.L);
-    dim3 grid((rg.nrows + 2 * rg.P - 1) / (2 * rg.P), B.count);
-    if (g->per[0]) {
-      if (ri || mode == ROW_FWD_PHYS) return fail(EIFE_EUNSUPPORTED, "periodic row pass variant");
-      if (long_lines<T>(rg.pl.L))
-        row_periodic_go<T, kLongThreads>(mode, grid, shm, s, src, dst, dst2, rg, tw, F);
-      else
-        row_periodic_go<T>(mode, grid, shm, s, src, dst, dst2, rg, tw, F);
-    } else if (ri)
-      row_generic_go<T, true>(mode, grid, shm, s, src, dst, dst2, rg, tw, F, ri);
-    else
-      if (long_lines<T>(rg.pl.L))
-        row_generic_go<T, false, kLongThreads>(mode, grid, shm, s, src, dst, dst2, rg, tw, F, ri);
-      else
-        row_generic_go<T, false>(mode, grid, shm, s, src, dst, dst2, rg, tw, F, ri);
+    if (g->per[0] && (ri || mode == ROW_FWD_PHYS)) return fail(EIFE_EUNSUPPORTED, "periodic row pass variant");
+    const int lp = mix_lp(B.prow, g->lp_row, [&](int q) { return int64_t((rg.nrows + (2 << q) - 1) / (2 << q)) * B.count; });
+    if (!mix::row_launch<T>(g->plan[0], lp, g->per[0], mode, B.count, s, src, dst, dst2, rg, tw, F, ri))
+      return fail(EIFE_EINVAL, "mixed-radix row pass shape");
   }
   if (g_bad_launch) return fail(EIFE_EINVAL, "%s", g_bad_launch);
   HIP_TRY(hipGetLastError());
@@ -1210,10 +551,6 @@ int launch_col(eife_grid_s* g, int axis, int mode, T* W, T* H, const Diag& dg, h
     cg.last_is_z = 1;
   }
   cg.ncols = g->n[0];
-  cg.pl = g->plan[axis];
-  cg.P = B.pcol > 0 ? B.pcol : g->pcol[axis];
-  while (g->pitch % (2 * cg.P) != 0) cg.P--;
-  cg.ls = cg.pl.L + 1;
   const ColInst<T>* ci = static_cast<const ColInst<T>*>(B.cinst);
   const Cx<T>* tw = reinterpret_cast<const Cx<T>*>(g->tw[axis]);
   int kind = EIFE_PASS_MID;
@@ -1228,21 +565,10 @@ int launch_col(eife_grid_s* g, int axis, int mode, T* W, T* H, const Diag& dg, h
   g_bad_launch = nullptr;
   if ((s3 || !(B.count == 1 && !ci && try_col_gemm<T>(g, axis, mode, outer, s, W, H, cg, dg))) &&
       !try_col_fast<T>(g, B.var_col, axis, mode, outer, B.count, s, W, H, cg, tw, dg, ci)) {
-    const size_t shm = lds_bytes(g, cg.P, cg.pl.L);
-    dim3 grid(g->pitch / (2 * cg.P), outer, B.count);
-    if (g->per[axis]) {
-      if (ci) return fail(EIFE_EUNSUPPORTED, "periodic batched column pass");
-      if (long_lines<T>(cg.pl.L))
-        col_periodic_go<T, kLongThreads>(mode, grid, shm, s, W, H, cg, tw, dg);
-      else
-        col_periodic_go<T>(mode, grid, shm, s, W, H, cg, tw, dg);
-    } else if (ci)
-      col_generic_go<T, true>(mode, grid, shm, s, W, H, cg, tw, dg, ci);
-    else
-      if (long_lines<T>(cg.pl.L))
-        col_generic_go<T, false, kLongThreads>(mode, grid, shm, s, W, H, cg, tw, dg, ci);
-      else
-        col_generic_go<T, false>(mode, grid, shm, s, W, H, cg, tw, dg, ci);
+    if (g->per[axis] && ci) return fail(EIFE_EUNSUPPORTED, "periodic batched column pass");
+    const int lp = mix_lp(B.pcol, g->lp_col[axis], [&](int q) { return int64_t(g->pitch / (2 << q)) * outer * B.count; });
+    if (!mix::col_launch<T>(g->plan[axis], lp, g->per[axis], g->per[0], mode, g->pitch, outer, B.count, s, W, H, cg, tw, dg, ci))
+      return fail(EIFE_EINVAL, "mixed-radix column pass shape");
   }
   if (g_bad_launch) return fail(EIFE_EINVAL, "%s", g_bad_launch);
   HIP_TRY(hipGetLastError());
@@ -1543,7 +869,7 @@ int eife_create_grid(int d, const int32_t* N, const double* h, double D, int bc,
   }
   for (int a = 0; a < 3; ++a) {
     // FFT length: the odd extension (2N) of a sine line, the line itself (N) when periodic
-    if (!factor_plan(g->per[a] ? g->N[a] : 2 * g->N[a], &g->plan[a])) {
+    if (!mix::make_plan(g->per[a] ? g->N[a] : 2 * g->N[a], &g->plan[a])) {
       const int bad = g->N[a];
       delete g;
       return fail(EIFE_EUNSUPPORTED, "N = %d: FFT length has more than three prime factors above 7", bad);
@@ -1569,23 +895,20 @@ int eife_create_grid(int d, const int32_t* N, const double* h, double D, int bc,
   int cus = 0;
   if (hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) == hipSuccess && cus > 0) g_cus = cus;
   // launch shapes
-  g->prow = pick_pairs(g, g->plan[0].L, std::min(16, (g->nlines_total() + 1) / 2));
+  g->lp_row = mix::pick_lp(g->plan[0], int(g->esz), 2);
+  size_t need = mix::lds_bytes(g->plan[0], g->lp_row, int(g->esz));
   for (int a = 1; a < 3; ++a) {
-    int P = pick_pairs(g, g->plan[a].L, 16);
-    while (g->pitch % (2 * P) != 0) P--;
-    g->pcol[a] = P;
+    g->lp_col[a] = mix::pick_lp(g->plan[a], int(g->esz), 3);
+    need = std::max(need, mix::lds_bytes(g->plan[a], g->lp_col[a], int(g->esz)));
   }
-  size_t need = lds_bytes(g, g->prow, g->plan[0].L);
-  for (int a = 1; a < 3; ++a) need = std::max(need, lds_bytes(g, g->pcol[a], g->plan[a].L));
   if (need > g->max_lds) {
     free_grid(g);
     return fail(EIFE_EUNSUPPORTED, "a line of this grid needs %zu bytes of LDS, device allows %zu", need,
                 g->max_lds);
   }
-  const int r = dtype == EIFE_F32 ? set_lds_attrs<float>(need) : set_lds_attrs<double>(need);
-  if (r != EIFE_OK) {
+  if (dtype == EIFE_F32 ? mix::set_attrs<float>(need) : mix::set_attrs<double>(need)) {
     free_grid(g);
-    return r;
+    return fail(EIFE_EHIP, "cannot allow %zu bytes of LDS per block", need);
   }
   const size_t elems = size_t(g->pitch) * g->n[1] * g->n[2];
   if (hipMalloc(&g->W, elems * g->esz) != hipSuccess || hipMalloc(&g->H, elems * g->esz) != hipSuccess) {
@@ -2099,9 +1422,14 @@ int tune_class(eife_batch_s* b, eife_batch_s::Class& c, const char* path, hipStr
   // line pairs per block whose LDS regions fit and whose tiles divide the pitch
   auto valid = [&](const std::array<int, 4>& cd) {
     if (fast) return cd[0] >= 0 && cd[0] < 2 && cd[1] >= 0 && cd[1] < ncol && cd[2] == 0 && cd[3] == 0;
-    return cd[0] == 0 && cd[1] == 0 && cd[2] >= 1 && cd[3] >= 1 && cd[2] <= 64 && cd[3] <= 64 && pick_pairs(g, g->plan[0].L, cd[2]) == cd[2] &&
-           pick_pairs(g, g->plan[1].L, cd[3]) == cd[3] && lds_bytes(g, cd[2], g->plan[0].L) <= 65536 &&
-           lds_bytes(g, cd[3], g->plan[1].L) <= 65536 && g->pitch % (2 * cd[3]) == 0;
+    // pairs per block: a power of two whose block fits and whose tiles divide the pitch
+    auto fits = [&](int a, int P) {
+      int jt, pts, lp = 0;
+      while ((2 << lp) <= P) ++lp;
+      return P >= 1 && P <= 16 && (1 << lp) == P && mix::lds_bytes(g->plan[a], lp, int(g->esz)) <= 65536 &&
+             mix::block_shape(g->plan[a], lp, int(g->esz), &jt, &pts);
+    };
+    return cd[0] == 0 && cd[1] == 0 && fits(0, cd[2]) && fits(1, cd[3]) && g->pitch % (2 * cd[3]) == 0;
   };
   int v[4];
   if (tune_lookup(path, key, v) && valid({v[0], v[1], v[2], v[3]})) {

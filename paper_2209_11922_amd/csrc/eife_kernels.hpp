@@ -7,8 +7,9 @@
 // length L = 2N (z_m = c_m, z_{2N-m} = -c_m, z_0 = z_N = 0), a complex FFT of
 // length L gives Z_k = -2i (P a + i P b)_k, so the orthonormal transform
 // S = sqrt(2/N) P is (S a)_k = -Im Z_k / sqrt(2N), (S b)_k = Re Z_k / sqrt(2N).
-// The FFT is a mixed radix-8/4/2/3/5/7 Stockham autosort on lines held in LDS
-// (prime factors above 7 take a direct-DFT stage each).
+// This file holds what the passes share: butterflies, the diagonal stages, the
+// reactions and the argument blocks; the passes themselves are in eife_fast.hpp,
+// eife_fold.hpp, eife_long.hpp and, for any length, eife_mix.hpp.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -150,11 +151,6 @@ struct Dft<T, 7> {
   }
 };
 
-// Per-thread element budget of one in-place Stockham stage: P * L <= kMaxElems * 256
-// (a 256-thread block holds 32 values per thread; the 1024-thread variants for
-// long lines hold 8).
-constexpr int kMaxElems = 32;
-
 // Multiplies input q of a butterfly by g^q, q = 1 .. R - 1 (g = W_L^{k L / (Ns R)}),
 // the powers formed by products at most four deep: one table load per
 // butterfly instead of R - 1.
@@ -166,136 +162,6 @@ __device__ __forceinline__ void twiddle_powers(Cx<T>* v, Cx<T> g) {
   for (int q = 2; q < R; ++q) p[q] = (q & 1) ? cmul(p[q - 1], g) : cmul(p[q / 2], p[q / 2]);
 #pragma unroll
   for (int q = 1; q < R; ++q) v[q] = cmul(v[q], p[q]);
-}
-
-// One radix-R stage on P lines of length L stored at lds + p * ls.  Ns is the
-// product of the radices already applied; tw[j] = exp(-2 pi i j / L).
-template <typename T, int R, int ME>
-__device__ void stockham_stage(Cx<T>* lds, int ls, int L, int P, int Ns, const Cx<T>* __restrict__ tw) {
-  constexpr int MAXB = (ME + R - 1) / R;
-  const int nbf = L / R;
-  const int total = P * nbf;
-  const int tws = L / (Ns * R);
-  Cx<T> v[MAXB][R];
-#pragma unroll
-  for (int s = 0; s < MAXB; ++s) {
-    const int b = threadIdx.x + s * blockDim.x;
-    if (b < total) {
-      const int p = b / nbf;
-      const int j = b - p * nbf;
-      const Cx<T>* line = lds + p * ls;
-      const int k = j % Ns;
-#pragma unroll
-      for (int q = 0; q < R; ++q) v[s][q] = line[j + q * nbf];
-      if (Ns > 1) twiddle_powers<T, R>(v[s], tw[k * tws]);
-      Dft<T, R>::run(v[s]);
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int s = 0; s < MAXB; ++s) {
-    const int b = threadIdx.x + s * blockDim.x;
-    if (b < total) {
-      const int p = b / nbf;
-      const int j = b - p * nbf;
-      const int k = j % Ns;
-      Cx<T>* line = lds + p * ls;
-      const int base = (j - k) * R + k;
-#pragma unroll
-      for (int q = 0; q < R; ++q) line[base + q * Ns] = v[s][q];
-    }
-  }
-  __syncthreads();
-}
-
-struct FftPlan {
-  int L;      // FFT length (2N)
-  int n8, n4, n2, n3, n5, n7;  // number of radix-8, -4, -2, -3, -5 and -7 stages
-  int nd;     // prime factors of L above 7 (at most 3 for L <= 8192), one direct-DFT stage each
-  int dr[3];
-};
-
-// One Stockham stage of a prime radix R > 7 as a direct R-point DFT: output m
-// of butterfly j (k = j mod Ns, nbf = L / R, S = L / (Ns R)) is
-//   sum_q line[j + q nbf] W_L^{q (k S + m nbf)},
-// the input twiddle and the DFT factor in one table entry per term.  The block
-// forms all its outputs in registers (sums in double) before the barrier and
-// writes them after it, so the stage runs in place.  R multiply-adds per
-// output: slow for a large prime, but it makes every N possible.
-template <typename T, int ME>
-__device__ void stockham_stage_dft(Cx<T>* lds, int ls, int L, int P, int Ns, int R, const Cx<T>* __restrict__ tw) {
-  const int nbf = L / R;
-  const int S = L / (Ns * R);
-  const int total = P * L;
-  Cx<T> out[ME];
-  int dst[ME];
-#pragma unroll
-  for (int s = 0; s < ME; ++s) {
-    const int i = int(threadIdx.x) + s * int(blockDim.x);
-    dst[s] = -1;
-    if (i < total) {
-      const int p = i / L;
-      const int r = i - p * L;
-      const int j = r % nbf;
-      const int m = r / nbf;
-      const int k = j % Ns;
-      const Cx<T>* line = lds + p * ls;
-      const int d = k * S + m * nbf;  // < L
-      double re = 0.0, im = 0.0;
-      int e = 0;
-      for (int q = 0; q < R; ++q) {
-        const Cx<T> x = line[j + q * nbf];
-        const Cx<T> w = tw[e];
-        re += double(x.re) * double(w.re) - double(x.im) * double(w.im);
-        im += double(x.re) * double(w.im) + double(x.im) * double(w.re);
-        e += d;
-        if (e >= L) e -= L;
-      }
-      out[s] = Cx<T>{T(re), T(im)};
-      dst[s] = p * ls + (j - k) * R + k + Ns * m;
-    }
-  }
-  __syncthreads();
-#pragma unroll
-  for (int s = 0; s < ME; ++s)
-    if (dst[s] >= 0) lds[dst[s]] = out[s];
-  __syncthreads();
-}
-
-// Forward FFT of P lines in LDS (natural order in and out).  Callers must
-// __syncthreads() before (inputs written) -- stages synchronise internally.
-// ME: values per thread the block's size allows (P * L <= ME * blockDim).
-template <typename T, int ME>
-__device__ void fft_lines(Cx<T>* lds, int ls, int P, FftPlan pl, const Cx<T>* __restrict__ tw) {
-  int Ns = 1;
-  for (int i = 0; i < pl.n8; ++i) {
-    stockham_stage<T, 8, ME>(lds, ls, pl.L, P, Ns, tw);
-    Ns *= 8;
-  }
-  for (int i = 0; i < pl.n4; ++i) {
-    stockham_stage<T, 4, ME>(lds, ls, pl.L, P, Ns, tw);
-    Ns *= 4;
-  }
-  for (int i = 0; i < pl.n2; ++i) {
-    stockham_stage<T, 2, ME>(lds, ls, pl.L, P, Ns, tw);
-    Ns *= 2;
-  }
-  for (int i = 0; i < pl.n3; ++i) {
-    stockham_stage<T, 3, ME>(lds, ls, pl.L, P, Ns, tw);
-    Ns *= 3;
-  }
-  for (int i = 0; i < pl.n5; ++i) {
-    stockham_stage<T, 5, ME>(lds, ls, pl.L, P, Ns, tw);
-    Ns *= 5;
-  }
-  for (int i = 0; i < pl.n7; ++i) {
-    stockham_stage<T, 7, ME>(lds, ls, pl.L, P, Ns, tw);
-    Ns *= 7;
-  }
-  for (int i = 0; i < pl.nd; ++i) {
-    stockham_stage_dft<T, ME>(lds, ls, pl.L, P, Ns, pl.dr[i], tw);
-    Ns *= pl.dr[i];
-  }
 }
 
 // ---------------------------------------------------------------------------
@@ -629,8 +495,7 @@ __device__ __forceinline__ T reaction(const Forcing& F, T u, int ix, int iy, int
 }
 
 // ---------------------------------------------------------------------------
-// Row passes: lines along x (contiguous).  A block handles 2P rows, pair p =
-// rows (r0 + 2p, r0 + 2p + 1).
+// Row passes: lines along x (contiguous).
 // ROW_FWD_PHYS (specialised kernels only): from the nodal values u, dst2 =
 // S_x u and dst = S_x f(u) in one pass (the first reaction of a run).
 // ROW_INV_CHG: ROW_INV_USER that also sums (u - u_n)^2 over each line pair
@@ -643,23 +508,8 @@ struct RowGeom {
   int nrows;     // number of rows (prod of the other axes)
   int ny;        // rows per z-slab (interior nodes along y)
   int64_t ld_src, ld_dst;  // row pitch of source / destination
-  FftPlan pl;
-  int P;         // pairs per block
-  int ls;        // LDS line stride (complex elements)
   double* chg = nullptr;  // ROW_INV_CHG: per line pair sums of (u - u_n)^2
 };
-
-template <typename T>
-__device__ __forceinline__ void zero_lines(Cx<T>* lds, int ls, int P) {
-  for (int i = threadIdx.x; i < P * ls; i += blockDim.x) lds[i] = Cx<T>{T(0), T(0)};
-}
-
-// Scatter value pairs into the odd extension: position k (1..N-1) and L-k.
-template <typename T>
-__device__ __forceinline__ void put_odd(Cx<T>* line, int L, int k, T a, T b) {
-  line[k] = Cx<T>{a, b};
-  line[L - k] = Cx<T>{-a, -b};
-}
 
 // Pointers of a row pass for one instance (batched launches) or the launch's own.
 template <typename T, int MODE>
@@ -681,107 +531,18 @@ __device__ __forceinline__ void row_inst_ptrs(const RowInst<T>* insts, const T*&
   }
 }
 
-template <typename T, int MODE, bool BAT, int NT = 256>
-__global__ void __launch_bounds__(NT) row_pass(const T* src, T* dst, T* dst2, RowGeom g,
-                                                const Cx<T>* __restrict__ tw, Forcing F,
-                                                const RowInst<T>* __restrict__ insts) {
-  if constexpr (BAT) row_inst_ptrs<T, MODE>(insts, src, dst, dst2, F);
-  extern __shared__ unsigned char smem_raw[];
-  Cx<T>* lds = reinterpret_cast<Cx<T>*>(smem_raw);
-  const int n = g.n;
-  const int L = g.pl.L;
-  const int N = L / 2;
-  const int P = g.P;
-  const int r0 = blockIdx.x * 2 * P;
-  const T scale = T(1.0 / sqrt(double(L)));
-
-  zero_lines(lds, g.ls, P);
-  __syncthreads();
-  // load: thread handles (p, m) for both rows of the pair
-  for (int i = threadIdx.x; i < P * n; i += blockDim.x) {
-    const int p = i / n;
-    const int m = i - p * n;
-    const int ra = r0 + 2 * p, rb = ra + 1;
-    T a = T(0), b = T(0);
-    if (ra < g.nrows) a = src[int64_t(ra) * g.ld_src + m];
-    if (rb < g.nrows) b = src[int64_t(rb) * g.ld_src + m];
-    put_odd(lds + p * g.ls, L, m + 1, a, b);
-  }
-  __syncthreads();
-  fft_lines<T, kMaxElems * 256 / NT>(lds, g.ls, P, g.pl, tw);
-
-  if (MODE == ROW_INV_USER) {
-    for (int i = threadIdx.x; i < P * n; i += blockDim.x) {
-      const int p = i / n;
-      const int m = i - p * n;
-      const int ra = r0 + 2 * p, rb = ra + 1;
-      const Cx<T> Z = lds[p * g.ls + m + 1];
-      if (ra < g.nrows) dst[int64_t(ra) * g.ld_dst + m] = -Z.im * scale;
-      if (rb < g.nrows) dst[int64_t(rb) * g.ld_dst + m] = Z.re * scale;
-    }
-    return;
-  }
-  if (MODE == ROW_FWD_USER) {
-    for (int i = threadIdx.x; i < P * n; i += blockDim.x) {
-      const int p = i / n;
-      const int m = i - p * n;
-      const int ra = r0 + 2 * p, rb = ra + 1;
-      const Cx<T> Z = lds[p * g.ls + m + 1];
-      const T va = -Z.im * scale, vb = Z.re * scale;
-      if (ra < g.nrows) {
-        dst[int64_t(ra) * g.ld_dst + m] = va;
-        dst2[int64_t(ra) * g.ld_dst + m] = va;
-      }
-      if (rb < g.nrows) {
-        dst[int64_t(rb) * g.ld_dst + m] = vb;
-        dst2[int64_t(rb) * g.ld_dst + m] = vb;
-      }
-    }
-    return;
-  }
-  // ROW_PHYS: inverse transform -> reaction -> forward transform
-  for (int i = threadIdx.x; i < P * n; i += blockDim.x) {
-    const int p = i / n;
-    const int m = i - p * n;
-    const int ra = r0 + 2 * p, rb = ra + 1;
-    Cx<T>* line = lds + p * g.ls;
-    const Cx<T> Z = line[m + 1];
-    const T ua = -Z.im * scale, ub = Z.re * scale;
-    T fa = T(0), fb = T(0);
-    if (ra < g.nrows) fa = reaction<T>(F, ua, m, ra % g.ny, ra / g.ny);
-    if (rb < g.nrows) fb = reaction<T>(F, ub, m, rb % g.ny, rb / g.ny);
-    put_odd(line, L, m + 1, fa, fb);
-    if (m == 0) {
-      line[0] = Cx<T>{T(0), T(0)};
-      line[N] = Cx<T>{T(0), T(0)};
-    }
-  }
-  __syncthreads();
-  fft_lines<T, kMaxElems * 256 / NT>(lds, g.ls, P, g.pl, tw);
-  for (int i = threadIdx.x; i < P * n; i += blockDim.x) {
-    const int p = i / n;
-    const int m = i - p * n;
-    const int ra = r0 + 2 * p, rb = ra + 1;
-    const Cx<T> Z = lds[p * g.ls + m + 1];
-    if (ra < g.nrows) dst[int64_t(ra) * g.ld_dst + m] = -Z.im * scale;
-    if (rb < g.nrows) dst[int64_t(rb) * g.ld_dst + m] = Z.re * scale;
-  }
-}
-
 // ---------------------------------------------------------------------------
-// Column passes: lines along a strided axis.  A block handles C = 2P adjacent
-// x-columns c0 .. c0 + C - 1 (pair p = columns c0 + 2p, c0 + 2p + 1) of one
-// "outer" index; element m of column c sits at
+// Column passes: lines along a strided axis.  A block handles pairs of adjacent
+// x-columns of one "outer" index; element m of column c sits at
 //   base + outer * ld_outer + m * ld_line + c.
-enum ColMode { COL_PLAIN = 0, COL_STAGE_A = 1, COL_STAGE_B = 2, COL_ETD1 = 3 };
+// COL_PLAIN_INV: the inverse transform of periodic lines (COL_PLAIN is its own
+// inverse on sine lines).
+enum ColMode { COL_PLAIN = 0, COL_STAGE_A = 1, COL_STAGE_B = 2, COL_ETD1 = 3, COL_PLAIN_INV = 4 };
 
 struct ColGeom {
   int n;            // line length
   int64_t ld_line;  // stride between consecutive elements of a line
   int64_t ld_outer; // stride between outer indices
-  FftPlan pl;
-  int P;
-  int ls;
   int last_is_z;    // 1: spectral index (kx, ky, kz) = (c, outer, m); 0: (c, m, 0)
   int ncols;        // real x-columns; columns ncols .. pitch-1 are padding, kept exactly zero
 };
@@ -829,18 +590,6 @@ __device__ __forceinline__ void stage3_pair(const Diag& dg, const S3K& k, const 
   if (MODE == COL_S3_1) *reinterpret_cast<Cx<T>*>(X + off) = mask_pad(Cx<T>{newx[0], newx[1]}, col, ncols);
 }
 
-template <typename T>
-__device__ __forceinline__ void col_inst_ptrs(const ColInst<T>* insts, T*& W, T*& H, Diag& dg) {
-  if (!insts) return;
-  const ColInst<T>& I = insts[blockIdx.z];
-  W = I.W;
-  H = I.H;
-  dg.ax[0] = I.ax[0];
-  dg.ax[1] = I.ax[1];
-  dg.ax[2] = I.ax[2];
-  dg.D = I.D;
-}
-
 // Block order of the generic column passes: the hardware hands linear block b
 // (x fastest) to XCD b mod 8, so adjacent column pairs -- which share 128-byte
 // lines -- would land on different XCDs and each XCD's L2 would fetch the whole
@@ -856,110 +605,6 @@ __device__ __forceinline__ void xcd_block(int& bx, int& by) {
   by = l / int(gridDim.x);
 }
 
-template <typename T, int MODE, bool BAT, int NT = 256>
-__global__ void __launch_bounds__(NT) col_pass(T* W, T* H, ColGeom g, const Cx<T>* __restrict__ tw, Diag dg,
-                                                const ColInst<T>* __restrict__ insts) {
-  if constexpr (BAT) col_inst_ptrs<T>(insts, W, H, dg);
-  extern __shared__ unsigned char smem_raw[];
-  Cx<T>* lds = reinterpret_cast<Cx<T>*>(smem_raw);
-  const int n = g.n;
-  const int L = g.pl.L;
-  const int N = L / 2;
-  const int P = g.P;
-  int bx, outer;
-  xcd_block(bx, outer);
-  const int c0 = bx * 2 * P;
-  const int64_t base = int64_t(outer) * g.ld_outer + c0;
-  const T scale = T(1.0 / sqrt(double(L)));
-
-  zero_lines(lds, g.ls, P);
-  __syncthreads();
-  for (int i = threadIdx.x; i < P * n; i += blockDim.x) {
-    const int m = i / P;
-    const int p = i - m * P;
-    const Cx<T> v = mask_pad(*reinterpret_cast<const Cx<T>*>(W + base + int64_t(m) * g.ld_line + 2 * p), c0 + 2 * p, g.ncols);
-    put_odd(lds + p * g.ls, L, m + 1, v.re, v.im);
-  }
-  __syncthreads();
-  fft_lines<T, kMaxElems * 256 / NT>(lds, g.ls, P, g.pl, tw);
-
-  if (MODE == COL_PLAIN) {
-    for (int i = threadIdx.x; i < P * n; i += blockDim.x) {
-      const int m = i / P;
-      const int p = i - m * P;
-      const Cx<T> Z = lds[p * g.ls + m + 1];
-      *reinterpret_cast<Cx<T>*>(W + base + int64_t(m) * g.ld_line + 2 * p) =
-          mask_pad(Cx<T>{-Z.im * scale, Z.re * scale}, c0 + 2 * p, g.ncols);
-    }
-    return;
-  }
-
-  // diagonal stage in spectral space, then the inverse transform
-  const double tau = dg.tau, c2 = dg.c2, D = dg.D;
-  if constexpr (MODE >= COL_S3_1) {
-    for (int i = threadIdx.x; i < P * n; i += blockDim.x) {
-      const int m = i / P;
-      const int p = i - m * P;
-      Cx<T>* line = lds + p * g.ls;
-      const Cx<T> Z = line[m + 1];
-      T outv[2];
-      Sep3 sxy[2];
-      sep3_pair(dg, c0 + 2 * p, g.last_is_z, outer, sxy);
-      stage3_pair<T, MODE>(dg, s3k_make(dg), sxy, g.last_is_z, m, c0 + 2 * p, base + int64_t(m) * g.ld_line + 2 * p, H,
-                           -Z.im * scale, Z.re * scale, g.ncols, outv);
-      put_odd(line, L, m + 1, outv[0], outv[1]);
-      if (m == 0) {
-        line[0] = Cx<T>{T(0), T(0)};
-        line[N] = Cx<T>{T(0), T(0)};
-      }
-    }
-  } else
-  for (int i = threadIdx.x; i < P * n; i += blockDim.x) {
-    const int m = i / P;
-    const int p = i - m * P;
-    Cx<T>* line = lds + p * g.ls;
-    const Cx<T> Z = line[m + 1];
-    const T ga = -Z.im * scale, gb = Z.re * scale;
-    const int ky = g.last_is_z ? outer : m;
-    const int kz = g.last_is_z ? m : 0;
-    const Sep syz = sep_combine(sep_load(dg.ax[1], ky), sep_load(dg.ax[2], kz));
-    T* hp = H + base + int64_t(m) * g.ld_line + 2 * p;
-    Cx<T> hv = *reinterpret_cast<Cx<T>*>(hp);
-    T outv[2];
-    T newh[2];
-    const T gin[2] = {ga, gb};
-    const T hin[2] = {hv.re, hv.im};
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const Sep s = sep_combine(sep_load(dg.ax[0], c0 + 2 * p + q), syz);
-      double o, nh;
-      if (MODE == COL_ETD1)
-        diag_apply<DIAG_ETD1>(s, D, tau, c2, double(gin[q]), double(hin[q]), &o, &nh);
-      else if (MODE == COL_STAGE_A)
-        diag_apply<DIAG_A>(s, D, tau, c2, double(gin[q]), double(hin[q]), &o, &nh);
-      else
-        diag_apply<DIAG_B>(s, D, tau, c2, double(gin[q]), double(hin[q]), &o, &nh);
-      outv[q] = T(o);
-      newh[q] = T(nh);
-    }
-    *reinterpret_cast<Cx<T>*>(hp) = mask_pad(Cx<T>{newh[0], newh[1]}, c0 + 2 * p, g.ncols);
-    put_odd(line, L, m + 1, outv[0], outv[1]);
-    if (m == 0) {
-      line[0] = Cx<T>{T(0), T(0)};
-      line[N] = Cx<T>{T(0), T(0)};
-    }
-  }
-  __syncthreads();
-  fft_lines<T, kMaxElems * 256 / NT>(lds, g.ls, P, g.pl, tw);
-  for (int i = threadIdx.x; i < P * n; i += blockDim.x) {
-    const int m = i / P;
-    const int p = i - m * P;
-    const Cx<T> Z = lds[p * g.ls + m + 1];
-    *reinterpret_cast<Cx<T>*>(W + base + int64_t(m) * g.ld_line + 2 * p) =
-        mask_pad(Cx<T>{-Z.im * scale, Z.re * scale}, c0 + 2 * p, g.ncols);
-  }
-}
-
 // ---------------------------------------------------------------------------
 // Periodic lines (the variant at the end of Section 4).  The 1D matrices are
 // circulant, diagonalised by the real orthonormal Fourier basis; position r of
@@ -973,222 +618,6 @@ __global__ void __launch_bounds__(NT) col_pass(T* W, T* H, ColGeom g, const Cx<T
 // and a_r = Z_r.re / sqrt(N), b_r = Z_r.im / sqrt(N) for r = 0 and r = N/2.  The
 // inverse rebuilds the Hermitian pair spectrum Z^ (Z^_k = a^_k + i b^_k) and,
 // since c = conj(FFT(conj(Z^))) / sqrt(N), runs the same forward FFT.
-
-// Forward: Z in the line -> (a_r, b_r) at position r, in place.  Each pair
-// (k, N - k) is read and written by one thread.
-template <typename T>
-__device__ __forceinline__ void per_unpack(Cx<T>* lds, int ls, int P, int N) {
-  const int half = N / 2 + 1;  // k = 0 .. N/2
-  const T s1 = T(1.0 / sqrt(double(N)));
-  const T s2 = T(1.0 / sqrt(2.0 * double(N)));
-  for (int i = threadIdx.x; i < P * half; i += blockDim.x) {
-    const int p = i / half;
-    const int k = i - p * half;
-    Cx<T>* line = lds + p * ls;
-    const int km = N - k;
-    if (k == 0 || 2 * k == N) {
-      const Cx<T> z = line[k];
-      line[k] = Cx<T>{z.re * s1, z.im * s1};
-    } else {
-      const Cx<T> zp = line[k], zm = line[km];
-      line[k] = Cx<T>{(zp.re + zm.re) * s2, (zp.im + zm.im) * s2};
-      line[km] = Cx<T>{(zm.im - zp.im) * s2, (zp.re - zm.re) * s2};
-    }
-  }
-}
-
-// Inverse, first half: (a_r, b_r) at position r -> conj(Z^) in the line, in place.
-template <typename T>
-__device__ __forceinline__ void per_pack(Cx<T>* lds, int ls, int P, int N) {
-  const int half = N / 2 + 1;
-  const T r2 = T(1.0 / sqrt(2.0));
-  for (int i = threadIdx.x; i < P * half; i += blockDim.x) {
-    const int p = i / half;
-    const int k = i - p * half;
-    Cx<T>* line = lds + p * ls;
-    const int km = N - k;
-    if (k == 0 || 2 * k == N) {
-      const Cx<T> c = line[k];
-      line[k] = Cx<T>{c.re, -c.im};
-    } else {
-      const Cx<T> ck = line[k], cm = line[km];  // (a_k, b_k), (a_{N-k}, b_{N-k})
-      // Z^_k = ((a_k + b_{N-k}) + i (b_k - a_{N-k})) / sqrt 2,
-      // Z^_{N-k} = ((a_k - b_{N-k}) + i (b_k + a_{N-k})) / sqrt 2; stored conjugated
-      line[k] = Cx<T>{(ck.re + cm.im) * r2, (cm.re - ck.im) * r2};
-      line[km] = Cx<T>{(ck.re - cm.im) * r2, -(ck.im + cm.re) * r2};
-    }
-  }
-}
-
-// Inverse, second half: after the FFT of conj(Z^), nodal (a_j, b_j) = (X.re, -X.im) / sqrt(N).
-template <typename T>
-__device__ __forceinline__ Cx<T> per_nodal(Cx<T> X, T s1) {
-  return Cx<T>{X.re * s1, -X.im * s1};
-}
-
-// Row pass of periodic lines (x): ROW_FWD_USER, ROW_INV_USER or ROW_PHYS.
-template <typename T, int MODE, int NT = 256>
-__global__ void __launch_bounds__(NT) row_pass_per(const T* src, T* dst, T* dst2, RowGeom g,
-                                                    const Cx<T>* __restrict__ tw, Forcing F) {
-  extern __shared__ unsigned char smem_raw[];
-  Cx<T>* lds = reinterpret_cast<Cx<T>*>(smem_raw);
-  const int n = g.n;  // = N, the FFT length
-  const int P = g.P;
-  const int r0 = blockIdx.x * 2 * P;
-  const T s1 = T(1.0 / sqrt(double(n)));
-  for (int i = threadIdx.x; i < P * n; i += blockDim.x) {
-    const int p = i / n;
-    const int m = i - p * n;
-    const int ra = r0 + 2 * p, rb = ra + 1;
-    const T a = ra < g.nrows ? src[int64_t(ra) * g.ld_src + m] : T(0);
-    const T b = rb < g.nrows ? src[int64_t(rb) * g.ld_src + m] : T(0);
-    lds[p * g.ls + m] = Cx<T>{a, b};
-  }
-  __syncthreads();
-  if (MODE != ROW_FWD_USER) {
-    // inverse transform to nodal values
-    per_pack(lds, g.ls, P, n);
-    __syncthreads();
-    fft_lines<T, kMaxElems * 256 / NT>(lds, g.ls, P, g.pl, tw);
-    for (int i = threadIdx.x; i < P * n; i += blockDim.x) {
-      const int p = i / n;
-      const int m = i - p * n;
-      const int ra = r0 + 2 * p, rb = ra + 1;
-      const Cx<T> u = per_nodal(lds[p * g.ls + m], s1);
-      if (MODE == ROW_INV_USER) {
-        if (ra < g.nrows) dst[int64_t(ra) * g.ld_dst + m] = u.re;
-        if (rb < g.nrows) dst[int64_t(rb) * g.ld_dst + m] = u.im;
-      } else {
-        T fa = T(0), fb = T(0);
-        if (ra < g.nrows) fa = reaction<T>(F, u.re, m - 1, ra % g.ny, ra / g.ny);
-        if (rb < g.nrows) fb = reaction<T>(F, u.im, m - 1, rb % g.ny, rb / g.ny);
-        lds[p * g.ls + m] = Cx<T>{fa, fb};
-      }
-    }
-    if (MODE == ROW_INV_USER) return;
-    __syncthreads();
-  }
-  // forward transform
-  fft_lines<T, kMaxElems * 256 / NT>(lds, g.ls, P, g.pl, tw);
-  per_unpack(lds, g.ls, P, n);
-  __syncthreads();
-  for (int i = threadIdx.x; i < P * n; i += blockDim.x) {
-    const int p = i / n;
-    const int m = i - p * n;
-    const int ra = r0 + 2 * p, rb = ra + 1;
-    const Cx<T> c = lds[p * g.ls + m];
-    if (ra < g.nrows) {
-      dst[int64_t(ra) * g.ld_dst + m] = c.re;
-      if (MODE == ROW_FWD_USER) dst2[int64_t(ra) * g.ld_dst + m] = c.re;
-    }
-    if (rb < g.nrows) {
-      dst[int64_t(rb) * g.ld_dst + m] = c.im;
-      if (MODE == ROW_FWD_USER) dst2[int64_t(rb) * g.ld_dst + m] = c.im;
-    }
-  }
-}
-
-// Column pass of periodic lines: COL_PLAIN (forward), COL_PLAIN_INV (inverse)
-// or a stage (forward, diagonal stage, inverse).  Tiles as col_pass.
-enum { COL_PLAIN_INV = 4 };
-
-template <typename T, int MODE, int NT = 256>
-__global__ void __launch_bounds__(NT) col_pass_per(T* W, T* H, ColGeom g, const Cx<T>* __restrict__ tw, Diag dg) {
-  extern __shared__ unsigned char smem_raw[];
-  Cx<T>* lds = reinterpret_cast<Cx<T>*>(smem_raw);
-  const int n = g.n;  // = N, the FFT length
-  const int P = g.P;
-  int bx, outer;
-  xcd_block(bx, outer);
-  const int c0 = bx * 2 * P;
-  const int64_t base = int64_t(outer) * g.ld_outer + c0;
-  const T s1 = T(1.0 / sqrt(double(n)));
-  for (int i = threadIdx.x; i < P * n; i += blockDim.x) {
-    const int m = i / P;
-    const int p = i - m * P;
-    lds[p * g.ls + m] =
-        mask_pad(*reinterpret_cast<const Cx<T>*>(W + base + int64_t(m) * g.ld_line + 2 * p), c0 + 2 * p, g.ncols);
-  }
-  __syncthreads();
-  if (MODE == COL_PLAIN_INV) {
-    per_pack(lds, g.ls, P, n);
-    __syncthreads();
-    fft_lines<T, kMaxElems * 256 / NT>(lds, g.ls, P, g.pl, tw);
-    for (int i = threadIdx.x; i < P * n; i += blockDim.x) {
-      const int m = i / P;
-      const int p = i - m * P;
-      *reinterpret_cast<Cx<T>*>(W + base + int64_t(m) * g.ld_line + 2 * p) =
-          mask_pad(per_nodal(lds[p * g.ls + m], s1), c0 + 2 * p, g.ncols);
-    }
-    return;
-  }
-  fft_lines<T, kMaxElems * 256 / NT>(lds, g.ls, P, g.pl, tw);
-  per_unpack(lds, g.ls, P, n);
-  __syncthreads();
-  if (MODE == COL_PLAIN) {
-    for (int i = threadIdx.x; i < P * n; i += blockDim.x) {
-      const int m = i / P;
-      const int p = i - m * P;
-      *reinterpret_cast<Cx<T>*>(W + base + int64_t(m) * g.ld_line + 2 * p) = mask_pad(lds[p * g.ls + m], c0 + 2 * p, g.ncols);
-    }
-    return;
-  }
-  // diagonal stage at position m of this axis, then the inverse transform
-  const double tau = dg.tau, c2 = dg.c2, D = dg.D;
-  if constexpr (MODE >= COL_S3_1) {
-    for (int i = threadIdx.x; i < P * n; i += blockDim.x) {
-      const int m = i / P;
-      const int p = i - m * P;
-      Cx<T>* line = lds + p * g.ls;
-      const Cx<T> gv = line[m];
-      T outv[2];
-      Sep3 sxy[2];
-      sep3_pair(dg, c0 + 2 * p, g.last_is_z, outer, sxy);
-      stage3_pair<T, MODE>(dg, s3k_make(dg), sxy, g.last_is_z, m, c0 + 2 * p, base + int64_t(m) * g.ld_line + 2 * p, H,
-                           gv.re, gv.im, g.ncols, outv);
-      line[m] = Cx<T>{outv[0], outv[1]};
-    }
-  } else
-  for (int i = threadIdx.x; i < P * n; i += blockDim.x) {
-    const int m = i / P;
-    const int p = i - m * P;
-    Cx<T>* line = lds + p * g.ls;
-    const Cx<T> gv = line[m];
-    const int ky = g.last_is_z ? outer : m;
-    const int kz = g.last_is_z ? m : 0;
-    const Sep syz = sep_combine(sep_load(dg.ax[1], ky), sep_load(dg.ax[2], kz));
-    T* hp = H + base + int64_t(m) * g.ld_line + 2 * p;
-    const Cx<T> hv = *reinterpret_cast<Cx<T>*>(hp);
-    const T gin[2] = {gv.re, gv.im};
-    const T hin[2] = {hv.re, hv.im};
-    T outv[2], newh[2];
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-      const Sep sp = sep_combine(sep_load(dg.ax[0], c0 + 2 * p + q), syz);
-      double o, nh;
-      if (MODE == COL_ETD1)
-        diag_apply<DIAG_ETD1>(sp, D, tau, c2, double(gin[q]), double(hin[q]), &o, &nh);
-      else if (MODE == COL_STAGE_A)
-        diag_apply<DIAG_A>(sp, D, tau, c2, double(gin[q]), double(hin[q]), &o, &nh);
-      else
-        diag_apply<DIAG_B>(sp, D, tau, c2, double(gin[q]), double(hin[q]), &o, &nh);
-      outv[q] = T(o);
-      newh[q] = T(nh);
-    }
-    *reinterpret_cast<Cx<T>*>(hp) = mask_pad(Cx<T>{newh[0], newh[1]}, c0 + 2 * p, g.ncols);
-    line[m] = Cx<T>{outv[0], outv[1]};
-  }
-  __syncthreads();
-  per_pack(lds, g.ls, P, n);
-  __syncthreads();
-  fft_lines<T, kMaxElems * 256 / NT>(lds, g.ls, P, g.pl, tw);
-  for (int i = threadIdx.x; i < P * n; i += blockDim.x) {
-    const int m = i / P;
-    const int p = i - m * P;
-    *reinterpret_cast<Cx<T>*>(W + base + int64_t(m) * g.ld_line + 2 * p) =
-        mask_pad(per_nodal(lds[p * g.ls + m], s1), c0 + 2 * p, g.ncols);
-  }
-}
 
 // ---------------------------------------------------------------------------
 // Norm reduction: per node, (M e)_i and (K_1 e)_i by the 3^d tensor stencil of

@@ -1,0 +1,114 @@
+// Launches of the mixed-radix passes for one element type (EIFE_T; included once by
+// eife_mix_f32.hip and once by eife_mix_f64.hip).
+#pragma once
+
+#include <algorithm>
+
+#include "eife_mix.hpp"
+
+namespace eife {
+namespace mix {
+
+namespace {
+
+template <typename F>
+bool for_pts(int pts, F f) {
+  if (pts == 16) return f(std::integral_constant<int, 16>());
+  return f(std::integral_constant<int, 32>());
+}
+
+template <typename T, int PTS, typename F>
+void each_kernel(F f) {
+  f(reinterpret_cast<const void*>(&row_mix<T, PTS, false>));
+  f(reinterpret_cast<const void*>(&row_mix<T, PTS, true>));
+  f(reinterpret_cast<const void*>(&col_mix<T, PTS, COL_PLAIN>));
+  f(reinterpret_cast<const void*>(&col_mix<T, PTS, COL_PLAIN_INV>));
+  f(reinterpret_cast<const void*>(&col_mix<T, PTS, COL_STAGE_A>));
+  f(reinterpret_cast<const void*>(&col_mix<T, PTS, COL_STAGE_B>));
+  f(reinterpret_cast<const void*>(&col_mix<T, PTS, COL_ETD1>));
+  f(reinterpret_cast<const void*>(&col_mix<T, PTS, COL_S3_1>));
+  f(reinterpret_cast<const void*>(&col_mix<T, PTS, COL_S3_2>));
+  f(reinterpret_cast<const void*>(&col_mix<T, PTS, COL_S3_3>));
+}
+
+}  // namespace
+
+template <typename T>
+int set_attrs(size_t bytes) {
+  if (bytes <= 65536) return 0;
+  int bad = 0;
+  auto set = [&](const void* f) {
+    if (hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, int(bytes)) != hipSuccess) bad = 1;
+  };
+  each_kernel<T, 16>(set);
+  each_kernel<T, 32>(set);
+  return bad;
+}
+
+template <typename T>
+bool row_launch(const Plan& pl, int lp, bool per, int mode, int count, hipStream_t s, const T* src, T* dst, T* dst2,
+                const RowGeom& rg, const Cx<T>* tw, const Forcing& F, const RowInst<T>* ri) {
+  Shape sh;
+  int pts;
+  sh.pl = pl;
+  sh.lp = lp;
+  sh.per = per;
+  sh.zero = 0;
+  if (!block_shape(pl, lp, sizeof(T), &sh.JT, &pts)) return false;
+  // two-value pieces: W rows always start on one, a caller's rows by pitch and base
+  // (a batch's instances lie anywhere in the caller's array)
+  auto al = [&](const void* p, int64_t ld) { return ld % 2 == 0 && reinterpret_cast<uintptr_t>(p) % (2 * sizeof(T)) == 0; };
+  sh.vec = (!ri || mode == ROW_PHYS) && al(src, rg.ld_src) && al(dst, rg.ld_dst) && (!dst2 || al(dst2, rg.ld_dst));
+  const dim3 grid((rg.nrows + (2 << lp) - 1) / (2 << lp), count);
+  const dim3 block(((sh.JT << lp) + 63) / 64 * 64);
+  const size_t shm = lds_bytes(pl, lp, sizeof(T));
+  return for_pts(pts, [&](auto c) {
+    constexpr int PTS = decltype(c)::value;
+    if (F.kind == FK_EX52)
+      hipLaunchKernelGGL((row_mix<T, PTS, true>), grid, block, shm, s, src, dst, dst2, rg, sh, tw, F, ri, mode);
+    else
+      hipLaunchKernelGGL((row_mix<T, PTS, false>), grid, block, shm, s, src, dst, dst2, rg, sh, tw, F, ri, mode);
+    return true;
+  });
+}
+
+template <typename T>
+bool col_launch(const Plan& pl, int lp, bool per, bool zero, int mode, int pitch, int outer, int count, hipStream_t s, T* W, T* H,
+                const ColGeom& cg, const Cx<T>* tw, const Diag& dg, const ColInst<T>* ci) {
+  Shape sh;
+  int pts;
+  sh.pl = pl;
+  sh.lp = lp;
+  sh.per = per;
+  sh.zero = zero;
+  sh.vec = 0;
+  if (pitch % (2 << lp) != 0 || !block_shape(pl, lp, sizeof(T), &sh.JT, &pts)) return false;
+  const dim3 grid(pitch / (2 << lp), outer, count);
+  const dim3 block(((sh.JT << lp) + 63) / 64 * 64);
+  const size_t shm = lds_bytes(pl, lp, sizeof(T));
+  return for_pts(pts, [&](auto c) {
+    constexpr int PTS = decltype(c)::value;
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, block, shm, s, W, H, cg, sh, tw, dg, ci); };
+    switch (mode) {
+      case COL_PLAIN: go(col_mix<T, PTS, COL_PLAIN>); break;
+      case COL_PLAIN_INV: go(col_mix<T, PTS, COL_PLAIN_INV>); break;
+      case COL_STAGE_A: go(col_mix<T, PTS, COL_STAGE_A>); break;
+      case COL_STAGE_B: go(col_mix<T, PTS, COL_STAGE_B>); break;
+      case COL_ETD1: go(col_mix<T, PTS, COL_ETD1>); break;
+      case COL_S3_1: go(col_mix<T, PTS, COL_S3_1>); break;
+      case COL_S3_2: go(col_mix<T, PTS, COL_S3_2>); break;
+      case COL_S3_3: go(col_mix<T, PTS, COL_S3_3>); break;
+      default: return false;
+    }
+    return true;
+  });
+}
+
+template int set_attrs<EIFE_T>(size_t);
+template bool row_launch<EIFE_T>(const Plan&, int, bool, int, int, hipStream_t, const EIFE_T*, EIFE_T*, EIFE_T*,
+                                 const RowGeom&, const Cx<EIFE_T>*, const Forcing&, const RowInst<EIFE_T>*);
+template bool col_launch<EIFE_T>(const Plan&, int, bool, bool, int, int, int, int, hipStream_t, EIFE_T*, EIFE_T*,
+                                 const ColGeom&, const Cx<EIFE_T>*, const Diag&, const ColInst<EIFE_T>*);
+
+}  // namespace mix
+}  // namespace eife
