@@ -241,6 +241,8 @@ Forcing make_forcing(const eife_grid_s* g, int kind, double t) {
     F.sinpi_ax[a] = g->sinpi_ax[a];
   }
   const double PI2 = 9.8696044010893586188;
+  F.ieps2 = kind == EIFE_F_TRAVELING_WAVE ? 1.0 / (g->c0 * g->c0) : 0.0;
+  F.wave = nullptr;
   F.et = kind == EIFE_F_EX51 ? std::exp(-PI2 * t) : std::exp(-t);
   return F;
 }
@@ -426,7 +428,7 @@ bool try_row_gemm(const eife_grid_s* g, int mode, hipStream_t s, const T* src, T
   if constexpr (sizeof(T) != 4) {
     return false;
   } else {
-    // the traveling wave's boundary code runs in the generic row pass only
+    // the traveling wave runs on the FFT row passes only
     if (g->transform != EIFE_TX_GEMM_SPLITBF16 || F.kind == FK_EX52) return false;
     const gemm::SMat S = smat_of(g, 0);
     const bool ac = F.kind == FK_AC;
@@ -641,6 +643,28 @@ int run_steps(eife_grid_s* g, const T* u, int64_t n_steps, int f_kind, double t0
   RET_IF(launch_col<T>(g, last, COL_PLAIN, H, H, dg0, s));
   const int64_t stride = taus ? step_table_stride(g) : 0;
   double tv = t0;  // running time of a variable-step run
+  const double nodes[3] = {0.0, node_c2(g), g->c3_3};
+  // The traveling wave's tables are formed kWaveEvals evaluation times ahead, in
+  // stream order with the row passes that read them.
+  const int n0 = g->n[0];
+  int64_t evals = 0;
+  auto wave_at = [&](int64_t st, double tn) -> const double* {
+    const int slot = int(evals++ % kWaveEvals);
+    if (slot == 0) {
+      WaveTimes tm{};
+      int cnt = 0;
+      double tl = tn;
+      // this evaluation is the first not tabulated: its stage, then the later ones
+      for (int64_t q = st, i0 = (evals - 1) % g->stages; q < n_steps && cnt < kWaveEvals; ++q, i0 = 0) {
+        if (q > st) tl = taus ? tl + taus[q - 1] : t0 + double(q) * g->tau;
+        const double tq = taus ? taus[q] : g->tau;
+        for (int64_t i = i0; i < g->stages && cnt < kWaveEvals; ++i) tm.t[cnt++] = i ? tl + nodes[i] * tq : tl;
+      }
+      hipLaunchKernelGGL(wave_tables, dim3((n0 + 2 + 255) / 256, cnt), dim3(256), 0, s, g->wave, tm, n0, g->a[0], g->h[0],
+                         g->D, g->c0);
+    }
+    return g->wave + int64_t(slot) * wave_stride(n0);
+  };
   for (int64_t st = 0; st < n_steps; ++st) {
     double tau = g->tau;
     Diag dg_var;
@@ -677,11 +701,12 @@ int run_steps(eife_grid_s* g, const T* u, int64_t n_steps, int f_kind, double t0
     // stage i: reaction at t_n + c_i tau, transforms, the stage's diagonal update
     static const int kModes[4][3] = {{0, 0, 0}, {COL_ETD1, 0, 0}, {COL_STAGE_A, COL_STAGE_B, 0},
                                      {COL_S3_1, COL_S3_2, COL_S3_3}};
-    const double nodes[3] = {0.0, node_c2(g), g->c3_3};
     for (int i = 0; i < g->stages; ++i) {
-      if (!(fused && st == 0 && i == 0))
-        RET_IF(launch_row<T>(g, ROW_PHYS, W, g->pitch, W, g->pitch, nullptr,
-                             make_forcing(g, f_kind, i ? tn + nodes[i] * tau : tn), s));
+      if (!(fused && st == 0 && i == 0)) {
+        Forcing F = make_forcing(g, f_kind, i ? tn + nodes[i] * tau : tn);
+        if (f_kind == EIFE_F_TRAVELING_WAVE) F.wave = wave_at(st, tn);
+        RET_IF(launch_row<T>(g, ROW_PHYS, W, g->pitch, W, g->pitch, nullptr, F, s));
+      }
       if (three) RET_IF(launch_col<T>(g, 1, COL_PLAIN, W, H, dg, s));
       RET_IF(launch_col<T>(g, last, kModes[g->stages][i], W, H, dg, s));
       if (three) RET_IF(launch_col<T>(g, 1, inv_plain, W, H, dg, s));
@@ -948,12 +973,15 @@ int eife_create_grid(int d, const int32_t* N, const double* h, double D, int bc,
       return fail(EIFE_ENOMEM, "table allocation failed");
     }
   }
-  if (hipMalloc(reinterpret_cast<void**>(&g->partials), kNormBlocksMax * kNormAcc * sizeof(double)) != hipSuccess ||
+  // the norm reduction's block rows, then the traveling wave's tables
+  const size_t part = size_t(kNormBlocksMax) * kNormAcc, wave = size_t(kWaveEvals) * wave_stride(g->n[0]);
+  if (hipMalloc(reinterpret_cast<void**>(&g->partials), (part + wave) * sizeof(double)) != hipSuccess ||
       hipMalloc(reinterpret_cast<void**>(&g->out5), kNormAcc * sizeof(double)) != hipSuccess ||
       hipHostMalloc(reinterpret_cast<void**>(&g->host5), kNormAcc * sizeof(double), 0) != hipSuccess) {
     free_grid(g);
     return fail(EIFE_ENOMEM, "norm buffers allocation failed");
   }
+  g->wave = g->partials + part;
   int rt = upload_tables(g);
   if (rt == EIFE_OK) rt = upload_sinpi(g);
   if (rt != EIFE_OK) {

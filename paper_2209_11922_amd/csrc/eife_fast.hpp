@@ -400,13 +400,24 @@ struct Line<T, L, false> {
 // the pair's own wavefront slice touches it between block barriers.
 
 // Reaction kinds that get their own code path (everything else is generic).
-enum { RK_GENERIC = 0, RK_AC = 1 };
+enum { RK_GENERIC = 0, RK_AC = 1, RK_WAVE = 2 };
 
+// The reaction along one row (y, z index iy, iz).
 template <typename T, int RK>
-__device__ __forceinline__ T reaction_k(const Forcing& F, T u, int ix, int iy, int iz) {
-  if (RK == RK_AC) return u - u * u * u;
-  return reaction<T, false>(F, u, ix, iy, iz);
-}
+struct RowReaction {
+  int iy, iz;
+  __device__ __forceinline__ RowReaction(const Forcing&, int y, int z) : iy(y), iz(z) {}
+  __device__ __forceinline__ T operator()(const Forcing& F, T u, int ix) const {
+    if (RK == RK_AC) return u - u * u * u;
+    return reaction<T>(F, u, ix, iy, iz);
+  }
+};
+template <typename T>
+struct RowReaction<T, RK_WAVE> {
+  ShellRow r;
+  __device__ __forceinline__ RowReaction(const Forcing& F, int y, int z) : r(shell_row(F, y, z)) {}
+  __device__ __forceinline__ T operator()(const Forcing& F, T u, int ix) const { return reaction_wave<T>(F, r, u, ix); }
+};
 
 // ---------------------------------------------------------------------------
 // Row passes (x lines, contiguous).  Block = PB line pairs = 2 PB rows; each
@@ -472,26 +483,20 @@ __global__ void __launch_bounds__((PB * Line<T, L>::LP), (MinWaves<T, L>::value)
       }
     }
     wave_sync();
-    const int iya = ra % g.ny, iza = ra / g.ny;
-    const int iyb = rb % g.ny, izb = rb / g.ny;
+    const RowReaction<T, RK> fa(F, ra % g.ny, ra / g.ny), fb(F, rb % g.ny, rb / g.ny);
 #pragma unroll
     for (int t = 0; t < RIT; ++t) {
       const int m = lane + LP * t;
-      if (m < n)
-        my[m] = Cx<T>{reaction_k<T, RK>(F, va[t], m, iya, iza), reaction_k<T, RK>(F, vb[t], m, iyb, izb)};
+      if (m < n) my[m] = Cx<T>{fa(F, va[t], m), fb(F, vb[t], m)};
     }
     wave_sync();
     Ln::transform(v, my, my, lane, twl, tw);
   }
 
   if (MODE == ROW_PHYS) {
-    const int iya = ra % g.ny, iza = ra / g.ny;
-    const int iyb = rb % g.ny, izb = rb / g.ny;
+    const RowReaction<T, RK> fa(F, ra % g.ny, ra / g.ny), fb(F, rb % g.ny, rb / g.ny);
     Ln::outputs(v, lane, tw, [&](int k, Cx<T> Z) {
-      const T ua = -Z.im * scale, ub = Z.re * scale;
-      const T fa = reaction_k<T, RK>(F, ua, k - 1, iya, iza);
-      const T fb = reaction_k<T, RK>(F, ub, k - 1, iyb, izb);
-      my[k - 1] = Cx<T>{fa, fb};
+      my[k - 1] = Cx<T>{fa(F, -Z.im * scale, k - 1), fb(F, Z.re * scale, k - 1)};
     });
     wave_sync();
     Ln::transform(v, my, my, lane, twl, tw);
@@ -1098,7 +1103,7 @@ __global__ void __launch_bounds__((PB * FftShape<L>::LP), (MinWaves<T, L>::value
       if (MODE == ROW_INV_USER)
         my[k] = Cx<T>{ua, ub};
       else
-        my[k] = Cx<T>{reaction_k<T, RK_GENERIC>(F, ua, k, 0, 0), reaction_k<T, RK_GENERIC>(F, ub, k, 0, 0)};
+        my[k] = Cx<T>{reaction<T>(F, ua, k, 0, 0), reaction<T>(F, ub, k, 0, 0)};
     });
     wave_sync();
   }

@@ -299,12 +299,10 @@ __global__ void __launch_bounds__(64, 4) row_fold(float* W, RowGeom g, const Cf*
   transform(R, lds, ln);
   {
     const int ta = blockIdx.x * 2 * PW + 2 * ln.p, tb = ta + 1;
-    const int iya = ta % g.ny, iza = ta / g.ny;
-    const int iyb = tb % g.ny, izb = tb / g.ny;
+    const fast::RowReaction<float, RK> fa(F, ta % g.ny, ta / g.ny), fb(F, tb % g.ny, tb / g.ny);
     const bool ina = ta < g.nrows, inb = tb < g.nrows;  // rows past the end stay zero
     outputs(R, ln, [&](int k, int s, Cf u) {
-      lds[s * PW + ln.p] = Cf{ina ? fast::reaction_k<float, RK>(F, u.re, k - 1, iya, iza) : 0.f,
-                              inb ? fast::reaction_k<float, RK>(F, u.im, k - 1, iyb, izb) : 0.f};
+      lds[s * PW + ln.p] = Cf{ina ? fa(F, u.re, k - 1) : 0.f, inb ? fb(F, u.im, k - 1) : 0.f};
     });
   }
   fast::wave_sync();

@@ -41,6 +41,7 @@ struct eife_grid_s {
   double* sinpi_ax[3] = {nullptr, nullptr, nullptr};  // sin(pi x) at the interior nodes of each axis
   int tablen[3] = {0, 0, 0};
   double* partials = nullptr;
+  double* wave = nullptr;  // traveling wave tables, kWaveEvals evaluation times (in the partials' allocation)
   double* out5 = nullptr;
   double* host5 = nullptr;  // pinned
   // per-step phi tables of variable-step runs (eife_step_variable): a chunk of

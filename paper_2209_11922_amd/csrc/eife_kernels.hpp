@@ -365,6 +365,9 @@ struct Forcing {
   // e^(-pi^2 t) for Example 5.1), formed once per launch instead of per node
   const double* sinpi_ax[3];
   double et;
+  // traveling wave: 1 / eps^2 and the boundary load's tables at the launch's time (ShellTab)
+  double ieps2;
+  const double* wave;
 };
 
 // sin(pi (a + (i + 1) h)) for i < n: the per-axis factors of the manufactured
@@ -388,47 +391,91 @@ __device__ __forceinline__ double ex52_wave(double x, double t, double eps, doub
 
 // Nonhomogeneous Dirichlet data as part of f (start of Section 4): with the
 // boundary nodes carrying g(t), the Galerkin load of interior node i gains
-// b_i = -sum over boundary neighbours j of (M_ij g_j' + D K1_ij g_j).  Returned
-// divided by prod(h), the scale of the lumped load f(u_i) prod(h), so it adds
-// to the reaction value.  Per axis the 1D entries over h are 2/3 (same node) and
-// 1/6 (neighbour) for the mass, 2/h^2 and -1/h^2 for the stiffness.  Nonzero
-// only on the shell of nodes next to the boundary.
-__device__ __forceinline__ double ex52_shell_load(const Forcing& F, int ix, int iy, int iz) {
-  const int idx[3] = {ix + 1, iy + 1, iz + 1};  // all-node indices
-  double acc = 0.0;
-  const int oz0 = F.d > 2 ? -1 : 0, oz1 = F.d > 2 ? 1 : 0;
-  const int oy0 = F.d > 1 ? -1 : 0, oy1 = F.d > 1 ? 1 : 0;
-  for (int oz = oz0; oz <= oz1; ++oz)
-    for (int oy = oy0; oy <= oy1; ++oy)
-      for (int ox = -1; ox <= 1; ++ox) {
-        const int o[3] = {ox, oy, oz};
-        bool bnd = false;
-        double al[3], be[3];
-        for (int a = 0; a < 3; ++a) {
-          if (a < F.d) {
-            const int j = idx[a] + o[a];
-            bnd = bnd || j == 0 || j == F.n[a] + 1;
-            al[a] = o[a] ? 1.0 / 6.0 : 2.0 / 3.0;
-            be[a] = (o[a] ? -1.0 : 2.0) / (F.h[a] * F.h[a]);
-          } else {
-            al[a] = 1.0;
-            be[a] = 0.0;
-          }
-        }
-        if (!bnd) continue;
-        const double mass = al[0] * al[1] * al[2];
-        const double stiff = be[0] * al[1] * al[2] + al[0] * be[1] * al[2] + al[0] * al[1] * be[2];
-        double g_t;
-        const double g = ex52_wave(F.a[0] + (idx[0] + ox) * F.h[0], F.t, F.c0, &g_t);
-        acc -= mass * g_t + F.D * stiff * g;
-      }
-  return acc;
+// b_i = -sum over boundary neighbours j of (M_ij g_j' + D K1_ij g_j), formed here
+// over prod(h), the scale of the lumped load f(u_i) prod(h), so that it adds to the
+// reaction value.  Per axis the 1D entries over h are 2/3 (same node) and 1/6
+// (neighbour) for the mass, 2/h^2 and -1/h^2 for the stiffness; nonzero only on the
+// shell of nodes next to the boundary.
+//
+// The wave depends on x alone, so the sum over the neighbours separates: with A, B
+// the 1D x entries and m, s the mass and stiffness sums over the row's (y, z)
+// neighbours that lie on the boundary,
+//   b_i = -(m P_i + s Q_i),  P = A g' + D B g,  Q = D A g   (at the x nodes i - 1 .. i + 1),
+// plus, at the ends of a row, the x boundary node with the sums over the other
+// (y, z) neighbours.  P and Q are tabulated per evaluation time (wave_tables), the
+// four sums per row (ShellRow); forming the neighbours' waves at every shell
+// node took most of the x pass and kept the traveling wave off the specialised row
+// kernels, for want of registers (1024 x 64 x 64 FP64: 204 us a pass; with the
+// tables 38.5 us, a pass without a load 37, and 4.7 us per 16 evaluation times for
+// the tables).
+constexpr int kWaveEvals = 16;  // evaluation times tabulated per launch
+struct WaveTimes {
+  double t[kWaveEvals];
+};
+// doubles of one evaluation's tables: P[n], Q[n], then the end terms
+// (A g' + D B g, D A g) of the left and of the right x boundary node
+__host__ __device__ constexpr int wave_stride(int n) { return 2 * n + 4; }
+
+static __global__ void __launch_bounds__(256) wave_tables(double* __restrict__ out, WaveTimes tm, int n, double a,
+                                                          double h, double D, double eps) {
+  const int i = blockIdx.x * blockDim.x + threadIdx.x;
+  const double t = tm.t[blockIdx.y];
+  double* tab = out + int64_t(blockIdx.y) * wave_stride(n);
+  if (i < n) {
+    double P = 0.0, Q = 0.0;
+    for (int o = -1; o <= 1; ++o) {
+      const double al = o ? 1.0 / 6.0 : 2.0 / 3.0, be = (o ? -1.0 : 2.0) / (h * h);
+      double g_t;
+      const double g = ex52_wave(a + (i + 1 + o) * h, t, eps, &g_t);
+      P += al * g_t + D * be * g;
+      Q += D * al * g;
+    }
+    tab[i] = P;
+    tab[n + i] = Q;
+  } else if (i < n + 2) {
+    double g_t;
+    const double g = ex52_wave(i == n ? a : a + (n + 1) * h, t, eps, &g_t);
+    tab[2 * n + 2 * (i - n)] = g_t / 6.0 - D / (h * h) * g;
+    tab[2 * n + 2 * (i - n) + 1] = D / 6.0 * g;
+  }
 }
 
-__device__ __forceinline__ double ex52_boundary_load(const Forcing& F, int ix, int iy, int iz) {
-  const bool shell = ix == 0 || ix == F.n[0] - 1 || (F.d > 1 && (iy == 0 || iy == F.n[1] - 1)) ||
-                     (F.d > 2 && (iz == 0 || iz == F.n[2] - 1));
-  return shell ? ex52_shell_load(F, ix, iy, iz) : 0.0;
+// The (y, z) sums of one row: over the neighbours on the boundary (m, s) and over
+// the others (mi, si).
+struct ShellRow {
+  double m, s, mi, si;
+};
+
+__device__ __forceinline__ ShellRow shell_row(const Forcing& F, int iy, int iz) {
+  ShellRow r{0.0, 0.0, 0.0, 0.0};
+  const double hy2 = 1.0 / (F.h[1] * F.h[1]), hz2 = 1.0 / (F.h[2] * F.h[2]);
+  for (int oz = F.d > 2 ? -1 : 0; oz <= (F.d > 2 ? 1 : 0); ++oz)
+    for (int oy = F.d > 1 ? -1 : 0; oy <= (F.d > 1 ? 1 : 0); ++oy) {
+      const bool by = F.d > 1 && (iy + oy < 0 || iy + oy >= F.n[1]), bz = F.d > 2 && (iz + oz < 0 || iz + oz >= F.n[2]);
+      const double ay = F.d > 1 ? (oy ? 1.0 / 6.0 : 2.0 / 3.0) : 1.0, az = F.d > 2 ? (oz ? 1.0 / 6.0 : 2.0 / 3.0) : 1.0;
+      const double sy = F.d > 1 ? (oy ? -hy2 : 2.0 * hy2) : 0.0, sz = F.d > 2 ? (oz ? -hz2 : 2.0 * hz2) : 0.0;
+      const double m = ay * az, s = sy * az + ay * sz;
+      if (by || bz) {
+        r.m += m;
+        r.s += s;
+      } else {
+        r.mi += m;
+        r.si += s;
+      }
+    }
+  return r;
+}
+
+// Example 5.2's reaction at x index ix of a row: (u - u^3) / eps^2 plus the boundary load.
+template <typename T>
+__device__ __forceinline__ T reaction_wave(const Forcing& F, const ShellRow& r, T u, int ix) {
+  const double ud = double(u);
+  double v = (ud - ud * ud * ud) * F.ieps2;
+  const int n = F.n[0];
+  if (r.m != 0.0) v -= fma(r.m, F.wave[ix], r.s * F.wave[n + ix]);
+  if (ix == 0) v -= fma(r.mi, F.wave[2 * n], r.si * F.wave[2 * n + 1]);
+  if (ix == n - 1) v -= fma(r.mi, F.wave[2 * n + 2], r.si * F.wave[2 * n + 3]);
+  return T(v);
 }
 
 // Per-instance data of a batched launch (instances of one size class share
@@ -450,10 +497,8 @@ struct ColInst {
   double D;
 };
 
-// EX52 = false leaves out the traveling wave's boundary code (its neighbour
-// loop raises the register demand of the specialised passes, which therefore
-// do not take that kind).
-template <typename T, bool EX52 = true>
+// Every kind but the traveling wave (reaction_wave).
+template <typename T>
 __device__ __forceinline__ T reaction(const Forcing& F, T u, int ix, int iy, int iz) {
   switch (F.kind) {
     case FK_AC:
@@ -466,14 +511,6 @@ __device__ __forceinline__ T reaction(const Forcing& F, T u, int ix, int iy, int
       return T(F.c0 + F.c1 * F.t);
     case FK_FH:  // Example 5.3: (theta/2) ln((1 - u)/(1 + u)) + theta_c u, theta = c0, theta_c = c1
       return T(0.5) * T(F.c0) * log((T(1) - u) / (T(1) + u)) + T(F.c1) * u;
-    case FK_EX52: {  // Example 5.2: (u - u^3) / eps^2, eps = c0, plus the traveling-wave boundary data
-      if constexpr (EX52) {
-        const double ud = double(u);
-        return T((ud - ud * ud * ud) / (F.c0 * F.c0) + ex52_boundary_load(F, ix, iy, iz));
-      } else {
-        return T(0);
-      }
-    }
     case FK_MMS: {
       double s = F.sinpi_ax[0][ix];
       if (F.d > 1) s *= F.sinpi_ax[1][iy];

@@ -247,11 +247,9 @@ __global__ void __launch_bounds__((Shape<L>::NT), (LongWaves<T, L>::value))
   Cx<T> v[16];
   odd_fft<T, L>(v, lds, lds, tw, gt, t);
   if constexpr (MODE == ROW_PHYS) {
-    const int iya = ra % g.ny, iza = ra / g.ny;
-    const int iyb = rb % g.ny, izb = rb / g.ny;
+    const fast::RowReaction<T, RK> fa(F, ra % g.ny, ra / g.ny), fb(F, rb % g.ny, rb / g.ny);
     outputs<T, L>(v, t, [&](int k, Cx<T> Z) {
-      const T ua = -Z.im * scale, ub = Z.re * scale;
-      lds[k - 1] = Cx<T>{fast::reaction_k<T, RK>(F, ua, k - 1, iya, iza), fast::reaction_k<T, RK>(F, ub, k - 1, iyb, izb)};
+      lds[k - 1] = Cx<T>{fa(F, -Z.im * scale, k - 1), fb(F, Z.re * scale, k - 1)};
     });
     __syncthreads();
     refresh(gt);

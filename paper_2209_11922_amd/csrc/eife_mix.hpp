@@ -339,7 +339,7 @@ struct Waves {
 };
 
 // Row pass (x lines, contiguous): rows 2 (P bx + p), + 1 are pair p.
-template <typename T, int PTS, bool EX52>
+template <typename T, int PTS, int RK>
 __global__ void __launch_bounds__(kMaxThreads, (Waves<T, PTS>::value))
     row_mix(const T* src, T* dst, T* dst2, RowGeom g, Shape sh, const Cx<T>* __restrict__ tw, Forcing F,
             const RowInst<T>* __restrict__ insts, int mode) {
@@ -389,12 +389,12 @@ __global__ void __launch_bounds__(kMaxThreads, (Waves<T, PTS>::value))
   } else {
     ln.inverse();
     if (mode == ROW_PHYS) {
-      const int iya = ra % g.ny, iza = ra / g.ny, iyb = rb % g.ny, izb = rb / g.ny;
+      const fast::RowReaction<T, RK> rfa(F, ra % g.ny, ra / g.ny), rfb(F, rb % g.ny, rb / g.ny);
       const int off = sh.per ? -1 : 0;  // the reaction counts interior nodes
       for (int m = ln.jt; m < n; m += JT) {
         const Cx<T> u = ln.node(m, scale);
-        const T fa = hasa ? reaction<T, EX52>(F, u.re, m + off, iya, iza) : T(0);
-        const T fb = hasb ? reaction<T, EX52>(F, u.im, m + off, iyb, izb) : T(0);
+        const T fa = hasa ? rfa(F, u.re, m + off) : T(0);
+        const T fb = hasb ? rfb(F, u.im, m + off) : T(0);
         ln.put(m, Cx<T>{fa, fb});
       }
       __syncthreads();

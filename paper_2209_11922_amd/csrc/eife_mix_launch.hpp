@@ -19,8 +19,8 @@ bool for_pts(int pts, F f) {
 
 template <typename T, int PTS, typename F>
 void each_kernel(F f) {
-  f(reinterpret_cast<const void*>(&row_mix<T, PTS, false>));
-  f(reinterpret_cast<const void*>(&row_mix<T, PTS, true>));
+  f(reinterpret_cast<const void*>(&row_mix<T, PTS, fast::RK_GENERIC>));
+  f(reinterpret_cast<const void*>(&row_mix<T, PTS, fast::RK_WAVE>));
   f(reinterpret_cast<const void*>(&col_mix<T, PTS, COL_PLAIN>));
   f(reinterpret_cast<const void*>(&col_mix<T, PTS, COL_PLAIN_INV>));
   f(reinterpret_cast<const void*>(&col_mix<T, PTS, COL_STAGE_A>));
@@ -65,9 +65,9 @@ bool row_launch(const Plan& pl, int lp, bool per, int mode, int count, hipStream
   return for_pts(pts, [&](auto c) {
     constexpr int PTS = decltype(c)::value;
     if (F.kind == FK_EX52)
-      hipLaunchKernelGGL((row_mix<T, PTS, true>), grid, block, shm, s, src, dst, dst2, rg, sh, tw, F, ri, mode);
+      hipLaunchKernelGGL((row_mix<T, PTS, fast::RK_WAVE>), grid, block, shm, s, src, dst, dst2, rg, sh, tw, F, ri, mode);
     else
-      hipLaunchKernelGGL((row_mix<T, PTS, false>), grid, block, shm, s, src, dst, dst2, rg, sh, tw, F, ri, mode);
+      hipLaunchKernelGGL((row_mix<T, PTS, fast::RK_GENERIC>), grid, block, shm, s, src, dst, dst2, rg, sh, tw, F, ri, mode);
     return true;
   });
 }

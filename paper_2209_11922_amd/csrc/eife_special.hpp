@@ -68,6 +68,9 @@ void row_fast_go(int mode, int nrows, int count, hipStream_t s, const T* src, T*
     if (F.kind == FK_AC)
       hipLaunchKernelGGL((fast::row_fast<T, L, PB, ROW_PHYS, fast::RK_AC, BAT>), grid, dim3(NT), 0, s, src, dst,
                          dst2, rg, tw, F, ri);
+    else if (!BAT && F.kind == FK_EX52)
+      hipLaunchKernelGGL((fast::row_fast<T, L, PB, ROW_PHYS, BAT ? fast::RK_GENERIC : fast::RK_WAVE, BAT>), grid,
+                         dim3(NT), 0, s, src, dst, dst2, rg, tw, F, ri);
     else
       hipLaunchKernelGGL((fast::row_fast<T, L, PB, ROW_PHYS, fast::RK_GENERIC, BAT>), grid, dim3(NT), 0, s, src,
                          dst, dst2, rg, tw, F, ri);
@@ -333,6 +336,8 @@ void row_long_launch(int mode, int nrows, hipStream_t s, const T* src, T* dst, T
   if (mode == ROW_PHYS) {
     if (F.kind == FK_AC)
       hipLaunchKernelGGL((lng::row_long<T, L, ROW_PHYS, fast::RK_AC>), grid, dim3(NT), 0, s, src, dst, dst2, rg, tw, F);
+    else if (F.kind == FK_EX52)
+      hipLaunchKernelGGL((lng::row_long<T, L, ROW_PHYS, fast::RK_WAVE>), grid, dim3(NT), 0, s, src, dst, dst2, rg, tw, F);
     else
       hipLaunchKernelGGL((lng::row_long<T, L, ROW_PHYS, fast::RK_GENERIC>), grid, dim3(NT), 0, s, src, dst, dst2, rg, tw,
                          F);
@@ -382,8 +387,7 @@ template <typename T>
 bool try_row_fast(const eife_grid_s* g, int var, int mode, int count, hipStream_t s, const T* src, T* dst, T* dst2,
                   const RowGeom& rg, const Cx<T>* tw, const Forcing& F, const RowInst<T>* ri) {
   if (g->per[0]) return try_row_fast_per<T>(g, mode, count, s, src, dst, dst2, rg, tw, F, ri);
-  // the traveling wave's boundary code runs in the generic row pass only
-  if (g->transform != EIFE_TX_FFT || F.kind == FK_EX52) return false;
+  if (g->transform != EIFE_TX_FFT) return false;
   if (long_len(g->N[0])) {
     if (count != 1 || ri || (mode != ROW_PHYS && mode != ROW_FWD_USER && mode != ROW_INV_USER)) return false;
     if (g->N[0] == 1024)
@@ -395,7 +399,7 @@ bool try_row_fast(const eife_grid_s* g, int var, int mode, int count, hipStream_
     return true;
   }
   if constexpr (sizeof(T) == 4) {
-    if (mode == ROW_PHYS && !ri && fold_rows<T>(g)) {
+    if (mode == ROW_PHYS && !ri && F.kind != FK_EX52 && fold_rows<T>(g)) {
       fold::row_launch(rg.nrows, s, dst, rg, tw, F);
       return true;
     }
