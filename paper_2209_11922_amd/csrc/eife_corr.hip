@@ -30,6 +30,7 @@
 #include <cstdint>
 #include <cstring>
 #include <string>
+#include <type_traits>
 #include <vector>
 
 #include "../../include/eife.h"
@@ -51,7 +52,7 @@ constexpr int OFF_L6 = SZ_L1 + N_MID * SZ_LM;
 constexpr int N_PARAMS = OFF_L6 + SZ_L6;
 static_assert(N_PARAMS == EIFE_CORR_PARAMS, "parameter count");
 
-constexpr int kPartBlocks = 512;  // blocks of the weight-gradient kernels (one partial row each)
+constexpr int kPartBlocks = 512;  // most blocks of the backward kernels (one partial row each)
 
 __device__ __forceinline__ int tap_dy(int t) { return t / 3 - 1; }
 __device__ __forceinline__ int tap_dx(int t) { return t % 3 - 1; }
@@ -144,8 +145,15 @@ __device__ __forceinline__ void split_bf16(float x, __bf16& hi, __bf16& lo) {
   lo = __bf16(x - float(hi));  // x - hi is exact in FP32
 }
 
-// A fragments (rows = output channels 16 mt + l % 16, k = 8 (l / 16) + j) and
-// the accumulator's starting bias for lane (col, q).
+// Output channel of row i of the two 16-row products of a layer whose results go to
+// memory: interleaved so that the rows 4 q .. 4 q + 3 that a lane gets of each are
+// the 8 neighbouring channels 8 q .. + 7, one 16-byte store (and a node's 64 bytes one
+// line of a wave's store; as two 8-byte stores the input layer took 28 us, not 23).
+__device__ __forceinline__ int out_ch(int mt, int i) { return 8 * (i >> 2) + 4 * mt + (i & 3); }
+
+// A fragments (rows = output channels, 16 mt + l % 16 or interleaved; k = 8 (l / 16) + j)
+// and the accumulator's starting bias for lane (col, q).
+template <bool INTERLEAVED>
 struct InW {
   bf16x8 hi[2], lo[2];
   f32x4 bias[2];
@@ -155,20 +163,21 @@ struct InW {
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const int k = 8 * q + j;
-        const float w = k < 18 ? prm[k * C + mt * 16 + col] : 0.f;  // W1[t][c][o] at (2 t + c) C + o
+        const float w = k < 18 ? prm[k * C + (INTERLEAVED ? out_ch(mt, col) : mt * 16 + col)] : 0.f;  // W1[t][c][o] at (2 t + c) C + o
         __bf16 h, l;
         split_bf16(w, h, l);
         hi[mt][j] = h;
         lo[mt][j] = l;
       }
 #pragma unroll
-      for (int r = 0; r < 4; ++r) bias[mt][r] = prm[SZ_W1 + mt * 16 + 4 * q + r];
+      for (int r = 0; r < 4; ++r) bias[mt][r] = prm[SZ_W1 + (INTERLEAVED ? out_ch(mt, 4 * q + r) : mt * 16 + 4 * q + r)];
     }
   }
 };
 
 // The 16-node tile's pre-activations: x[j] = X[8 q + j][node col].
-__device__ __forceinline__ void in_products(const InW& w, const float (&x)[8], f32x4 (&acc)[2]) {
+template <bool INTERLEAVED>
+__device__ __forceinline__ void in_products(const InW<INTERLEAVED>& w, const float (&x)[8], f32x4 (&acc)[2]) {
   bf16x8 xh, xl;
 #pragma unroll
   for (int j = 0; j < 8; ++j) {
@@ -185,49 +194,63 @@ __device__ __forceinline__ void in_products(const InW& w, const float (&x)[8], f
   }
 }
 
-// One wave per 16-node tile of the flattened [batch][ny][nx] nodes.
-__global__ void __launch_bounds__(256) conv_in_fwd(const float* __restrict__ un, const float* __restrict__ uc,
-                                                   const float* __restrict__ cs, const float* __restrict__ prm,
-                                                   __bf16* __restrict__ Y, int nx, int ny, int64_t npix) {
+// relu of a lane's 8 interleaved channels, BF16, to p.
+__device__ __forceinline__ void store_relu(__bf16* p, const f32x4 (&acc)[2]) {
+  *reinterpret_cast<uint4*>(p) = uint4{relu_bf16x2(acc[0][0], acc[0][1]), relu_bf16x2(acc[0][2], acc[0][3]),
+                                       relu_bf16x2(acc[1][0], acc[1][1]), relu_bf16x2(acc[1][2], acc[1][3])};
+}
+
+// Strips of 16 nodes in x by `rows` rows, one to a wave at a time: n_strips in all.
+__host__ __forceinline__ int64_t n_strips(int nx, int ny, int batch, int rows) {
+  return int64_t(batch) * ((ny + rows - 1) / rows) * ((nx + 15) / 16);
+}
+
+// A wave walks its strips row by row, one 16-node tile each, the next row's inputs in
+// flight; the weights' fragments and every index but the row stay in registers
+// (formed per tile they took most of the time: 4 images of 511 x 511, 41 us, so
+// 23 us, 71 MB).
+__global__ void __launch_bounds__(256, 4) conv_in_fwd(const float* __restrict__ un, const float* __restrict__ uc,
+                                                      const float* __restrict__ cs, const float* __restrict__ prm,
+                                                      __bf16* __restrict__ Y, int nx, int ny, int rows, int nstrip) {
   const int lane = threadIdx.x & 63;
   const int col = lane & 15, q = lane >> 4;
-  const int64_t tile = int64_t(blockIdx.x) * 4 + (threadIdx.x >> 6);
-  const int64_t p = tile * 16 + col;
-  if (tile * 16 >= npix) return;
-  InW w;
+  InW<true> w;
   w.load(prm, col, q);
-  const int64_t pc = p < npix ? p : npix - 1;
-  const int64_t npix1 = int64_t(nx) * ny;
-  const int64_t b = pc / npix1;
-  const int x = int(pc % nx);
-  const int y = int((pc / nx) % ny);
-  const float rc = 1.f / cs[b];
-  float xv[8];
+  const int nsx = (nx + 15) / 16, nsy = (ny + rows - 1) / rows;
+  for (int si = blockIdx.x * 4 + (threadIdx.x >> 6); si < nstrip; si += gridDim.x * 4) {
+    const int x = si % nsx * 16 + col, img = si / nsx / nsy;
+    const int y0 = si / nsx % nsy * rows, y1 = min(y0 + rows, ny);
+    const int base = img * ny;
+    const float rc = 1.f / cs[img];
+    float vc[4], vn[4];
+    // k = 8 q + 2 j is channel 0 of tap t = 4 q + j, k + 1 channel 1
+    auto load = [&](int y) {
 #pragma unroll
-  for (int j = 0; j < 8; j += 2) {
-    const int t = (8 * q + j) >> 1;  // k = 8 q + j (even) is channel 0 of tap t, k + 1 channel 1
-    float vc = 0.f, vn = 0.f;
-    if (t < 9) {
-      const int yy = y + tap_dy(t), xx = x + tap_dx(t);
-      if (yy >= 0 && yy < ny && xx >= 0 && xx < nx) {
-        const int64_t qi = pc + int64_t(tap_dy(t)) * nx + tap_dx(t);
-        vc = uc[qi];
-        vn = un[qi];
+      for (int j = 0; j < 4; ++j) {
+        const int t = 4 * q + j, yy = y + tap_dy(t), xx = x + tap_dx(t);
+        vc[j] = vn[j] = 0.f;
+        if (t < 9 && yy >= 0 && yy < ny && xx >= 0 && xx < nx) {
+          vc[j] = uc[(base + yy) * nx + xx];
+          vn[j] = un[(base + yy) * nx + xx];
+        }
+      }
+    };
+    load(y0);
+    for (int y = y0; y < y1; ++y) {
+      float xv[8];
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+#pragma clang fp contract(off)
+        xv[2 * j] = vc[j];
+        xv[2 * j + 1] = (vc[j] - vn[j]) * rc;
+      }
+      load(y + 1);
+      f32x4 acc[2];
+      in_products(w, xv, acc);
+      if (x < nx) {
+        store_relu(Y + int64_t((base + y) * nx + x) * C + 8 * q, acc);
       }
     }
-    xv[j] = vc;
-    {
-#pragma clang fp contract(off)
-      xv[j + 1] = (vc - vn) * rc;
-    }
-  }
-  f32x4 acc[2];
-  in_products(w, xv, acc);
-  if (p < npix) {
-#pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
-      *reinterpret_cast<uint2*>(Y + p * C + mt * 16 + 4 * q) =
-          uint2{relu_bf16x2(acc[mt][0], acc[mt][1]), relu_bf16x2(acc[mt][2], acc[mt][3])};
   }
 }
 
@@ -241,145 +264,134 @@ __global__ void __launch_bounds__(256) conv_in_fwd(const float* __restrict__ un,
 // accumulator starting at the bias.  Lane layout of v_mfma_f32_16x16x32_bf16:
 // A row l%16 / B column l%16 with k = 8 (l/16) + j; D[4 (l/16) + r][l%16].
 //   CONV_FWD   Y = relu(D + bias)                           (32 outputs, BF16)
-//   CONV_BWD   Y = D where mask > 0 else 0                  (32 outputs, BF16;
-//              Wk = transposed, tap-flipped weights, mask = the activations
-//              the layer's input came from)
 //   OUT_INFER  out = s_out c_b (D[0] + b6)                   (1 output, FP32;
-//              Wk rows 1..15 are zero)
+//              row 0 of Wk)
 //   OUT_TRAIN  e = D[0] + b6 - (uf - uc) / (s_out c_b); out = 2 e / count;
 //              per-block sum of e^2 in loss_part[blockIdx.x]
-enum { CONV_FWD = 0, CONV_BWD = 1, OUT_INFER = 2, OUT_TRAIN = 3 };
+enum { CONV_FWD = 0, OUT_INFER = 1, OUT_TRAIN = 2 };
 
 constexpr int kPr = 4, kPx = 64;              // patch rows / nodes
 constexpr int kHr = kPr + 2, kHx = kPx + 2;   // with halo
-constexpr int kNs = 40;                       // LDS node stride (BF16): 80 bytes, conflict-free 16-byte reads
+
+// The stage of a patch's nodes with their halo: 64-byte nodes whose 16-byte channel
+// chunks are exchanged by x (swz), which leaves 16 neighbouring nodes' equal chunks
+// on distinct banks.  Thread i takes chunk i % 4 of stage column i / 4 in every row,
+// and the first 48 also the last two columns; the loads go to registers first, so
+// that the next patch's are in flight while the current one is computed from LDS.
+constexpr int kRow = kHx * 64, kStage = kHr * kRow;  // bytes
+__device__ __forceinline__ int swz(int x) { return ((x >> 1) & 2) | ((x >> 3) & 1); }
+
+struct Stage {
+  bf16x8 v[kHr], vh;
+  __device__ __forceinline__ void load(const __bf16* __restrict__ X, int64_t pi, int64_t npatch, int npx, int npy, int nx,
+                                       int ny) {
+    const int sc = threadIdx.x & 3, sx = threadIdx.x >> 2;
+    const int hx = kPx + (sx & 1), hr = sx >> 1;
+    const int64_t rest = pi / npx;
+    const int y0 = int(rest % npy) * kPr, x0 = int(pi % npx) * kPx;
+    const int64_t row0 = rest / npy * ny + y0;
+    const bool in = pi < npatch;
+    const int gx = x0 + sx - 1;
+#pragma unroll
+    for (int r = 0; r < kHr; ++r) {
+      const int gy = y0 + r - 1;
+      v[r] = bf16x8{};
+      if (in && gy >= 0 && gy < ny && gx >= 0 && gx < nx)
+        v[r] = *reinterpret_cast<const bf16x8*>(X + (row0 + r - 1) * nx * C + gx * C + sc * 8);
+    }
+    vh = bf16x8{};
+    if (in && threadIdx.x < 8 * kHr && y0 + hr - 1 >= 0 && y0 + hr - 1 < ny && x0 + hx - 1 < nx)
+      vh = *reinterpret_cast<const bf16x8*>(X + ((row0 + hr - 1) * nx + x0 + hx - 1) * C + sc * 8);
+  }
+  __device__ __forceinline__ void store(char* st) const {
+    const int sc = threadIdx.x & 3, sx = threadIdx.x >> 2;
+    const int hx = kPx + (sx & 1), hr = sx >> 1;
+#pragma unroll
+    for (int r = 0; r < kHr; ++r) *reinterpret_cast<bf16x8*>(st + sx * 64 + ((sc ^ swz(sx)) << 4) + r * kRow) = v[r];
+    if (threadIdx.x < 8 * kHr) *reinterpret_cast<bf16x8*>(st + hr * kRow + hx * 64 + ((sc ^ swz(hx)) << 4)) = vh;
+  }
+};
 
 template <int MODE>
-__global__ void __launch_bounds__(256) conv_patch(const __bf16* __restrict__ X, void* __restrict__ out,
-                                                  const __bf16* __restrict__ Wk, const float* __restrict__ bias,
-                                                  const __bf16* __restrict__ mask, float s_out,
-                                                  const float* __restrict__ cs, const float* __restrict__ uc,
-                                                  const float* __restrict__ uf,
-                                                  double* __restrict__ loss_part, double inv_count, int nx, int ny,
-                                                  int64_t npatch) {
-  constexpr int NMT = (MODE == CONV_FWD || MODE == CONV_BWD) ? 2 : 1;
-  __shared__ __attribute__((aligned(16))) __bf16 sp[kHr * kHx * kNs];
-  __shared__ __attribute__((aligned(16))) __bf16 ws[9 * 16 * NMT * C];
-  __shared__ double red[256];
+__global__ void __launch_bounds__(256, 2) conv_patch(const __bf16* __restrict__ X, void* __restrict__ out,
+                                                     const __bf16* __restrict__ Wk, const float* __restrict__ bias,
+                                                     float s_out, const float* __restrict__ cs,
+                                                     const float* __restrict__ uc, const float* __restrict__ uf,
+                                                     double* __restrict__ loss_part, double inv_count, int nx, int ny,
+                                                     int64_t npatch) {
+  constexpr int NMT = MODE == CONV_FWD ? 2 : 1;
+  __shared__ __attribute__((aligned(16))) char sp[kStage];
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int col = lane & 15, q = lane >> 4;
-  // weights: staged once per block in LDS, then held in registers by every wave
-  for (int i = tid; i < 9 * 16 * NMT * C / 8; i += 256)
-    *reinterpret_cast<bf16x8*>(ws + 8 * i) = *reinterpret_cast<const bf16x8*>(Wk + 8 * i);
-  __syncthreads();
+  // weights, held in registers; the output layer's one row is given to all 16, so
+  // that every lane gets the node's value
   bf16x8 wa[9][NMT];
 #pragma unroll
   for (int t = 0; t < 9; ++t)
 #pragma unroll
     for (int mt = 0; mt < NMT; ++mt)
-      wa[t][mt] = *reinterpret_cast<const bf16x8*>(ws + (t * 16 * NMT + mt * 16 + col) * C + 8 * q);
-  float bv[NMT][4];
+      wa[t][mt] = *reinterpret_cast<const bf16x8*>(Wk + (t * 16 * NMT + (MODE == CONV_FWD ? out_ch(mt, col) : 0)) * C + 8 * q);
+  f32x4 bv[NMT];
 #pragma unroll
   for (int mt = 0; mt < NMT; ++mt)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) {
-      if (MODE == CONV_FWD)
-        bv[mt][r] = bias[mt * 16 + 4 * q + r];
-      else if (MODE == OUT_INFER || MODE == OUT_TRAIN)
-        bv[mt][r] = bias[0];
-      else
-        bv[mt][r] = 0.f;
-    }
+    for (int r = 0; r < 4; ++r) bv[mt][r] = MODE == CONV_FWD ? bias[out_ch(mt, 4 * q + r)] : bias[0];
+  int bo[3];  // B operand per dx
+#pragma unroll
+  for (int d = 0; d < 3; ++d) bo[d] = wave * kRow + (col + d) * 64 + ((q ^ swz(col + d)) << 4);
   const int npx = (nx + kPx - 1) / kPx;
   const int npy = (ny + kPr - 1) / kPr;
   double e2 = 0.0;
-  // the next patch's nodes are loaded into registers while the current one is
-  // computed from LDS
-  constexpr int NLD = (kHr * kHx * 4 + 255) / 256;
-  bf16x8 v[NLD];
-  auto load = [&](int64_t pi) {
-    const int pxi = int(pi % npx);
-    const int64_t rest = pi / npx;
-    const int y0 = int(rest % npy) * kPr, x0 = pxi * kPx;
-    const int64_t b = rest / npy;
-#pragma unroll
-    for (int k = 0; k < NLD; ++k) {
-      const int i = tid + 256 * k;
-      const int node = i >> 2, ch = (i & 3) * 8;
-      const int r = node / kHx, xi = node % kHx;
-      const int gy = y0 + r - 1, gx = x0 + xi - 1;
-      v[k] = bf16x8{};
-      if (pi < npatch && i < kHr * kHx * 4 && gy >= 0 && gy < ny && gx >= 0 && gx < nx)
-        v[k] = *reinterpret_cast<const bf16x8*>(X + ((b * ny + gy) * nx + gx) * C + ch);
-    }
-  };
-  load(blockIdx.x);
+  Stage sg;
+  sg.load(X, blockIdx.x, npatch, npx, npy, nx, ny);
   for (int64_t pi = blockIdx.x; pi < npatch; pi += gridDim.x) {
-    const int pxi = int(pi % npx);
     const int64_t rest = pi / npx;
-    const int pyi = int(rest % npy);
+    const int x0 = int(pi % npx) * kPx, y = int(rest % npy) * kPr + wave;
     const int64_t b = rest / npy;
-    const int x0 = pxi * kPx, y0 = pyi * kPr;
-    __syncthreads();
-#pragma unroll
-    for (int k = 0; k < NLD; ++k) {
-      const int i = tid + 256 * k;
-      if (i < kHr * kHx * 4) *reinterpret_cast<bf16x8*>(sp + (i >> 2) * kNs + (i & 3) * 8) = v[k];
-    }
-    __syncthreads();
-    load(pi + gridDim.x);
-    const int y = y0 + wave;
-    if (y >= ny) continue;
     const int64_t rowoff = (b * ny + y) * nx;
+    __syncthreads();
+    sg.store(sp);
+    __syncthreads();
+    sg.load(X, pi + gridDim.x, npatch, npx, npy, nx, ny);
+    if (y >= ny) continue;
+    float dif = 0.f;  // the lane's node of the output modes
+    if (MODE == OUT_TRAIN && x0 + lane < nx) dif = uf[rowoff + x0 + lane] - uc[rowoff + x0 + lane];
+    float o = 0.f;
 #pragma unroll
     for (int tile = 0; tile < kPx / 16; ++tile) {
-      const int xl = tile * 16 + col;  // node within the patch
       f32x4 acc[NMT];
 #pragma unroll
-      for (int mt = 0; mt < NMT; ++mt) acc[mt] = f32x4{bv[mt][0], bv[mt][1], bv[mt][2], bv[mt][3]};
+      for (int mt = 0; mt < NMT; ++mt) acc[mt] = bv[mt];
 #pragma unroll
       for (int t = 0; t < 9; ++t) {
-        const bf16x8 bfr = *reinterpret_cast<const bf16x8*>(
-            sp + ((wave + tap_dy(t) + 1) * kHx + xl + tap_dx(t) + 1) * kNs + 8 * q);
+        const bf16x8 bfr = *reinterpret_cast<const bf16x8*>(sp + bo[t % 3] + (t / 3) * kRow + tile * 1024);
 #pragma unroll
         for (int mt = 0; mt < NMT; ++mt)
           acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[t][mt], bfr, acc[mt], 0, 0, 0);
       }
-      const int px = x0 + xl;
-      if (px >= nx) continue;
-      const int64_t p = rowoff + px;
-      if (MODE == CONV_FWD || MODE == CONV_BWD) {
-        __bf16* Y = static_cast<__bf16*>(out);
-#pragma unroll
-        for (int mt = 0; mt < NMT; ++mt) {
-          const int oc0 = mt * 16 + 4 * q;
-          if (MODE == CONV_FWD) {
-            *reinterpret_cast<uint2*>(Y + p * C + oc0) =
-                uint2{relu_bf16x2(acc[mt][0], acc[mt][1]), relu_bf16x2(acc[mt][2], acc[mt][3])};
-          } else {
-            const bf16x4 m = *reinterpret_cast<const bf16x4*>(mask + p * C + oc0);
-            bf16x4 h;
-#pragma unroll
-            for (int r = 0; r < 4; ++r) h[r] = (float(m[r]) > 0.f) ? __bf16(acc[mt][r]) : __bf16(0.f);
-            *reinterpret_cast<bf16x4*>(Y + p * C + oc0) = h;
-          }
-        }
-      } else if (q == 0) {
-        float* o = static_cast<float*>(out);
-        const float v = acc[0][0];  // output channel 0 = D row 0 (r = 0 of lanes 0..15), bias included
-        const float sc = s_out * cs[b];
-        if (MODE == OUT_INFER) {
-          o[p] = sc * v;
-        } else {
-          const float e = v - (uf[p] - uc[p]) / sc;
-          o[p] = float(2.0 * double(e) * inv_count);
-          e2 += double(e) * double(e);
-        }
+      if constexpr (MODE == CONV_FWD) {
+        const int px = x0 + tile * 16 + col;
+        if (px < nx) store_relu(static_cast<__bf16*>(out) + (rowoff + px) * C + 8 * q, acc);
+      } else if (q == tile) {
+        o = acc[0][0];  // output channel 0 at node 16 q + col = lane, bias included
+      }
+    }
+    if (MODE != CONV_FWD && x0 + lane < nx) {
+      float* of = static_cast<float*>(out) + rowoff + x0 + lane;
+      const float sc = s_out * cs[b];
+      if (MODE == OUT_INFER) {
+        *of = sc * o;
+      } else {
+        const float e = o - dif / sc;
+        *of = float(2.0 * double(e) * inv_count);
+        e2 += double(e) * double(e);
       }
     }
   }
   if (MODE == OUT_TRAIN) {
+    __syncthreads();
+    double* const red = reinterpret_cast<double*>(sp);
     red[tid] = e2;
     __syncthreads();
     for (int k = 128; k > 0; k >>= 1) {
@@ -391,222 +403,434 @@ __global__ void __launch_bounds__(256) conv_patch(const __bf16* __restrict__ X, 
 }
 
 // ---------------------------------------------------------------------------
-// Gradient into the output layer's input: dZ5[q][ic] = (Y5[q][ic] > 0) * sum_t W6[t][ic] g[q - off_t].
-__global__ void __launch_bounds__(256) conv_out_bwd(const float* __restrict__ g, const float* __restrict__ prm6,
-                                                    const __bf16* __restrict__ Y, __bf16* __restrict__ dZ, int nx,
-                                                    int ny, int64_t npix) {
-  __shared__ float w[SZ_W6];
-  for (int i = threadIdx.x; i < SZ_W6; i += blockDim.x) w[i] = prm6[i];
-  __syncthreads();
-  const int64_t p = int64_t(blockIdx.x) * blockDim.x + threadIdx.x;
-  if (p >= npix) return;
-  const int x = int(p % nx);
-  const int y = int((p / nx) % ny);
-  float acc[C];
-#pragma unroll
-  for (int c = 0; c < C; ++c) acc[c] = 0.f;
-#pragma unroll
-  for (int t = 0; t < 9; ++t) {
-    const int yy = y - tap_dy(t), xx = x - tap_dx(t);
-    if (yy < 0 || yy >= ny || xx < 0 || xx >= nx) continue;
-    const float gv = g[p - int64_t(tap_dy(t)) * nx - tap_dx(t)];
-#pragma unroll
-    for (int c = 0; c < C; ++c) acc[c] = fmaf(w[t * C + c], gv, acc[c]);
-  }
-  const bf16x8* ysrc = reinterpret_cast<const bf16x8*>(Y + p * C);
-  bf16x8* dst = reinterpret_cast<bf16x8*>(dZ + p * C);
-#pragma unroll
-  for (int v = 0; v < 4; ++v) {
-    const bf16x8 m = ysrc[v];
-    bf16x8 h;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) h[j] = float(m[j]) > 0.f ? __bf16(acc[8 * v + j]) : __bf16(0.f);
-    dst[v] = h;
-  }
+// Backward.  The weight gradients are sums over the nodes; every block adds its
+// share in FP32 into one partial row, and reduce_rows adds the rows in a fixed
+// order (deterministic).  With q = p + off_t a layer's weight gradient is
+//   dW[t][oc][ic] = sum_q X[q][ic] dZ[q - off_t][oc],
+// which reads X at the patch's nodes and dZ with a halo, as the gradient into the
+// layer's input does (there X is the ReLU mask): one kernel per layer forms both
+// from one read of X and dZ.
+
+// 32 -> 32 layer: Y = (sum_t Wb[t] dZ[q + off_t]) where X > 0 else 0 (Wb the
+// transposed, tap-flipped weights), and the block's share of dW (part[blk][t][oc][ic])
+// and of db (part[blk][SZ_WM + oc] = sum dZ), on the matrix cores.
+//
+// Patches as in conv_patch, dZ with its halo and X in LDS.  For Y wave w takes row
+// w; for dW, K = 32 nodes of a row per product, wave w takes output channels
+// 16 (w % 2) .. + 15 of rows 2 (w / 2), + 1 with all taps' accumulators in registers,
+// and the LDS transpose reads hand each lane 4 nodes of its channel (the K order is
+// the same for both operands, so any is right); swz leaves the 8 nodes' 32-byte halves
+// of such a read on distinct banks too.
+// db rides along as one product of the centre tap's operand with ones.
+// 4 images of 511 x 511: 145 us (dW, gathering 2-byte LDS reads) + 46 us (Y) as two
+// kernels, 53 us as one (201 MB of activations and gradients).
+__device__ __forceinline__ bf16x8 tr_read(const char* p, int second) {
+  typedef short s4 __attribute__((ext_vector_type(4)));
+  typedef short s8 __attribute__((ext_vector_type(8)));
+  typedef __attribute__((address_space(3))) s4* lp;
+  const s4 a = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(p));
+  const s4 b = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lp)(p + second));
+  const s8 v = __builtin_shufflevector(a, b, 0, 1, 2, 3, 4, 5, 6, 7);
+  return __builtin_bit_cast(bf16x8, v);
 }
 
-// ---------------------------------------------------------------------------
-// Weight gradients.  Every block writes one partial row (its share of the
-// pixel sum); reduce_rows adds the rows in a fixed order (deterministic).
-
-// The weight-gradient kernels walk 32-node row segments (persistent blocks,
-// segment seg = blockIdx.x, blockIdx.x + gridDim.x, ...), staging the segment
-// and the input rows around it in LDS.
-constexpr int kSeg = 32;
-
-// Output layer: part[blk][t * 32 + ic] = sum_p g[p] Y5[p + off_t][ic], part[blk][288] = sum_p g[p].
-// Thread j < 288 owns (t = j / 32, ic = j % 32), thread 288 the bias.
-__global__ void __launch_bounds__(320) dw_out(const float* __restrict__ g, const __bf16* __restrict__ Y,
-                                              float* __restrict__ part, int nx, int ny, int64_t nseg) {
-  __shared__ __attribute__((aligned(16))) __bf16 ys[3 * (kSeg + 2) * C];
-  __shared__ float gs[kSeg];
-  const int j = threadIdx.x;
-  const int t = j / C, ic = j % C;
-  const int r = t < 9 ? t / 3 : 0, xo = t < 9 ? t % 3 : 0;  // row and x offset (dx + 1) in the stage
-  float acc = 0.f;
-  const int nsx = (nx + kSeg - 1) / kSeg;
-  for (int64_t seg = blockIdx.x; seg < nseg; seg += gridDim.x) {
-    const int sx = int(seg % nsx);
-    const int64_t row = seg / nsx;
-    const int y = int(row % ny);
-    const int x0 = sx * kSeg;
-    __syncthreads();
-    for (int i = j; i < 3 * (kSeg + 2) * 4; i += blockDim.x) {
-      const int node = i >> 2, ch = (i & 3) * 8;
-      const int rr = node / (kSeg + 2), xi = node % (kSeg + 2);
-      const int yy = y + rr - 1, xx = x0 + xi - 1;
-      bf16x8 v = {};
-      if (yy >= 0 && yy < ny && xx >= 0 && xx < nx)
-        v = *reinterpret_cast<const bf16x8*>(Y + ((row + rr - 1) * nx + xx) * C + ch);
-      *reinterpret_cast<bf16x8*>(ys + node * C + ch) = v;
-    }
-    if (j < kSeg) gs[j] = (x0 + j < nx) ? g[row * nx + x0 + j] : 0.f;
-    __syncthreads();
-    if (j < SZ_W6) {
-#pragma unroll 8
-      for (int i = 0; i < kSeg; ++i) acc = fmaf(gs[i], float(ys[(r * (kSeg + 2) + i + xo) * C + ic]), acc);
-    } else if (j == SZ_W6) {
-      for (int i = 0; i < kSeg; ++i) acc += gs[i];
-    }
-  }
-  if (j < SZ_L6) part[int64_t(blockIdx.x) * SZ_L6 + j] = acc;
-}
-
-// Input layer: part[blk][(t * 2 + c) * 32 + oc] = sum_p X0[p + off_t][c] dZ1[p][oc],
-// part[blk][576 + oc] = sum_p dZ1[p][oc], X0 = (u_c, (u_c - u_n) / c_b).  Thread
-// j < 576 owns (t, c, oc), 576 + oc the bias.
-__global__ void __launch_bounds__(640) dw_in(const __bf16* __restrict__ dZ, const float* __restrict__ un,
-                                             const float* __restrict__ uc, const float* __restrict__ cs,
-                                             float* __restrict__ part, int nx, int ny, int64_t nseg) {
-  __shared__ float xs[2][3][kSeg + 2];
-  __shared__ __attribute__((aligned(16))) __bf16 zs[kSeg * C];
-  const int j = threadIdx.x;
-  const int t = j / (2 * C), c = (j / C) % 2, oc = j % C;
-  const int r = t < 9 ? t / 3 : 0, xo = t < 9 ? t % 3 : 0;
-  float acc = 0.f;
-  const int nsx = (nx + kSeg - 1) / kSeg;
-  for (int64_t seg = blockIdx.x; seg < nseg; seg += gridDim.x) {
-    const int sx = int(seg % nsx);
-    const int64_t row = seg / nsx;
-    const int y = int(row % ny);
-    const int x0 = sx * kSeg;
-    __syncthreads();
-    if (j < 2 * 3 * (kSeg + 2)) {
-      const int cc = j / (3 * (kSeg + 2)), node = j % (3 * (kSeg + 2));
-      const int rr = node / (kSeg + 2), xi = node % (kSeg + 2);
-      const int yy = y + rr - 1, xx = x0 + xi - 1;
-      float v = 0.f;
-      if (yy >= 0 && yy < ny && xx >= 0 && xx < nx) {
-        const int64_t q = (row + rr - 1) * nx + xx;
-        v = cc == 0 ? uc[q] : (uc[q] - un[q]) * (1.f / cs[row / ny]);
-      }
-      xs[cc][rr][xi] = v;
-    } else if (j >= 256 && j < 256 + kSeg * 4) {
-      const int k = j - 256;
-      const int xi = k >> 2, ch = (k & 3) * 8;
-      bf16x8 v = {};
-      if (x0 + xi < nx) v = *reinterpret_cast<const bf16x8*>(dZ + (row * nx + x0 + xi) * C + ch);
-      *reinterpret_cast<bf16x8*>(zs + xi * C + ch) = v;
-    }
-    __syncthreads();
-    if (j < SZ_W1) {
-#pragma unroll 8
-      for (int i = 0; i < kSeg; ++i) acc = fmaf(xs[c][r][i + xo], float(zs[i * C + oc]), acc);
-    } else if (j < SZ_L1) {
-      for (int i = 0; i < kSeg; ++i) acc += float(zs[i * C + oc]);
-    }
-  }
-  if (j < SZ_L1) part[int64_t(blockIdx.x) * SZ_L1 + j] = acc;
-}
-
-// 32 -> 32 layer on the matrix cores: dW[t][oc][ic] = sum_p dZ[p][oc] X[p + off_t][ic],
-// K = 32 nodes of one row per product.  A block stages a 32-node row segment of
-// dZ and the three input rows around it (34 nodes with the halo) in LDS; wave w
-// owns the output tile (oc tile w / 2, ic tile w % 2) for all 9 taps and gathers
-// its operands (8 consecutive nodes of one channel) from LDS.
-constexpr int kPs = 36;  // LDS node stride (BF16): 72 bytes, conflict-free gathers
-__global__ void __launch_bounds__(256) dw_mid(const __bf16* __restrict__ dZ, const __bf16* __restrict__ X,
-                                              float* __restrict__ part, int nx, int ny, int64_t nseg) {
-  __shared__ __attribute__((aligned(16))) __bf16 xs[3 * (kSeg + 2) * kPs];
-  __shared__ __attribute__((aligned(16))) __bf16 zs[kSeg * kPs];
+__global__ void __launch_bounds__(256, 2) conv_bwd(const __bf16* __restrict__ dZ, const __bf16* __restrict__ X,
+                                                   const __bf16* __restrict__ Wb, __bf16* __restrict__ Y,
+                                                   float* __restrict__ part, int nx, int ny, int64_t npatch) {
+  constexpr int kXRow = kPx * 64, kX = kPr * kXRow;
+  static_assert(kStage + kX >= SZ_LM * 4, "the block's partial row goes through the patch memory");
+  __shared__ __attribute__((aligned(16))) char lds[kStage + kX];
+  char* const zs = lds;
+  char* const xs = lds + kStage;
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int mt = wave >> 1, nt = wave & 1;
   const int col = lane & 15, q = lane >> 4;
-  f32x4 acc[9];
-#pragma unroll
-  for (int t = 0; t < 9; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-  float dbias = 0.f;
-  const int nsx = (nx + kSeg - 1) / kSeg;
-  for (int64_t seg = blockIdx.x; seg < nseg; seg += gridDim.x) {
-    const int sx = int(seg % nsx);
-    const int64_t row = seg / nsx;  // b * ny + y
-    const int y = int(row % ny);
-    const int x0 = sx * kSeg;
-    __syncthreads();
-    // stage: 3 rows x 34 nodes of X and 32 nodes of dZ, 4 chunks of 8 channels per node
-    for (int i = tid; i < (3 * (kSeg + 2) + kSeg) * 4; i += 256) {
-      const int node = i >> 2, ch = (i & 3) * 8;
-      bf16x8 v = {};
-      __bf16* dst;
-      if (node < 3 * (kSeg + 2)) {
-        const int r = node / (kSeg + 2), xi = node % (kSeg + 2);
-        const int yy = y + r - 1, xx = x0 + xi - 1;
-        if (yy >= 0 && yy < ny && xx >= 0 && xx < nx)
-          v = *reinterpret_cast<const bf16x8*>(X + ((row + r - 1) * nx + xx) * C + ch);
-        dst = xs + node * kPs + ch;
-      } else {
-        const int xi = node - 3 * (kSeg + 2);
-        const int xx = x0 + xi;
-        if (xx < nx) v = *reinterpret_cast<const bf16x8*>(dZ + (row * nx + xx) * C + ch);
-        dst = zs + xi * kPs + ch;
-      }
-      // 72-byte node stride: write as two 8-byte halves
-      bf16x4 lo = {v[0], v[1], v[2], v[3]}, hi = {v[4], v[5], v[6], v[7]};
-      *reinterpret_cast<bf16x4*>(dst) = lo;
-      *reinterpret_cast<bf16x4*>(dst + 4) = hi;
-    }
-    __syncthreads();
-    if (tid < C) {
-      float s = 0.f;
-      for (int xi = 0; xi < kSeg; ++xi) s += float(zs[xi * kPs + tid]);
-      dbias += s;
-    }
-    bf16x8 a;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) a[j] = zs[(8 * q + j) * kPs + mt * 16 + col];
-#pragma unroll
-    for (int t = 0; t < 9; ++t) {
-      const int r = tap_dy(t) + 1;
-      const int xb = 1 + tap_dx(t) + 8 * q;
-      bf16x8 b;
-#pragma unroll
-      for (int j = 0; j < 8; ++j) b[j] = xs[(r * (kSeg + 2) + xb + j) * kPs + nt * 16 + col];
-      acc[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, acc[t], 0, 0, 0);
-    }
-  }
-  float* prow = part + int64_t(blockIdx.x) * SZ_LM;
+  bf16x8 wa[9][2];
 #pragma unroll
   for (int t = 0; t < 9; ++t)
 #pragma unroll
-    for (int r = 0; r < 4; ++r) prow[(t * C + mt * 16 + 4 * q + r) * C + nt * 16 + col] = acc[t][r];
-  if (tid < C) prow[SZ_WM + tid] = dbias;
+    for (int mt = 0; mt < 2; ++mt)
+      wa[t][mt] = *reinterpret_cast<const bf16x8*>(Wb + (t * C + out_ch(mt, col)) * C + 8 * q);
+  // lane offsets: B operand of Y (per dx), mask, and the transpose reads of dZ (per dx) and X (per half)
+  const int mo = wave & 1, rp = wave >> 1;
+  int bo[3], zo[3], xo[2];
+  const int tn = 4 * q + (col >> 2);  // the transpose read's node
+#pragma unroll
+  for (int d = 0; d < 3; ++d) {
+    const int x = col + d, xt = tn + 2 - d;  // dx = d - 1: x + dx + 1, and x - dx + 1
+    bo[d] = wave * kRow + x * 64 + ((q ^ swz(x)) << 4);
+    zo[d] = 2 * rp * kRow + xt * 64 + (((2 * mo + ((col >> 1) & 1)) ^ swz(xt)) << 4) + (col & 1) * 8;
+  }
+#pragma unroll
+  for (int m = 0; m < 2; ++m)
+    xo[m] = 2 * rp * kXRow + tn * 64 + (((2 * m + ((col >> 1) & 1)) ^ swz(tn)) << 4) + (col & 1) * 8;
+  const int ko = wave * kXRow + col * 64 + ((q ^ swz(col)) << 4);
+  f32x4 dw[9][2], db = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+  for (int t = 0; t < 9; ++t) dw[t][0] = dw[t][1] = f32x4{0.f, 0.f, 0.f, 0.f};
+  bf16x8 ones;
+#pragma unroll
+  for (int j = 0; j < 8; ++j) ones[j] = __bf16(1.f);
+  const int npx = (nx + kPx - 1) / kPx;
+  const int npy = (ny + kPr - 1) / kPr;
+  const int sc = tid & 3, sx = tid >> 2;
+  Stage sg;
+  bf16x8 vx[kPr];
+  auto load = [&](int64_t pi) {
+    sg.load(dZ, pi, npatch, npx, npy, nx, ny);
+    const int64_t rest = pi / npx;
+    const int y0 = int(rest % npy) * kPr, gx = int(pi % npx) * kPx + sx;
+    const int64_t row0 = rest / npy * ny + y0;
+#pragma unroll
+    for (int r = 0; r < kPr; ++r) {
+      vx[r] = bf16x8{};
+      if (pi < npatch && y0 + r < ny && gx < nx)
+        vx[r] = *reinterpret_cast<const bf16x8*>(X + (row0 + r) * nx * C + gx * C + sc * 8);
+    }
+  };
+  load(blockIdx.x);
+  for (int64_t pi = blockIdx.x; pi < npatch; pi += gridDim.x) {
+    const int pxi = int(pi % npx);
+    const int64_t rest = pi / npx;
+    const int y0 = int(rest % npy) * kPr, x0 = pxi * kPx;
+    const int64_t b = rest / npy;
+    __syncthreads();
+    sg.store(zs);
+#pragma unroll
+    for (int r = 0; r < kPr; ++r)
+      *reinterpret_cast<bf16x8*>(xs + r * kXRow + sx * 64 + ((sc ^ swz(sx)) << 4)) = vx[r];
+    __syncthreads();
+    load(pi + gridDim.x);
+    const int y = y0 + wave;
+    if (y < ny) {
+      const int64_t rowoff = (b * ny + y) * nx;
+#pragma unroll
+      for (int tile = 0; tile < kPx / 16; ++tile) {
+        f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
+#pragma unroll
+        for (int t = 0; t < 9; ++t) {
+          const bf16x8 bfr = *reinterpret_cast<const bf16x8*>(zs + bo[t % 3] + (t / 3) * kRow + tile * 1024);
+#pragma unroll
+          for (int mt = 0; mt < 2; ++mt)
+            acc[mt] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wa[t][mt], bfr, acc[mt], 0, 0, 0);
+        }
+        const int px = x0 + tile * 16 + col;
+        if (px >= nx) continue;
+        const bf16x8 m = *reinterpret_cast<const bf16x8*>(xs + ko + tile * 1024);
+        bf16x8 o;
+#pragma unroll
+        for (int r = 0; r < 8; ++r) o[r] = float(m[r]) > 0.f ? __bf16(acc[r >> 2][r & 3]) : __bf16(0.f);
+        *reinterpret_cast<bf16x8*>(Y + (rowoff + px) * C + 8 * q) = o;
+      }
+    }
+#pragma unroll
+    for (int rr = 0; rr < 2; ++rr) {
+      if (y0 + 2 * rp + rr >= ny) break;
+#pragma unroll
+      for (int hb = 0; hb < kPx / 32; ++hb) {
+        const bf16x8 b0 = tr_read(xs + xo[0] + rr * kXRow + hb * 2048, 1024);
+        const bf16x8 b1 = tr_read(xs + xo[1] + rr * kXRow + hb * 2048, 1024);
+#pragma unroll
+        for (int t = 0; t < 9; ++t) {
+          const bf16x8 a = tr_read(zs + zo[t % 3] + (rr + 2 - t / 3) * kRow + hb * 2048, 1024);
+          dw[t][0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b0, dw[t][0], 0, 0, 0);
+          dw[t][1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b1, dw[t][1], 0, 0, 0);
+          if (t == 4) db = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, ones, db, 0, 0, 0);
+        }
+      }
+    }
+  }
+  // the two row pairs' sums, then the partial row
+  float* const red = reinterpret_cast<float*>(lds);
+  __syncthreads();
+  if (rp == 1) {
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+#pragma unroll
+      for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) red[(t * C + mo * 16 + 4 * q + r) * C + nt * 16 + col] = dw[t][nt][r];
+    if (col == 0)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) red[SZ_WM + mo * 16 + 4 * q + r] = db[r];
+  }
+  __syncthreads();
+  if (rp == 0) {
+    float* prow = part + int64_t(blockIdx.x) * SZ_LM;
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+#pragma unroll
+      for (int nt = 0; nt < 2; ++nt)
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int o = (t * C + mo * 16 + 4 * q + r) * C + nt * 16 + col;
+          prow[o] = dw[t][nt][r] + red[o];
+        }
+    if (col == 0)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const int o = SZ_WM + mo * 16 + 4 * q + r;
+        prow[o] = db[r] + red[o];
+      }
+  }
 }
 
-// out[o] = sum over rows of part[row][o]: 4 row slices per output, each summed
-// in double, then added in a fixed order (deterministic).
-__global__ void __launch_bounds__(256) reduce_rows(const float* __restrict__ part, int rows, int width,
-                                                   float* __restrict__ out) {
-  __shared__ double red[4][64];
+// The two vector-unit weight gradients (output and input layer) take strips of 16
+// nodes in x by `rows` rows: lane l of a wave holds channels 8 (l % 4) .. + 7 of node
+// l / 4 and walks down the rows with the 3 x 3 neighbourhood of the one- or
+// two-channel field in registers (three loads a row and channel), every tap's
+// accumulators of its channels in registers.  Two rows' loads are in flight while two
+// are computed: the registers leave two waves per SIMD, too few to hide the latency of
+// loads one row ahead (dw_in 52 us for 28).
+
+// The sums of N values (a multiple of 4) over the 16 lanes of equal l % 4.  The first
+// two steps halve the values a lane carries on, so that v[k], k < N / 4, of a lane
+// ends as value k + (l & 16 ? N / 4 : 0) + (l & 32 ? N / 2 : 0).
+template <int N>
+__device__ __forceinline__ void strip_sums(float (&v)[N]) {
+  static_assert(N % 4 == 0);
+  auto fold = [](float a, float b, bool wide) {
+    const uint32_t ia = __builtin_bit_cast(uint32_t, a), ib = __builtin_bit_cast(uint32_t, b);
+    const auto r = wide ? __builtin_amdgcn_permlane32_swap(ia, ib, false, false)
+                        : __builtin_amdgcn_permlane16_swap(ia, ib, false, false);
+    return __builtin_bit_cast(float, uint32_t(r[0])) + __builtin_bit_cast(float, uint32_t(r[1]));
+  };
+  auto ror = [](float a, auto ctrl) {
+    return a + __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, a), decltype(ctrl)::value,
+                                                                     0xf, 0xf, false));
+  };
+#pragma unroll
+  for (int k = 0; k < N / 2; ++k) v[k] = fold(v[k], v[k + N / 2], true);
+#pragma unroll
+  for (int k = 0; k < N / 4; ++k) {
+    v[k] = fold(v[k], v[k + N / 4], false);
+    v[k] = ror(v[k], std::integral_constant<int, 0x124>());  // row_ror:4
+    v[k] = ror(v[k], std::integral_constant<int, 0x128>());  // row_ror:8
+  }
+}
+
+// Output layer: dZ5[q][ic] = (Y5[q][ic] > 0) sum_t W6[t][ic] g[q - off_t], and the
+// block's share of dW6[t][ic] = sum_q Y5[q][ic] g[q - off_t] and of db6 = sum g
+// (part[blk][288]).  FP32 throughout (144 multiply-adds per 16 bytes of Y5).
+// 4 images of 511 x 511: 112 + 39 us as two kernels, 31 us as one (138 MB).
+__global__ void __launch_bounds__(256, 2) out_bwd(const float* __restrict__ g, const float* __restrict__ prm6,
+                                                  const __bf16* __restrict__ Y, __bf16* __restrict__ dZ,
+                                                  float* __restrict__ part, int nx, int ny, int rows, int nstrip) {
+  __shared__ float red[4][SZ_L6];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int ch = (lane & 3) * 8;
+  float w[9][8], acc[76] = {};  // acc[8 t + j], acc[72] = the sum of g
+
+#pragma unroll
+  for (int t = 0; t < 9; ++t)
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+      w[t][j] = prm6[t * C + ch + j];
+    }
+  const int nsx = (nx + 15) / 16, nsy = (ny + rows - 1) / rows;
+  for (int si = blockIdx.x * 4 + wave; si < nstrip; si += gridDim.x * 4) {
+    const int x = si % nsx * 16 + (lane >> 2), img = si / nsx / nsy;
+    const int y0 = si / nsx % nsy * rows, y1 = min(y0 + rows, ny);
+    const int base = img * ny;
+    // win[r][d]: g at row y - 1 + r, column x - 1 + d (zero outside, from an address kept inside)
+    float win[3][3];
+    const int xc[3] = {max(min(x, nx) - 1, 0), min(x, nx - 1), min(x + 1, nx - 1)};
+    const bool xin[3] = {x >= 1 && x <= nx, x < nx, x + 1 < nx};
+    auto load = [&](int yy, float (&v)[3]) {
+      const float* gr = g + (base + max(min(yy, ny - 1), 0)) * nx;
+#pragma unroll
+      for (int d = 0; d < 3; ++d) v[d] = gr[xc[d]];
+    };
+    auto field = [&](int yy, const float (&v)[3], float (&f)[3]) {
+#pragma unroll
+      for (int d = 0; d < 3; ++d) f[d] = yy >= 0 && yy < ny && xin[d] ? v[d] : 0.f;
+    };
+    auto node = [&](int yy) {
+      return yy < y1 && x < nx ? *reinterpret_cast<const bf16x8*>(Y + int64_t((base + yy) * nx + x) * C + ch) : bf16x8{};
+    };
+    bf16x8 m[2] = {node(y0), node(y0 + 1)};
+    float nw[2][3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) load(y0 - 1 + r, win[r]);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) load(y0 + 2 + k, nw[k]);
+#pragma unroll
+    for (int r = 0; r < 3; ++r) field(y0 - 1 + r, win[r], win[r]);
+    for (int y = y0; y < y1; y += 2) {
+      bf16x8 mc[2];
+      float wc[2][3];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        mc[k] = m[k];
+        m[k] = node(y + 2 + k);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) wc[k][d] = nw[k][d];
+        load(y + 4 + k, nw[k]);
+      }
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        if (y + k >= y1) break;
+        float z[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) z[j] = 0.f;
+#pragma unroll
+        for (int t = 0; t < 9; ++t) {
+          const float gv = win[2 - t / 3][2 - t % 3];
+#pragma unroll
+          for (int j = 0; j < 8; ++j) {
+            z[j] = fmaf(w[t][j], gv, z[j]);
+            acc[8 * t + j] = fmaf(gv, float(mc[k][j]), acc[8 * t + j]);
+          }
+        }
+        if (x < nx) {
+          acc[72] += win[1][1];
+          bf16x8 h;
+#pragma unroll
+          for (int j = 0; j < 8; ++j) h[j] = float(mc[k][j]) > 0.f ? __bf16(z[j]) : __bf16(0.f);
+          *reinterpret_cast<bf16x8*>(dZ + int64_t((base + y + k) * nx + x) * C + ch) = h;
+        }
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+          win[0][d] = win[1][d];
+          win[1][d] = win[2][d];
+        }
+        field(y + k + 2, wc[k], win[2]);
+      }
+    }
+  }
+  strip_sums(acc);
+  const int k0 = (lane & 16 ? 19 : 0) + (lane & 32 ? 38 : 0);
+  if ((lane & 12) == 0)
+#pragma unroll
+    for (int k = 0; k < 19; ++k) {
+      const int i = k0 + k;
+      if (i < 72) red[wave][(i >> 3) * C + ch + (i & 7)] = acc[k];
+      if (i == 72 && ch == 0) red[wave][SZ_W6] = acc[k];
+    }
+  __syncthreads();
+  for (int i = threadIdx.x; i < SZ_L6; i += 256)
+    part[int64_t(blockIdx.x) * SZ_L6 + i] = (red[0][i] + red[1][i]) + (red[2][i] + red[3][i]);
+}
+
+// Input layer: part[blk][(t * 2 + c) * 32 + oc] = the block's share of
+// sum_p X0[p + off_t][c] dZ1[p][oc], X0 = (u_c, (u_c - u_n) / c_b), and
+// part[blk][576 + oc] of sum_p dZ1[p][oc].  FP32 (152 operations per 16 bytes of dZ1).
+// 4 images of 511 x 511: 107 us with the operands read from LDS per product, 28 us
+// so (76 MB).
+__global__ void __launch_bounds__(256, 2) dw_in(const __bf16* __restrict__ dZ, const float* __restrict__ un,
+                                                const float* __restrict__ uc, const float* __restrict__ cs,
+                                                float* __restrict__ part, int nx, int ny, int rows, int nstrip) {
+  __shared__ float red[4][SZ_L1];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int ch = (lane & 3) * 8;
+  float acc[152] = {};  // acc[8 (2 t + c) + j], acc[144 + j] = the sum of dZ1
+  const int nsx = (nx + 15) / 16, nsy = (ny + rows - 1) / rows;
+  for (int si = blockIdx.x * 4 + wave; si < nstrip; si += gridDim.x * 4) {
+    const int x = si % nsx * 16 + (lane >> 2), img = si / nsx / nsy;
+    const int y0 = si / nsx % nsy * rows, y1 = min(y0 + rows, ny);
+    const int base = img * ny;
+    const float rc = 1.f / cs[img];
+    float w0[3][3], w1[3][3];
+    const int xc[3] = {max(min(x, nx) - 1, 0), min(x, nx - 1), min(x + 1, nx - 1)};
+    const bool xin[3] = {x >= 1 && x <= nx, x < nx, x + 1 < nx};
+    // a row's u_c and u_n as loaded (from addresses kept inside) ...
+    auto load = [&](int yy, float (&a)[3], float (&b)[3]) {
+      const int r = (base + max(min(yy, ny - 1), 0)) * nx;
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        a[d] = uc[r + xc[d]];
+        b[d] = un[r + xc[d]];
+      }
+    };
+    // ... and the channels from them
+    auto chan = [&](int yy, float (&a)[3], float (&b)[3]) {
+      const bool yin = yy >= 0 && yy < ny;
+#pragma unroll
+      for (int d = 0; d < 3; ++d) {
+        b[d] = yin && xin[d] ? (a[d] - b[d]) * rc : 0.f;
+        a[d] = yin && xin[d] ? a[d] : 0.f;
+      }
+    };
+    auto node = [&](int yy) {
+      return yy < y1 && x < nx ? *reinterpret_cast<const bf16x8*>(dZ + int64_t((base + yy) * nx + x) * C + ch) : bf16x8{};
+    };
+    bf16x8 z[2] = {node(y0), node(y0 + 1)};
+    float n0[2][3], n1[2][3];
+#pragma unroll
+    for (int r = 0; r < 3; ++r) load(y0 - 1 + r, w0[r], w1[r]);
+#pragma unroll
+    for (int k = 0; k < 2; ++k) load(y0 + 2 + k, n0[k], n1[k]);
+#pragma unroll
+    for (int r = 0; r < 3; ++r) chan(y0 - 1 + r, w0[r], w1[r]);
+    for (int y = y0; y < y1; y += 2) {
+      bf16x8 zc[2];
+      float c0[2][3], c1[2][3];
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        zc[k] = z[k];
+        z[k] = node(y + 2 + k);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+          c0[k][d] = n0[k][d];
+          c1[k][d] = n1[k][d];
+        }
+        load(y + 4 + k, n0[k], n1[k]);
+      }
+#pragma unroll
+      for (int k = 0; k < 2; ++k) {
+        if (y + k >= y1) break;
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+          const float v = float(zc[k][j]);
+          acc[144 + j] += v;
+#pragma unroll
+          for (int t = 0; t < 9; ++t) {
+            acc[16 * t + j] = fmaf(w0[t / 3][t % 3], v, acc[16 * t + j]);
+            acc[16 * t + 8 + j] = fmaf(w1[t / 3][t % 3], v, acc[16 * t + 8 + j]);
+          }
+        }
+        chan(y + k + 2, c0[k], c1[k]);
+#pragma unroll
+        for (int d = 0; d < 3; ++d) {
+          w0[0][d] = w0[1][d];
+          w0[1][d] = w0[2][d];
+          w0[2][d] = c0[k][d];
+          w1[0][d] = w1[1][d];
+          w1[1][d] = w1[2][d];
+          w1[2][d] = c1[k][d];
+        }
+      }
+    }
+  }
+  strip_sums(acc);
+  const int k0 = (lane & 16 ? 38 : 0) + (lane & 32 ? 76 : 0);
+  if ((lane & 12) == 0)
+#pragma unroll
+    for (int k = 0; k < 38; ++k) red[wave][((k0 + k) >> 3) * C + ch + ((k0 + k) & 7)] = acc[k];
+  __syncthreads();
+  for (int i = threadIdx.x; i < SZ_L1; i += 256)
+    part[int64_t(blockIdx.x) * SZ_L1 + i] = (red[0][i] + red[1][i]) + (red[2][i] + red[3][i]);
+}
+
+// out[o] = sum over rows of part[row][o]: 16 row slices per output, each summed
+// in double, then added in a fixed order (deterministic).  512 rows of 9248: 8 us
+// with 4 slices (a chain of loads), 4.8 us with 16.
+constexpr int kRedSlices = 16;
+__global__ void __launch_bounds__(64 * kRedSlices) reduce_rows(const float* __restrict__ part, int rows, int width,
+                                                              float* __restrict__ out) {
+  __shared__ double red[kRedSlices][64];
   const int oi = threadIdx.x % 64, sl = threadIdx.x / 64;
   const int o = blockIdx.x * 64 + oi;
   double s = 0.0;
   if (o < width) {
 #pragma unroll 8
-    for (int r = sl; r < rows; r += 4) s += double(part[int64_t(r) * width + o]);
+    for (int r = sl; r < rows; r += kRedSlices) s += double(part[int64_t(r) * width + o]);
   }
   red[sl][oi] = s;
   __syncthreads();
-  if (sl == 0 && o < width) out[o] = float(((red[0][oi] + red[1][oi]) + red[2][oi]) + red[3][oi]);
+  if (sl == 0 && o < width) {
+    for (int k = 1; k < kRedSlices; ++k) s += red[k][oi];
+    out[o] = float(s);
+  }
 }
 
 __global__ void reduce_loss(const double* __restrict__ part, int rows, double* __restrict__ out) {
@@ -810,7 +1034,7 @@ __global__ void __launch_bounds__(kFthreads) corr_fused(const float* __restrict_
   {
     constexpr int X1 = kFx + 10, XC = kFx + 12;
     constexpr int NT = (kFnA + 15) / 16;
-    InW w;
+    InW<false> w;
     w.load(prm, col, q);
     for (int tile = wave; tile < NT; tile += kFwaves) {
       const int f = tile * 16 + col;
@@ -1106,13 +1330,14 @@ void free_corr(eife_corr_s* c) {
 
 int grid1(int64_t n, int threads) { return int((n + threads - 1) / threads); }
 
-// Persistent blocks of the patch convolutions: at most 2 per compute unit,
-// so each block's register-held weights serve several patches.
+// Persistent blocks of the patch convolutions, so that a block's register-held
+// weights serve several patches: at most 2 per compute unit (their registers allow no
+// more), 4 for the one-output layer (4 images of 511 x 511: 29 us with 2, 22 with 4).
 int64_t n_patches(const eife_corr_s* c, int batch) {
   return int64_t(batch) * ((c->ny + kPr - 1) / kPr) * ((c->nx + kPx - 1) / kPx);
 }
 
-int patch_blocks(int64_t npatch) {
+int patch_blocks(int64_t npatch, int per_cu = 2) {
   static int cus = 0;
   if (cus == 0) {
     int dev = 0, v = 0;
@@ -1122,7 +1347,7 @@ int patch_blocks(int64_t npatch) {
     else
       cus = 256;
   }
-  return int(std::max<int64_t>(1, std::min<int64_t>(npatch, 2 * cus)));
+  return int(std::max<int64_t>(1, std::min<int64_t>(npatch, per_cu * cus)));
 }
 
 int refresh_copies(eife_corr_s* c, hipStream_t s, bool step, double lr) {
@@ -1159,17 +1384,26 @@ int check_batch(const eife_corr_s* c, int batch) {
   return EIFE_OK;
 }
 
+// Rows per strip: the most, up to 32, that give each of the `waves` that run at once a
+// strip (each starts with an exposed load), and no fewer than 4.
+int strip_rows(const eife_corr_s* c, int batch, int waves) {
+  int rows = 32;
+  while (rows > 4 && n_strips(c->nx, c->ny, batch, rows) < waves) rows /= 2;
+  return rows;
+}
+
 // Forward through the first five layers: the RMS coarse change, act[1..5].
 int forward_body(eife_corr_s* c, const float* un, const float* uc, int batch, hipStream_t s) {
   const int64_t npix = c->npix1 * batch;
   change_rms(c, un, uc, batch, s);
-  hipLaunchKernelGGL(conv_in_fwd, dim3(grid1(npix, 64)), dim3(256), 0, s, un, uc, c->cs, c->prm, c->act[1], c->nx,
-                     c->ny, npix);
+  const int rows = strip_rows(c, batch, 4096), ns = int(n_strips(c->nx, c->ny, batch, rows));
+  hipLaunchKernelGGL(conv_in_fwd, dim3(std::min((ns + 3) / 4, 1024)), dim3(256), 0, s, un, uc, c->cs, c->prm, c->act[1],
+                     c->nx, c->ny, rows, ns);
   const int64_t np = n_patches(c, batch);
   const int blocks = patch_blocks(np);
   for (int l = 0; l < N_MID; ++l)
     hipLaunchKernelGGL((conv_patch<CONV_FWD>), dim3(blocks), dim3(256), 0, s, c->act[l + 1], (void*)c->act[l + 2],
-                       c->wf + l * SZ_WM, c->prm + OFF_MID + l * SZ_LM + SZ_WM, (const __bf16*)nullptr, 0.f,
+                       c->wf + l * SZ_WM, c->prm + OFF_MID + l * SZ_LM + SZ_WM, 0.f,
                        (const float*)nullptr, (const float*)nullptr, (const float*)nullptr, (double*)nullptr, 0.0,
                        c->nx, c->ny, np);
   CHIP(hipGetLastError());
@@ -1182,32 +1416,30 @@ int grad_body(eife_corr_s* c, const float* un, const float* uc, const float* uf,
   CRET(forward_body(c, un, uc, batch, s));
   const int64_t np = n_patches(c, batch);
   const int blocks = patch_blocks(np);
-  hipLaunchKernelGGL((conv_patch<OUT_TRAIN>), dim3(blocks), dim3(256), 0, s, c->act[5], (void*)c->gout, c->w6b,
-                     c->prm + OFF_L6 + SZ_W6, (const __bf16*)nullptr, float(c->s_out), c->cs, uc, uf, c->dpart,
+  const int oblocks = patch_blocks(np, 4);
+  hipLaunchKernelGGL((conv_patch<OUT_TRAIN>), dim3(oblocks), dim3(256), 0, s, c->act[5], (void*)c->gout, c->w6b,
+                     c->prm + OFF_L6 + SZ_W6, float(c->s_out), c->cs, uc, uf, c->dpart,
                      1.0 / double(npix), c->nx, c->ny, np);
-  hipLaunchKernelGGL(reduce_loss, dim3(1), dim3(256), 0, s, c->dpart, blocks, c->dres);
+  hipLaunchKernelGGL(reduce_loss, dim3(1), dim3(256), 0, s, c->dpart, oblocks, c->dres);
+  auto reduce = [&](int rows, int width, float* dst) {
+    hipLaunchKernelGGL(reduce_rows, dim3(grid1(width, 64)), dim3(64 * kRedSlices), 0, s, c->part, rows, width, dst);
+  };
   // output layer
-  const int64_t nseg = int64_t(batch) * c->ny * ((c->nx + kSeg - 1) / kSeg);
-  hipLaunchKernelGGL(dw_out, dim3(kPartBlocks), dim3(320), 0, s, c->gout, c->act[5], c->part, c->nx, c->ny, nseg);
-  hipLaunchKernelGGL(reduce_rows, dim3(grid1(SZ_L6, 64)), dim3(256), 0, s, c->part, kPartBlocks, SZ_L6,
-                     c->grad + OFF_L6);
-  hipLaunchKernelGGL(conv_out_bwd, dim3(grid1(npix, 256)), dim3(256), 0, s, c->gout, c->prm + OFF_L6, c->act[5],
-                     c->dz[0], c->nx, c->ny, npix);
+  const int rows = strip_rows(c, batch, 4 * kPartBlocks), ns = int(n_strips(c->nx, c->ny, batch, rows));
+  const int sblocks = std::min((ns + 3) / 4, kPartBlocks), bblocks = std::min(blocks, kPartBlocks);
+  hipLaunchKernelGGL(out_bwd, dim3(sblocks), dim3(256), 0, s, c->gout, c->prm + OFF_L6, c->act[5], c->dz[0], c->part,
+                     c->nx, c->ny, rows, ns);
+  reduce(sblocks, SZ_L6, c->grad + OFF_L6);
   // 32 -> 32 layers, last to first: layer l maps act[l + 1] -> act[l + 2]
   int cur = 0;
   for (int l = N_MID - 1; l >= 0; --l) {
-    hipLaunchKernelGGL(dw_mid, dim3(kPartBlocks), dim3(256), 0, s, c->dz[cur], c->act[l + 1], c->part, c->nx, c->ny,
-                       nseg);
-    hipLaunchKernelGGL(reduce_rows, dim3(grid1(SZ_LM, 64)), dim3(256), 0, s, c->part, kPartBlocks, SZ_LM,
-                       c->grad + OFF_MID + l * SZ_LM);
-    hipLaunchKernelGGL((conv_patch<CONV_BWD>), dim3(blocks), dim3(256), 0, s, c->dz[cur], (void*)c->dz[1 - cur],
-                       c->wb + l * SZ_WM, (const float*)nullptr, c->act[l + 1], 0.f, (const float*)nullptr,
-                       (const float*)nullptr, (const float*)nullptr, (double*)nullptr, 0.0, c->nx, c->ny, np);
+    hipLaunchKernelGGL(conv_bwd, dim3(bblocks), dim3(256), 0, s, c->dz[cur], c->act[l + 1], c->wb + l * SZ_WM,
+                       c->dz[1 - cur], c->part, c->nx, c->ny, np);
+    reduce(bblocks, SZ_LM, c->grad + OFF_MID + l * SZ_LM);
     cur = 1 - cur;
   }
-  hipLaunchKernelGGL(dw_in, dim3(kPartBlocks), dim3(640), 0, s, c->dz[cur], un, uc, c->cs, c->part, c->nx, c->ny,
-                     nseg);
-  hipLaunchKernelGGL(reduce_rows, dim3(grid1(SZ_L1, 64)), dim3(256), 0, s, c->part, kPartBlocks, SZ_L1, c->grad);
+  hipLaunchKernelGGL(dw_in, dim3(sblocks), dim3(256), 0, s, c->dz[cur], un, uc, c->cs, c->part, c->nx, c->ny, rows, ns);
+  reduce(sblocks, SZ_L1, c->grad);
   CHIP(hipGetLastError());
   return EIFE_OK;
 }
@@ -1339,8 +1571,8 @@ int eife_corr_forward(eife_corr c, const float* un, const float* uc, float* delt
   }
   CRET(forward_body(c, un, uc, batch, s));
   const int64_t np = n_patches(c, batch);
-  hipLaunchKernelGGL((conv_patch<OUT_INFER>), dim3(patch_blocks(np)), dim3(256), 0, s, c->act[5], (void*)delta,
-                     c->w6b, c->prm + OFF_L6 + SZ_W6, (const __bf16*)nullptr, float(c->s_out), c->cs,
+  hipLaunchKernelGGL((conv_patch<OUT_INFER>), dim3(patch_blocks(np, 4)), dim3(256), 0, s, c->act[5], (void*)delta,
+                     c->w6b, c->prm + OFF_L6 + SZ_W6, float(c->s_out), c->cs,
                      (const float*)nullptr, (const float*)nullptr, (double*)nullptr, 0.0, c->nx, c->ny, np);
   CHIP(hipGetLastError());
   return EIFE_OK;
