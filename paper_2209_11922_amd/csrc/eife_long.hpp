@@ -1,18 +1,27 @@
 // Sine-transform passes for long lines: N = 1024, 2048 and 4096 intervals
-// (complex FFTs of L = 2048, 4096 and 8192 points of the odd extension of a
-// line pair, as in Section 4's per-dimension transforms; the packing is the one
-// of eife_kernels.hpp).
+// (complex FFTs of L = 2 N points of the odd extension of a line pair, as in
+// Section 4's per-dimension transforms; the packing is the one of eife_kernels.hpp).
 //
-// A wavefront cannot hold such a line, so one block transforms one line pair:
-// NT = L / 16 threads with 16 complex values each, Stockham stages of radix 16
-// (16^3 = 4096; a 2048-point line ends with a radix-8 stage, an 8192-point line
-// adds a final radix-2 stage) whose exchanges go through the pair's LDS buffer
-// with block barriers, and the last stage's outputs left in registers.  The
-// generic passes do every stage as a full LDS sweep; here the values stay in
-// registers between exchanges.  Each thread loads its twiddle generators once
-// per kernel (two per radix-16 stage, one for the last stage) and forms the
-// powers for each stage by products at most three deep, so no stage waits on
-// a table load.
+// The FFT is split as L = A M with M = 512 (A = 4, 8, 16): A-point butterflies over
+// the columns x_{j + M a}, a twiddle w_L^{j r}, and for each r an M-point FFT whose
+// output k' is Z_{r + A k'}.  The input is odd, x_{L-m} = -x_m, and so half of it is
+// never formed:
+//  - column M - j follows from column j: its butterfly outputs, twiddled, are
+//    G_{M-j}[r] = -conj(w_L^{j r}) F_j[A - r], so j = 0 .. M/2 are enough, and their
+//    upper inputs are mirrored nodes, x_{j + M (a + A/2)} = -x_{M - j + M (A/2 - 1 - a)};
+//  - Z_{L-k} = -Z_k: the transforms r and A - r hold the same outputs, so
+//    r = 0 .. A/2 are enough.
+// That is A/2 + 1 transforms of 512 instead of A, and as much of the line memory.
+// A wavefront takes one transform of 512 points, 8 values a lane in three radix-8
+// stages whose exchanges stay inside the wavefront's own piece of LDS (the first
+// wavefront takes r = 0 and A/2); the block synchronises only around the butterflies
+// and the node order.  4096 intervals in FP64 leave room for two blocks per compute
+// unit, one's memory accesses under the other's arithmetic.
+//
+// Against one block per pair with all L points in 16-point pieces per thread (8192 FP64
+// points fill LDS): 4096 x 2048 FP64 x pass 93 -> 49 us (134 MB), y stages 119 -> 94 and
+// 115 -> 90 us (268 MB); 4096 x 4096 FP32 x pass 72 -> 46 us, y stages 157 -> 146 us;
+// 1024 x 1024 FP64 23 -> 20.5 us; a single line of 4096 FP64 63 -> 37 us a step.
 #pragma once
 
 #include "eife_kernels.hpp"
@@ -22,213 +31,338 @@ namespace eife {
 namespace lng {
 
 using fast::DftN;
-using fast::xpad;
 
-template <int L>
+constexpr int kM = 512;  // points of a wavefront's transform
+
+template <int L, bool OWN>
 struct Shape {
-  static constexpr int E = 16;                        // complex values per thread
-  static constexpr int NT = L / E;                    // threads per line pair
-  static constexpr int BUF = ((L + L / 8 + 63) / 64) * 64 + 2;  // padded exchange buffer
-  static constexpr int RL = (L == 8192) ? 2 : (L == 2048 ? 8 : 16);  // radix of the last stage
-  static_assert(L == 2048 || L == 4096 || L == 8192, "long-line passes: 2048, 4096 or 8192 FFT points");
+  static constexpr int A = L / kM;
+  static constexpr int N = L / 2;
+  // Wavefronts per line pair: transform r = A / 2 has one of its own (OWN) where the
+  // shorter chain counts for more than the registers; else the first takes it after r = 0.
+  static constexpr int WAVES = A / 2 + (OWN ? 1 : 0);
+  static constexpr int NT = 64 * WAVES;           // threads per line pair
+  static constexpr int BUF = (A / 2 + 1) * kM;    // complex values of a line pair in LDS
+  static constexpr int COLS = kM / 2;             // butterfly columns (0 and M/2 share one)
+  static_assert(A == 4 || A == 8 || A == 16, "long-line passes: 2048, 4096 or 8192 FFT points");
+  static_assert(N + N / 16 + 9 <= BUF, "the node order fits");
 };
 
-// Registers per thread: FP32 8192-point lines fit 4 waves per SIMD (two blocks
-// per compute unit); the other shapes take what they need (FP32 2048-point
-// stage passes spill at 4).
-template <typename T, int L>
-struct LongWaves {
-  static constexpr int value = (sizeof(T) == 4 && L == 8192) ? 4 : 1;
-};
+// Position of node k = 0 .. N in LDS: one slot of padding every 16, for the outputs'
+// stride of A.
+__device__ __forceinline__ int node_pos(int k) { return k + (k >> 4); }
+// Start of pair p's node order within a block's LDS: the second of two pairs is moved by
+// half the banks, for lanes that take the two in turn.
+template <int L>
+__device__ __forceinline__ int pair_base(int p) {
+  return p * Shape<L, false>::BUF + 8 * (p & 1);
+}
+// Position of value i of a 512-point transform: neighbours in steps of 1, 8 and 64
+// all fall on distinct banks.
+__device__ __forceinline__ int fft_pos(int i) { return i ^ ((i >> 3) & 31); }
 
-// Twiddle generators of one thread (tw[i] = exp(-2 pi i i / L)): for the
-// stage after Ns = 16 points (radix 16) and the one after Ns = 256 (radix 16,
-// or 8 when L = 2048), g = W_L^{k S} and g4 = W_L^{4 k S} with k = t mod Ns
-// and S = L / (Ns R); for the radix-2 stage after Ns = 4096 (L = 8192), W_L^t.
-template <typename T, int L>
-struct LongTw {
-  Cx<T> a1, a4, b1, b4, c1;
-  __device__ __forceinline__ LongTw(const Cx<T>* __restrict__ tw, int t) {
-    constexpr int SA = L / 256;
-    constexpr int RB = L == 2048 ? 8 : 16;
-    constexpr int SB = L / (256 * RB);
-    a1 = tw[(t & 15) * SA];
-    a4 = tw[4 * (t & 15) * SA];
-    b1 = tw[(t & 255) * SB];
-    b4 = tw[4 * (t & 255) * SB];
-    c1 = L == 8192 ? tw[t] : Cx<T>{T(1), T(0)};
-  }
-};
-
-// Makes the generators opaque to the optimiser, so that a second transform
-// forms its powers again instead of keeping the first one's in registers.
-template <typename T, int L>
-__device__ __forceinline__ void refresh(LongTw<T, L>& gt) {
-  asm volatile("" : "+v"(gt.a1.re), "+v"(gt.a1.im), "+v"(gt.a4.re), "+v"(gt.a4.im), "+v"(gt.b1.re), "+v"(gt.b1.im),
-               "+v"(gt.b4.re), "+v"(gt.b4.im), "+v"(gt.c1.re), "+v"(gt.c1.im));
+// x as a value the optimiser knows nothing about: what is formed from it (LDS
+// addresses, table loads) stays where it is used instead of in registers throughout.
+__device__ __forceinline__ int fresh(int x) {
+  asm volatile("" : "+v"(x));
+  return x;
 }
 
-// p[q] = g^q, q = 1 .. R - 1 (R = 2, 8 or 16), from g and g4 = g^4: q = 4a + c
-// as g4^a g^c.
-template <typename T, int R>
-__device__ __forceinline__ void gen_powers(Cx<T> g, Cx<T> g4, Cx<T> (&p)[R]) {
-  p[1] = g;
-  if constexpr (R > 2) {
-    p[2] = cmul(g, g);
-    p[3] = cmul(p[2], g);
-    p[4] = g4;
-  }
-  if constexpr (R > 8) {
-    p[8] = cmul(g4, g4);
-    p[12] = cmul(p[8], g4);
-  }
-#pragma unroll
-  for (int q = 5; q < R; ++q)
-    if (q & 3) p[q] = cmul(p[q & ~3], p[q & 3]);
+// v[q] *= g^q, q = 1 .. 7, from g and g4 = g^4.
+template <typename T>
+__device__ __forceinline__ void twiddle8(Cx<T> (&v)[8], Cx<T> g, Cx<T> g4) {
+  const Cx<T> p2 = cmul(g, g), p3 = cmul(p2, g);
+  v[1] = cmul(v[1], g);
+  v[2] = cmul(v[2], p2);
+  v[3] = cmul(v[3], p3);
+  v[4] = cmul(v[4], g4);
+  v[5] = cmul(v[5], cmul(g4, g));
+  v[6] = cmul(v[6], cmul(g4, p2));
+  v[7] = cmul(v[7], cmul(g4, p3));
 }
 
-// Twiddle, butterflies and (unless LAST) the Stockham write of one stage of
-// radix R after Ns points: butterfly j = t + NT b reads inputs j + (L/R) q,
-// multiplies input q by W_{Ns R}^{(j mod Ns) q} = W_L^{(j mod Ns) q S}, S = L / (Ns R).
-// The thread's powers p[q] = W_L^{(t mod Ns) q S} come from its generators g,
-// g4; when NT < Ns, j mod Ns = t + NT b and the factor W_L^{NT b q S} is the
-// same for every thread (a table load from a uniform address).
-template <typename T, int L, int R, int Ns, bool LAST>
-__device__ __forceinline__ void stage(Cx<T> (&v)[16], Cx<T>* buf, const Cx<T>* __restrict__ tw, Cx<T> g,
-                                      Cx<T> g4, int t) {
-  constexpr int NT = Shape<L>::NT;
-  constexpr int NB = 16 / R;
-  constexpr int S = L / (Ns * R);
-  Cx<T> p[R];
-  if constexpr (Ns > 1) gen_powers<T, R>(g, g4, p);
+// NF 512-point FFTs of the wavefront's values z[fft_pos(i)], the second one's NEXT
+// values on: v[f][q] is output l + 64 q of FFT f.  fft_pos of l + 64 q, 8 l + q and
+// 64 (l / 8) + l % 8 + 8 q differ from q = 0 by an exclusive or and an offset.
+template <typename T, int L, int NF = 1, int NEXT = 0>
+__device__ __forceinline__ void fft512(Cx<T> (&v)[NF][8], Cx<T>* z, const Cx<T>* __restrict__ tw, int lane) {
+  const int l = fresh(lane);
+  // tw[i] = exp(-2 pi i i / L): first and fourth powers for the second and third stage
+  const Cx<T> a1 = tw[(l & 7) * (L / 64)], a4 = tw[4 * (l & 7) * (L / 64)];
+  const Cx<T> b1 = tw[l * (L / kM)], b4 = tw[4 * l * (L / kM)];
+  const int p = l ^ (l >> 3);
+  auto gather = [&]() {
 #pragma unroll
-  for (int b = 0; b < NB; ++b) {
-    if constexpr (Ns > 1) {
-      static_assert(NT % Ns == 0 || NT * NB <= Ns, "stage shape");
+    for (int f = 0; f < NF; ++f)
 #pragma unroll
-      for (int q = 1; q < R; ++q) {
-        Cx<T> w = p[q];
-        if constexpr (NT % Ns != 0)
-          if (b > 0) w = cmul(w, tw[(NT * b * q * S) & (L - 1)]);
-        v[b * R + q] = cmul(v[b * R + q], w);
+      for (int q = 0; q < 8; ++q) v[f][q] = z[(p ^ (8 * (q & 3))) + 64 * q + f * NEXT];
+  };
+  gather();
+#pragma unroll
+  for (int f = 0; f < NF; ++f) DftN<T, 8>::run(v[f]);
+  fast::wave_sync();
+  const int p8 = (8 * l) ^ (l & 31);
+#pragma unroll
+  for (int f = 0; f < NF; ++f)
+#pragma unroll
+    for (int q = 0; q < 8; ++q) (z + f * NEXT)[p8 ^ q] = v[f][q];
+  fast::wave_sync();
+  gather();
+#pragma unroll
+  for (int f = 0; f < NF; ++f) {
+    twiddle8(v[f], a1, a4);
+    DftN<T, 8>::run(v[f]);
+  }
+  fast::wave_sync();
+  const int p64 = (64 * (l >> 3) + (l & 7)) ^ (l & 24);
+#pragma unroll
+  for (int f = 0; f < NF; ++f)
+#pragma unroll
+    for (int q = 0; q < 8; ++q) (z + f * NEXT)[p64 ^ (9 * q)] = v[f][q];
+  fast::wave_sync();
+  gather();
+#pragma unroll
+  for (int f = 0; f < NF; ++f) {
+    twiddle8(v[f], b1, b4);
+    DftN<T, 8>::run(v[f]);
+  }
+}
+
+// Butterfly outputs r and A - r of column j into the r-th transform's values j and
+// M - j: y1 = w F_j[r], y2 = -conj(w) F_j[A - r].  Columns 0 and M/2, each its own
+// mirror image, went through one butterfly as their sum S: with S = F_0 + F_{M/2},
+// F_0[A - r] = -F_0[r] and F_{M/2}[A - r] = -w_A^r F_{M/2}[r],
+//   F_{M/2}[r] = (S[r] + S[A - r]) / (1 - w_A^r),  1 / (1 - w_A^r) = 1/2 - i/2 cot(pi r / A),
+// F_0[r] the rest, both zero at r = 0.
+template <typename T, int A, int R>
+__device__ __forceinline__ void put(Cx<T>* z, int j, Cx<T> w, Cx<T> fr, Cx<T> fm) {
+  // cot(pi r / 16) and exp(-i pi r / 16), r = 0 .. 8
+  constexpr double COT[9] = {0.0, 5.0273394921258481, 2.4142135623730950, 1.4966057626654890, 1.0,
+                             0.66817863791929892, 0.41421356237309505, 0.19891236737965801, 0.0};
+  constexpr double C[9] = {1.0, 0.98078528040323045, 0.92387953251128676, 0.83146961230254524, 0.70710678118654752,
+                           0.55557023301960222, 0.38268343236508977, 0.19509032201612827, 0.0};
+  constexpr int r16 = R * (16 / A);
+  Cx<T> y1 = cmul(w, fr), y2 = cmul(Cx<T>{w.re, -w.im}, fm);
+  y2 = Cx<T>{-y2.re, -y2.im};
+  int j2 = kM - j;
+  if (j == 0) {
+    j2 = kM / 2;
+    if constexpr (R == 0) {
+      y1 = y2 = Cx<T>{T(0), T(0)};
+    } else {
+      const Cx<T> s = cadd(fr, fm);
+      const T c = T(0.5 * COT[r16]);
+      const Cx<T> b{T(0.5) * s.re + c * s.im, T(0.5) * s.im - c * s.re};
+      y1 = csub(fr, b);
+      y2 = cmul(b, Cx<T>{T(C[r16]), T(-C[8 - r16])});
+    }
+  }
+  z[R * kM + fft_pos(j)] = y1;
+  z[R * kM + fft_pos(j2)] = y2;
+}
+
+// The butterflies of the line pair's nodes (node order, node 0 and N zero) into the
+// transforms' values (zn and z, in the same memory); every thread of the block takes part.
+template <typename T, int L, bool OWN>
+__device__ __forceinline__ void columns(Cx<T>* z, const Cx<T>* zn, const Cx<T>* __restrict__ tw, int thread) {
+  const int t = fresh(thread);
+  constexpr int A = Shape<L, OWN>::A, H = A / 2;
+  const bool on = !OWN || __builtin_amdgcn_readfirstlane(t) < 32 * A;  // an own wavefront of r = A / 2 only waits here
+  const Cx<T> g1 = tw[t & (Shape<L, OWN>::COLS - 1)], g2 = tw[2 * (t & (Shape<L, OWN>::COLS - 1))];  // w_L^j, w_L^{2 j}
+  // x_{j + M a} and the mirrored x_{M - j + M a}, a < A / 2
+  auto nodes = [&](int j, Cx<T> (&lo)[H], Cx<T> (&hi)[H]) {
+#pragma unroll
+    for (int a = 0; a < H; ++a) {
+      lo[a] = zn[node_pos(j + kM * a)];
+      hi[a] = zn[node_pos(kM - j + kM * a)];
+    }
+    if (j == 0) {
+#pragma unroll
+      for (int a = 0; a < H; ++a) {
+        const Cx<T> h = zn[node_pos(kM / 2 + kM * a)];
+        lo[a] = cadd(lo[a], h);
+        hi[a] = cadd(hi[a], h);
       }
     }
-    DftN<T, R>::run(&v[b * R]);
-  }
-  if constexpr (!LAST) {
-    // output q of butterfly j goes to (j - k) R + k + Ns q (k = j mod Ns), padded
-    // one slot every 8 (Ns is 1 or a multiple of 8, so every offset is exact)
+  };
+  if constexpr (A == 16) {
+    // two threads a column, the even and the odd outputs, from x_a + x_{a + 8} and
+    // x_a - x_{a + 8} (four at a time: sixteen values at once do not fit the registers)
+    const int j = t & 255;
+    const bool even = __builtin_amdgcn_readfirstlane(t) < 256;
+    const T sg = even ? T(-1) : T(1);
+    Cx<T> lo[8];
 #pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      const int j = t + NT * b;
-      const int k = j & (Ns - 1);
-      Cx<T>* o = buf + xpad((j - k) * R + k);
+    for (int h = 0; h < 8; h += 4) {
 #pragma unroll
-      for (int q = 0; q < R; ++q) o[q * Ns + (q * Ns) / 8] = v[b * R + q];
+      for (int a = h; a < h + 4; ++a) {
+        lo[a] = zn[node_pos(j + kM * a)];
+        Cx<T> hi = zn[node_pos(kM - j + kM * (7 - a))];
+        if (j == 0) {
+          lo[a] = cadd(lo[a], zn[node_pos(kM / 2 + kM * a)]);
+          hi = cadd(hi, zn[node_pos(kM / 2 + kM * (7 - a))]);
+        }
+        lo[a] = Cx<T>{fma(sg, hi.re, lo[a].re), fma(sg, hi.im, lo[a].im)};
+      }
+      __builtin_amdgcn_sched_barrier(0);
     }
-  }
-}
-
-// Inputs of a stage of radix R: v[b R + q] = buf at j + (L/R) q, j = t + NT b.
-template <typename T, int L, int R>
-__device__ __forceinline__ void gather(Cx<T> (&v)[16], const Cx<T>* buf, int t) {
-  constexpr int NT = Shape<L>::NT;
-  constexpr int S = L / R;
-  const Cx<T>* rb = buf + xpad(t);
-#pragma unroll
-  for (int b = 0; b < 16 / R; ++b)
-#pragma unroll
-    for (int q = 0; q < R; ++q) v[b * R + q] = rb[(NT * b + S * q) + (NT * b + S * q) / 8];
-}
-
-// Forward FFT of length L of the odd extension of the pair whose values sit at
-// node[0 .. N-2] (N = L / 2); node may overlay buf.  On return v[b RL + q] is
-// output t + NT b + q (L / RL).  Every thread of the block takes part.
-template <typename T, int L>
-__device__ __forceinline__ void odd_fft(Cx<T> (&v)[16], const Cx<T>* node, Cx<T>* buf,
-                                        const Cx<T>* __restrict__ tw, const LongTw<T, L>& gt, int t) {
-  constexpr int NT = Shape<L>::NT;
-  constexpr int N = L / 2;
-#pragma unroll
-  for (int q = 0; q < 16; ++q) {
-    const int m = t + NT * q;  // m < N exactly for q < 8
-    if (q < 8) {
-      v[q] = (m == 0) ? Cx<T>{T(0), T(0)} : node[m - 1];
-    } else if (m == N) {
-      v[q] = Cx<T>{T(0), T(0)};
+    __syncthreads();  // every node is read before its place is written
+    const Cx<T> w4 = cmul(g2, g2);
+    if (even) {
+      DftN<T, 8>::run(lo);
+      put<T, A, 0>(z, j, Cx<T>{T(1), T(0)}, lo[0], lo[0]);
+      put<T, A, 2>(z, j, g2, lo[1], lo[7]);
+      put<T, A, 4>(z, j, w4, lo[2], lo[6]);
+      put<T, A, 6>(z, j, cmul(w4, g2), lo[3], lo[5]);
+      put<T, A, 8>(z, j, cmul(w4, w4), lo[4], lo[4]);
     } else {
-      const Cx<T> c = node[2 * N - m - 1];
-      v[q] = Cx<T>{-c.re, -c.im};
+      const T c1 = T(0.92387953251128675613), s1 = T(0.38268343236508977173), h = T(0.70710678118654752440);
+      const Cx<T> w16[8] = {{T(1), T(0)}, {c1, -s1}, {h, -h}, {s1, -c1}, {T(0), T(-1)}, {-s1, -c1}, {-h, -h}, {-c1, -s1}};
+#pragma unroll
+      for (int a = 1; a < 8; ++a) lo[a] = cmul(lo[a], w16[a]);
+      DftN<T, 8>::run(lo);
+      const Cx<T> w3 = cmul(g1, g2);
+      put<T, A, 1>(z, j, g1, lo[0], lo[7]);
+      put<T, A, 3>(z, j, w3, lo[1], lo[6]);
+      put<T, A, 5>(z, j, cmul(g1, w4), lo[2], lo[5]);
+      put<T, A, 7>(z, j, cmul(w3, w4), lo[3], lo[4]);
     }
-  }
-  __syncthreads();  // every node value is read before the buffer is written
-  stage<T, L, 16, 1, false>(v, buf, tw, gt.a1, gt.a4, t);
-  __syncthreads();
-  gather<T, L, 16>(v, buf, t);
-  __syncthreads();
-  stage<T, L, 16, 16, false>(v, buf, tw, gt.a1, gt.a4, t);
-  __syncthreads();
-  if constexpr (L == 2048) {
-    gather<T, L, 8>(v, buf, t);
-    stage<T, L, 8, 256, true>(v, buf, tw, gt.b1, gt.b4, t);
-    __syncthreads();  // the buffer may be rewritten next
-    return;
-  }
-  gather<T, L, 16>(v, buf, t);
-  if constexpr (L == 8192) {
+  } else if constexpr (A == 8) {
+    const int j = t;
+    Cx<T> x[8];
+    if (on) {
+      Cx<T> lo[4], hi[4];
+      nodes(j, lo, hi);
+#pragma unroll
+      for (int a = 0; a < 4; ++a) {
+        x[a] = lo[a];
+        x[4 + a] = Cx<T>{-hi[3 - a].re, -hi[3 - a].im};
+      }
+    }
     __syncthreads();
-    stage<T, L, 16, 256, false>(v, buf, tw, gt.b1, gt.b4, t);
-    __syncthreads();
-    gather<T, L, 2>(v, buf, t);
-    stage<T, L, 2, 4096, true>(v, buf, tw, gt.c1, gt.c1, t);
+    if (!on) return;
+    DftN<T, 8>::run(x);
+    put<T, A, 0>(z, j, Cx<T>{T(1), T(0)}, x[0], x[0]);
+    put<T, A, 1>(z, j, g1, x[1], x[7]);
+    put<T, A, 2>(z, j, g2, x[2], x[6]);
+    put<T, A, 3>(z, j, cmul(g1, g2), x[3], x[5]);
+    put<T, A, 4>(z, j, cmul(g2, g2), x[4], x[4]);
   } else {
-    stage<T, L, 16, 256, true>(v, buf, tw, gt.b1, gt.b4, t);
-  }
-  __syncthreads();  // the buffer may be rewritten next
-}
-
-// The sine outputs k in [1, N-1] this thread holds: f(k, Z_k).
-template <typename T, int L, typename F>
-__device__ __forceinline__ void outputs(const Cx<T> (&v)[16], int t, F f) {
-  constexpr int NT = Shape<L>::NT;
-  constexpr int RL = Shape<L>::RL;
+    // two columns a thread: j and j + 128, w_L^{128} = w_16
+    Cx<T> x[2][4];
+    if (on) {
 #pragma unroll
-  for (int b = 0; b < 16 / RL; ++b)
-#pragma unroll
-    for (int q = 0; q < RL / 2; ++q) {
-      const int k = t + NT * b + q * (L / RL);
-      if (k >= 1) f(k, v[b * RL + q]);
+      for (int c = 0; c < 2; ++c) {
+        Cx<T> lo[2], hi[2];
+        nodes(t + 128 * c, lo, hi);
+        x[c][0] = lo[0];
+        x[c][1] = lo[1];
+        x[c][2] = Cx<T>{-hi[1].re, -hi[1].im};
+        x[c][3] = Cx<T>{-hi[0].re, -hi[0].im};
+      }
     }
+    __syncthreads();
+    if (!on) return;
+#pragma unroll
+    for (int c = 0; c < 2; ++c) {
+      const int j = t + 128 * c;
+      Cx<T> w1 = g1, w2 = g2;
+      if (c) {
+        w1 = cmul(g1, Cx<T>{T(0.92387953251128675613), T(-0.38268343236508977173)});
+        w2 = cmul(g2, Cx<T>{T(0.70710678118654752440), T(-0.70710678118654752440)});
+      }
+      DftN<T, 4>::run(x[c]);
+      put<T, A, 0>(z, j, Cx<T>{T(1), T(0)}, x[c][0], x[c][0]);
+      put<T, A, 1>(z, j, w1, x[c][1], x[c][3]);
+      put<T, A, 2>(z, j, w2, x[c][2], x[c][2]);
+    }
+  }
 }
 
-// The outputs k < N of a thread, numbered i = 0 .. COUNT-1: output index k(t, i)
-// and its register slot (same set as outputs(), which also skips k = 0).
-template <int L>
-struct OutIdx {
-  static constexpr int RL = Shape<L>::RL;
-  static constexpr int COUNT = (16 / RL) * (RL / 2);
-  static __device__ __forceinline__ int k(int t, int i) {
-    return t + Shape<L>::NT * (i / (RL / 2)) + (i % (RL / 2)) * (L / RL);
+// Sine transform of the line pair whose nodes are in zn (within z; node order; nodes 0 and N
+// zero), back into the same order: node k gets f(k, Z_k), k = 1 .. N - 1.  Every
+// thread of the block takes part.
+template <typename T, int L, bool OWN, typename F>
+__device__ __forceinline__ void sine(Cx<T>* z, Cx<T>* zn, const Cx<T>* __restrict__ tw, int t, F f) {
+  constexpr int A = Shape<L, OWN>::A;
+  const int r = __builtin_amdgcn_readfirstlane(t >> 6);
+  __syncthreads();
+  columns<T, L, OWN>(z, zn, tw, t);
+  __syncthreads();
+  Cx<T> v[1][8], e[4];
+  int l = t & 63;
+  if constexpr (!OWN && sizeof(T) == 4) {
+    if (r == 0) {
+      Cx<T> w[2][8];  // both at once: half the chain
+      fft512<T, L, 2, A / 2 * kM>(w, z, tw, l);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) {
+        e[q] = w[0][q];
+        v[0][q] = w[1][q];
+      }
+    } else {
+      fft512<T, L>(v, z + r * kM, tw, l);
+    }
+  } else {
+    if (!OWN && r == 0) {
+      fft512<T, L>(v, z, tw, l);
+#pragma unroll
+      for (int q = 0; q < 4; ++q) e[q] = v[0][q];
+    }
+    fft512<T, L>(v, z + (!OWN && r == 0 ? A / 2 : r) * kM, tw, l);
   }
-  static constexpr int slot(int i) { return (i / (RL / 2)) * RL + i % (RL / 2); }
+  __syncthreads();  // every value is read before its place is written
+  l = fresh(l);
+  if (r == 0 || (OWN && r == A / 2)) {
+    // these two hold each output twice
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int k = A * (l + 64 * q);
+      if (OWN) {
+        zn[node_pos(k + r)] = k + r ? f(k + r, v[0][q]) : Cx<T>{T(0), T(0)};
+      } else {
+        zn[node_pos(k)] = k ? f(k, e[q]) : Cx<T>{T(0), T(0)};
+        zn[node_pos(k + A / 2)] = f(k + A / 2, v[0][q]);
+      }
+    }
+    if (l == 0 && r == 0) zn[node_pos(L / 2)] = Cx<T>{T(0), T(0)};
+  } else {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const int k = r + A * (l + 64 * q);
+      if (q < 4)
+        zn[node_pos(k)] = f(k, v[0][q]);
+      else
+        zn[node_pos(L - k)] = f(L - k, Cx<T>{-v[0][q].re, -v[0][q].im});
+    }
+  }
+  __syncthreads();
+}
+
+// Registers: as many waves per SIMD as the blocks that fit a compute unit's LDS (at
+// most 4).
+template <typename T, int L, bool OWN, int NP>
+struct LongWaves {
+  static constexpr int blocks = 160 * 1024 / int(NP * Shape<L, OWN>::BUF * sizeof(Cx<T>));
+  static constexpr int all = blocks * NP * Shape<L, OWN>::WAVES / 4;
+  static constexpr int value = all > 4 ? 4 : (all < 1 ? 1 : all);
 };
 
 // Row pass (x lines, contiguous): one line pair (rows 2 blockIdx.x, +1) per
 // block; modes ROW_PHYS (inverse, reaction, forward), ROW_FWD_USER (forward of
 // the caller's array into dst and dst2) and ROW_INV_USER (inverse into dst).
-template <typename T, int L, int MODE, int RK>
-__global__ void __launch_bounds__((Shape<L>::NT), (LongWaves<T, L>::value))
+template <typename T, int L, bool OWN, int MODE, int RK>
+__global__ void __launch_bounds__((Shape<L, OWN>::NT), (LongWaves<T, L, OWN, 1>::value))
     row_long(const T* src, T* dst, T* dst2, RowGeom g, const Cx<T>* __restrict__ tw, Forcing F) {
-  constexpr int NT = Shape<L>::NT;
+  constexpr int NT = Shape<L, OWN>::NT;
   constexpr int N = L / 2;
   constexpr int n = N - 1;
   constexpr int RIT = (n + NT - 1) / NT;
-  __shared__ Cx<T> lds[Shape<L>::BUF];
+  __shared__ Cx<T> z[Shape<L, OWN>::BUF];
   const int t = threadIdx.x;
   const int ra = blockIdx.x * 2, rb = ra + 1;
   const bool hasb = rb < g.nrows;
   const T scale = T(1.0 / sqrt(double(L)));
-  LongTw<T, L> gt(tw, t);
   {
     const T* sa = src + int64_t(ra) * g.ld_src + t;
     const T* sb = src + int64_t(rb) * g.ld_src + t;
@@ -241,22 +375,17 @@ __global__ void __launch_bounds__((Shape<L>::NT), (LongWaves<T, L>::value))
     }
 #pragma unroll
     for (int i = 0; i < RIT; ++i)
-      if (t + NT * i < n) lds[t + NT * i] = Cx<T>{va[i], vb[i]};
+      if (t + NT * i <= n) z[node_pos(t + NT * i + 1)] = Cx<T>{va[i], vb[i]};  // node N = n + 1 too: zero
+    static_assert(NT * RIT > n, "node N is written");
+    if (t == 0) z[0] = Cx<T>{T(0), T(0)};
   }
-  __syncthreads();
-  Cx<T> v[16];
-  odd_fft<T, L>(v, lds, lds, tw, gt, t);
   if constexpr (MODE == ROW_PHYS) {
     const fast::RowReaction<T, RK> fa(F, ra % g.ny, ra / g.ny), fb(F, rb % g.ny, rb / g.ny);
-    outputs<T, L>(v, t, [&](int k, Cx<T> Z) {
-      lds[k - 1] = Cx<T>{fa(F, -Z.im * scale, k - 1), fb(F, Z.re * scale, k - 1)};
+    sine<T, L, OWN>(z, z, tw, t, [&](int k, Cx<T> Z) {
+      return Cx<T>{fa(F, -Z.im * scale, k - 1), fb(F, Z.re * scale, k - 1)};
     });
-    __syncthreads();
-    refresh(gt);
-    odd_fft<T, L>(v, lds, lds, tw, gt, t);
   }
-  outputs<T, L>(v, t, [&](int k, Cx<T> Z) { lds[k - 1] = Cx<T>{-Z.im * scale, Z.re * scale}; });
-  __syncthreads();
+  sine<T, L, OWN>(z, z, tw, t, [&](int, Cx<T> Z) { return Cx<T>{-Z.im * scale, Z.re * scale}; });
   T* da = dst + int64_t(ra) * g.ld_dst + t;
   T* db = dst + int64_t(rb) * g.ld_dst + t;
   T* da2 = dst2 + int64_t(ra) * g.ld_dst + t;
@@ -264,7 +393,7 @@ __global__ void __launch_bounds__((Shape<L>::NT), (LongWaves<T, L>::value))
 #pragma unroll
   for (int i = 0; i < RIT; ++i) {
     if (t + NT * i < n) {
-      const Cx<T> o = lds[t + NT * i];
+      const Cx<T> o = z[node_pos(t + NT * i + 1)];
       da[NT * i] = o.re;
       if (hasb) db[NT * i] = o.im;
       if constexpr (MODE == ROW_FWD_USER) {
@@ -275,182 +404,131 @@ __global__ void __launch_bounds__((Shape<L>::NT), (LongWaves<T, L>::value))
   }
 }
 
-// Column pass (strided axis): one column pair (columns 2 bx, 2 bx + 1 at outer
-// index by) per block, blocks in XCD-contiguous order so that the pairs of a
-// 128-byte line share one L2.  COL_PLAIN: forward transform; COL_STAGE_A,
-// COL_STAGE_B, COL_ETD1: forward, the diagonal stage with the spectral state H
-// (its values for this thread's outputs loaded before the transform), inverse.
-template <typename T, int L, int MODE>
-__global__ void __launch_bounds__((Shape<L>::NT), (LongWaves<T, L>::value))
-    col_long(T* W, T* H, ColGeom g, const Cx<T>* __restrict__ tw, Diag dg) {
-  constexpr int NT = Shape<L>::NT;
-  constexpr int N = L / 2;
-  constexpr int n = N - 1;
-  constexpr int RIT = (n + NT - 1) / NT;
-  constexpr int NO = OutIdx<L>::COUNT;
-  __shared__ Cx<T> lds[Shape<L>::BUF];
-  const int t = threadIdx.x;
-  int bx, outer;
-  xcd_block(bx, outer);
-  const int c0 = 2 * bx;
-  const int64_t base = int64_t(outer) * g.ld_outer + c0;
-  const T scale = T(1.0 / sqrt(double(L)));
-  LongTw<T, L> gt(tw, t);
-  Cx<T> hv[MODE == COL_PLAIN ? 1 : NO];
-  if constexpr (MODE != COL_PLAIN) {
-#pragma unroll
-    for (int i = 0; i < NO; ++i) {
-      const int k = OutIdx<L>::k(t, i);
-      hv[i] = (k >= 1) ? *reinterpret_cast<const Cx<T>*>(H + base + int64_t(k - 1) * g.ld_line) : Cx<T>{T(0), T(0)};
-    }
-  }
-#pragma unroll
-  for (int i = 0; i < RIT; ++i) {
-    const int m = t + NT * i;
-    if (m < n)
-      lds[m] = mask_pad(*reinterpret_cast<const Cx<T>*>(W + base + int64_t(m) * g.ld_line), c0, g.ncols);
-  }
-  __syncthreads();
-  Cx<T> v[16];
-  odd_fft<T, L>(v, lds, lds, tw, gt, t);
-  if constexpr (MODE != COL_PLAIN) {
-    const double tau = dg.tau, D = dg.D;
-    const double rtc2 = 1.0 / (tau * dg.c2);
-    const Sep sx0 = sep_load(dg.ax[0], c0), sx1 = sep_load(dg.ax[0], c0 + 1);
-    const Sep so = g.last_is_z ? sep_load(dg.ax[1], outer) : sep_load(dg.ax[2], 0);
-    const AxisTab line_tab = g.last_is_z ? dg.ax[2] : dg.ax[1];
-    const Sep s0 = sep_combine(sx0, so), s1 = sep_combine(sx1, so);
-#pragma unroll
-    for (int i = 0; i < NO; ++i) {
-      const int k = OutIdx<L>::k(t, i);
-      if (k < 1) continue;
-      const int m = k - 1;
-      const Cx<T> Z = v[OutIdx<L>::slot(i)];
-      const Sep sl = sep_load(line_tab, m);
-      double o0, o1, n0, n1;
-      fast::diag_fast<MODE>(sep_combine(s0, sl), D, tau, rtc2, double(-Z.im * scale), double(hv[i].re), &o0, &n0);
-      fast::diag_fast<MODE>(sep_combine(s1, sl), D, tau, rtc2, double(Z.re * scale), double(hv[i].im), &o1, &n1);
-      *reinterpret_cast<Cx<T>*>(H + base + int64_t(m) * g.ld_line) = mask_pad(Cx<T>{T(n0), T(n1)}, c0, g.ncols);
-      lds[m] = Cx<T>{T(o0), T(o1)};
-    }
-    __syncthreads();
-    refresh(gt);
-    odd_fft<T, L>(v, lds, lds, tw, gt, t);
-  }
-  outputs<T, L>(v, t, [&](int k, Cx<T> Z) { lds[k - 1] = Cx<T>{-Z.im * scale, Z.re * scale}; });
-  __syncthreads();
-#pragma unroll
-  for (int i = 0; i < RIT; ++i) {
-    const int m = t + NT * i;
-    if (m < n) *reinterpret_cast<Cx<T>*>(W + base + int64_t(m) * g.ld_line) = mask_pad(lds[m], c0, g.ncols);
-  }
-}
-
-// Columns c .. c + 3 of one row: one 16-byte access (FP32) or two adjacent
-// 16-byte accesses (FP64).
-template <typename T>
-__device__ __forceinline__ void load4(const T* p, Cx<T>& a, Cx<T>& b) {
-  if constexpr (sizeof(T) == 4) {
+// Column pass (strided axis): NP adjacent column pairs per block (columns
+// 2 NP bx .. at outer index by), each with its own threads and LDS.  In memory order
+// neighbouring lanes take the 16-byte parts of a row's columns (FP64: one pair, FP32:
+// two), so that a row's piece is one access (a lane taking both parts of an FP64 piece:
+// 115 us for 92 at 4096 x 2048).  Blocks run in XCD-contiguous order: the
+// pieces of a 128-byte line share one L2.  COL_PLAIN: forward transform; COL_STAGE_A,
+// COL_STAGE_B, COL_ETD1: forward, the diagonal stage over the coefficients in LDS with
+// the spectral state H (loaded before the transform), inverse.
+template <typename T, int NP>
+struct Piece {
+  static constexpr int V = (sizeof(T) == 4 && NP % 2 == 0) ? 2 : 1;  // pairs per lane
+  static constexpr int LANES = NP / V;                               // lanes per row
+};
+template <typename T, int V>
+__device__ __forceinline__ void load_pairs(const T* p, Cx<T> (&v)[V]) {
+  if constexpr (V == 2) {
     const float4 w = *reinterpret_cast<const float4*>(p);
-    a = Cx<T>{w.x, w.y};
-    b = Cx<T>{w.z, w.w};
+    v[0] = Cx<T>{w.x, w.y};
+    v[1] = Cx<T>{w.z, w.w};
   } else {
-    a = reinterpret_cast<const Cx<T>*>(p)[0];
-    b = reinterpret_cast<const Cx<T>*>(p)[1];
+    v[0] = *reinterpret_cast<const Cx<T>*>(p);
   }
 }
-template <typename T>
-__device__ __forceinline__ void store4(T* p, Cx<T> a, Cx<T> b) {
-  if constexpr (sizeof(T) == 4) {
+template <typename T, int V>
+__device__ __forceinline__ void store_pairs(T* p, const Cx<T> (&v)[V], int c, int ncols) {
+  const Cx<T> a = mask_pad(v[0], c, ncols);
+  if constexpr (V == 2) {
+    const Cx<T> b = mask_pad(v[1], c + 2, ncols);
     *reinterpret_cast<float4*>(p) = float4{a.re, a.im, b.re, b.im};
   } else {
-    reinterpret_cast<Cx<T>*>(p)[0] = a;
-    reinterpret_cast<Cx<T>*>(p)[1] = b;
+    *reinterpret_cast<Cx<T>*>(p) = a;
   }
 }
 
-// Column pass over two adjacent column pairs per block: columns c0 .. c0+3 of
-// a row are read and written as one piece (16 bytes FP32, 32 bytes FP64),
-// which halves the memory requests of the strided axis against one pair per
-// block.  Threads [0, NT) transform the first pair and [NT, 2 NT) the second,
-// each in its own LDS buffer (two FP64 buffers fit up to 4096 points); the
-// diagonal stage runs row by row over the sine coefficients both halves left
-// in LDS, so H moves as whole row pieces as well.  Modes as col_long; blocks
-// in XCD-contiguous order.
-template <typename T, int L, int MODE>
-__global__ void __launch_bounds__((2 * Shape<L>::NT), (LongWaves<T, L>::value))
-    col_long4(T* W, T* H, ColGeom g, const Cx<T>* __restrict__ tw, Diag dg) {
-  static_assert(2 * Shape<L>::BUF * sizeof(Cx<T>) <= 160 * 1024, "two pair buffers per block");
-  constexpr int NT = Shape<L>::NT;
-  constexpr int N = L / 2;
-  constexpr int n = N - 1;
-  constexpr int RIT = (n + 2 * NT - 1) / (2 * NT);
-  __shared__ Cx<T> lds2[2][Shape<L>::BUF];
-  const int half = int(threadIdx.x) / NT;  // uniform per wavefront (NT is a multiple of 64)
-  const int t = int(threadIdx.x) - half * NT;
-  const int tb = int(threadIdx.x);
-  Cx<T>* lds = lds2[half];
+template <typename T, int L, bool OWN, int NP, int MODE>
+__global__ void __launch_bounds__((NP * Shape<L, OWN>::NT), (LongWaves<T, L, OWN, NP>::value))
+    col_long(T* W, T* H, ColGeom g, const Cx<T>* __restrict__ tw, Diag dg) {
+  constexpr int NT = Shape<L, OWN>::NT, NB = NP * NT, BUF = Shape<L, OWN>::BUF;
+  constexpr int V = Piece<T, NP>::V, LR = Piece<T, NP>::LANES;
+  constexpr int n = L / 2 - 1, MS = NB / LR;  // rows per sweep
+  constexpr int RIT = (n + MS - 1) / MS;
+  __shared__ Cx<T> zs[NP * BUF];
+  const int tb = threadIdx.x;
+  const int pair = NP == 1 ? 0 : __builtin_amdgcn_readfirstlane(tb / NT);
+  const int t = tb - pair * NT;
   int bx, outer;
   xcd_block(bx, outer);
-  const int c0 = 4 * bx;
-  const int64_t base = int64_t(outer) * g.ld_outer + c0;
+  const int p0 = LR == 1 ? 0 : (tb % LR) * V, m0 = tb / LR;  // the lane's pair(s) and first row
+  const int c = 2 * (NP * bx + p0);
+  const int64_t base = int64_t(outer) * g.ld_outer + c;
   const T scale = T(1.0 / sqrt(double(L)));
-  LongTw<T, L> gt(tw, t);
+  // H ahead of the transform where the registers allow
+  constexpr bool AHEAD = MODE != COL_PLAIN && (sizeof(T) == 4 || Shape<L, OWN>::A < 16);
+  Cx<T> hv[AHEAD ? RIT : 1][V];
+  {
+    Cx<T> v[RIT][V];
 #pragma unroll
-  for (int i = 0; i < RIT; ++i) {
-    const int m = tb + 2 * NT * i;
-    if (m < n) {
-      Cx<T> a, b;
-      load4(W + base + int64_t(m) * g.ld_line, a, b);
-      lds2[0][m] = mask_pad(a, c0, g.ncols);
-      lds2[1][m] = mask_pad(b, c0 + 2, g.ncols);
+    for (int i = 0; i < RIT; ++i) {
+#pragma unroll
+      for (int e = 0; e < V; ++e) v[i][e] = Cx<T>{T(0), T(0)};
+      if (m0 + MS * i < n) load_pairs<T, V>(W + base + int64_t(m0 + MS * i) * g.ld_line, v[i]);
     }
+    if constexpr (AHEAD) {
+#pragma unroll
+      for (int i = 0; i < RIT; ++i) {
+#pragma unroll
+        for (int e = 0; e < V; ++e) hv[i][e] = Cx<T>{T(0), T(0)};
+        if (m0 + MS * i < n) load_pairs<T, V>(H + base + int64_t(m0 + MS * i) * g.ld_line, hv[i]);
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < RIT; ++i)
+#pragma unroll
+      for (int e = 0; e < V; ++e)
+        if (m0 + MS * i <= n)  // node N = n + 1 too: zero
+          zs[pair_base<L>(p0 + e) + node_pos(m0 + MS * i + 1)] = mask_pad(v[i][e], c + 2 * e, g.ncols);
+    static_assert(MS * RIT > n, "node N is written");
+    if (tb < NP) zs[pair_base<L>(tb)] = Cx<T>{T(0), T(0)};
   }
-  __syncthreads();
-  Cx<T> v[16];
-  odd_fft<T, L>(v, lds, lds, tw, gt, t);
+  Cx<T>* z = zs + pair * BUF;
+  sine<T, L, OWN>(z, zs + pair_base<L>(pair), tw, t, [&](int, Cx<T> Z) { return Cx<T>{-Z.im * scale, Z.re * scale}; });
   if constexpr (MODE != COL_PLAIN) {
-    outputs<T, L>(v, t, [&](int k, Cx<T> Z) { lds[k - 1] = Cx<T>{-Z.im * scale, Z.re * scale}; });
-    __syncthreads();
     const double tau = dg.tau, D = dg.D;
     const double rtc2 = 1.0 / (tau * dg.c2);
     const Sep so = g.last_is_z ? sep_load(dg.ax[1], outer) : sep_load(dg.ax[2], 0);
     const AxisTab line_tab = g.last_is_z ? dg.ax[2] : dg.ax[1];
+    const int mr = fresh(m0);
 #pragma unroll
     for (int i = 0; i < RIT; ++i) {
-      const int m = tb + 2 * NT * i;
+      if (sizeof(T) == 8 && i % 2 == 0) __builtin_amdgcn_sched_barrier(0);  // the rows' tables two at a time
+      const int m = mr + MS * i;
       if (m >= n) continue;
-      Cx<T> ha, hb;
-      load4(H + base + int64_t(m) * g.ld_line, ha, hb);
-      const Cx<T> a = lds2[0][m], b = lds2[1][m];
       const Sep sl = sep_load(line_tab, m);
-      const T gin[4] = {a.re, a.im, b.re, b.im};
-      const T hin[4] = {ha.re, ha.im, hb.re, hb.im};
-      T o[4], nh[4];
+      Cx<T> nh[V], h[V];
+      if constexpr (AHEAD) {
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        double oq, nq;
-        fast::diag_fast<MODE>(sep_combine(sep_combine(sep_load(dg.ax[0], c0 + q), so), sl), D, tau, rtc2,
-                              double(gin[q]), double(hin[q]), &oq, &nq);
-        o[q] = T(oq);
-        nh[q] = T(nq);
+        for (int e = 0; e < V; ++e) h[e] = hv[i][e];
+      } else {
+        load_pairs<T, V>(H + base + int64_t(m) * g.ld_line, h);
       }
-      const Cx<T> h0 = mask_pad(Cx<T>{nh[0], nh[1]}, c0, g.ncols), h1 = mask_pad(Cx<T>{nh[2], nh[3]}, c0 + 2, g.ncols);
-      store4(H + base + int64_t(m) * g.ld_line, h0, h1);
-      lds2[0][m] = Cx<T>{o[0], o[1]};
-      lds2[1][m] = Cx<T>{o[2], o[3]};
+#pragma unroll
+      for (int e = 0; e < V; ++e) {
+        Cx<T>* const zp = zs + pair_base<L>(p0 + e) + node_pos(m + 1);
+        const Cx<T> a = *zp;
+        double o0, o1, n0, n1;
+        fast::diag_fast<MODE>(sep_combine(sep_combine(sep_load(dg.ax[0], c + 2 * e), so), sl), D, tau, rtc2,
+                              double(a.re), double(h[e].re), &o0, &n0);
+        fast::diag_fast<MODE>(sep_combine(sep_combine(sep_load(dg.ax[0], c + 2 * e + 1), so), sl), D, tau, rtc2,
+                              double(a.im), double(h[e].im), &o1, &n1);
+        nh[e] = Cx<T>{T(n0), T(n1)};
+        *zp = Cx<T>{T(o0), T(o1)};
+      }
+      store_pairs<T, V>(H + base + int64_t(m) * g.ld_line, nh, c, g.ncols);
     }
-    __syncthreads();
-    refresh(gt);
-    odd_fft<T, L>(v, lds, lds, tw, gt, t);
+    sine<T, L, OWN>(z, zs + pair_base<L>(pair), tw, t, [&](int, Cx<T> Z) { return Cx<T>{-Z.im * scale, Z.re * scale}; });
   }
-  outputs<T, L>(v, t, [&](int k, Cx<T> Z) { lds[k - 1] = Cx<T>{-Z.im * scale, Z.re * scale}; });
-  __syncthreads();
+  const int mr = fresh(m0);
 #pragma unroll
   for (int i = 0; i < RIT; ++i) {
-    const int m = tb + 2 * NT * i;
+    const int m = mr + MS * i;
     if (m < n) {
-      store4(W + base + int64_t(m) * g.ld_line, mask_pad(lds2[0][m], c0, g.ncols), mask_pad(lds2[1][m], c0 + 2, g.ncols));
+      Cx<T> v[V];
+#pragma unroll
+      for (int e = 0; e < V; ++e) v[e] = zs[pair_base<L>(p0 + e) + node_pos(m + 1)];
+      store_pairs<T, V>(W + base + int64_t(m) * g.ld_line, v, c, g.ncols);
     }
   }
 }

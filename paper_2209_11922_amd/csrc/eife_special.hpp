@@ -323,61 +323,79 @@ bool try_col_fast_per(const eife_grid_s* g, int axis, int mode, int outer, int c
 }
 
 // Lines of 1024, 2048 and 4096 intervals (2048-, 4096- and 8192-point odd
-// extensions): one line pair per block (eife_long.hpp); single grids,
-// non-periodic.
+// extensions; eife_long.hpp); single grids, non-periodic.
 inline bool long_len(int N) { return N == 1024 || N == 2048 || N == 4096; }
 
 template <typename T, int L>
 void row_long_launch(int mode, int nrows, hipStream_t s, const T* src, T* dst, T* dst2, const RowGeom& rg,
                      const Cx<T>* tw, const Forcing& F) {
-  constexpr int NT = lng::Shape<L>::NT;
+  constexpr bool OWN = L == 2048 || (L == 4096 && sizeof(T) == 4);  // else the registers are short
+  constexpr int NT = lng::Shape<L, OWN>::NT;
   const dim3 grid((nrows + 1) / 2);
-  if (!launch_shape_ok(grid, NT, lng::Shape<L>::BUF * sizeof(Cx<T>))) return;
+  if (!launch_shape_ok(grid, NT, lng::Shape<L, OWN>::BUF * sizeof(Cx<T>))) return;
   if (mode == ROW_PHYS) {
     if (F.kind == FK_AC)
-      hipLaunchKernelGGL((lng::row_long<T, L, ROW_PHYS, fast::RK_AC>), grid, dim3(NT), 0, s, src, dst, dst2, rg, tw, F);
+      hipLaunchKernelGGL((lng::row_long<T, L, OWN, ROW_PHYS, fast::RK_AC>), grid, dim3(NT), 0, s, src, dst, dst2, rg, tw, F);
     else if (F.kind == FK_EX52)
-      hipLaunchKernelGGL((lng::row_long<T, L, ROW_PHYS, fast::RK_WAVE>), grid, dim3(NT), 0, s, src, dst, dst2, rg, tw, F);
+      hipLaunchKernelGGL((lng::row_long<T, L, OWN, ROW_PHYS, fast::RK_WAVE>), grid, dim3(NT), 0, s, src, dst, dst2, rg, tw, F);
     else
-      hipLaunchKernelGGL((lng::row_long<T, L, ROW_PHYS, fast::RK_GENERIC>), grid, dim3(NT), 0, s, src, dst, dst2, rg, tw,
+      hipLaunchKernelGGL((lng::row_long<T, L, OWN, ROW_PHYS, fast::RK_GENERIC>), grid, dim3(NT), 0, s, src, dst, dst2, rg, tw,
                          F);
   } else if (mode == ROW_FWD_USER) {
-    hipLaunchKernelGGL((lng::row_long<T, L, ROW_FWD_USER, fast::RK_GENERIC>), grid, dim3(NT), 0, s, src, dst, dst2, rg,
+    hipLaunchKernelGGL((lng::row_long<T, L, OWN, ROW_FWD_USER, fast::RK_GENERIC>), grid, dim3(NT), 0, s, src, dst, dst2, rg,
                        tw, F);
   } else {
-    hipLaunchKernelGGL((lng::row_long<T, L, ROW_INV_USER, fast::RK_GENERIC>), grid, dim3(NT), 0, s, src, dst, dst2, rg,
+    hipLaunchKernelGGL((lng::row_long<T, L, OWN, ROW_INV_USER, fast::RK_GENERIC>), grid, dim3(NT), 0, s, src, dst, dst2, rg,
                        tw, F);
   }
+}
+
+template <typename T, int L, bool OWN, int NP>
+void col_long_np(int mode, int pitch, int outer, hipStream_t s, T* W, T* H, const ColGeom& cg, const Cx<T>* tw,
+                 const Diag& dg) {
+  constexpr int NT = NP * lng::Shape<L, OWN>::NT;
+  const dim3 grid(pitch / (2 * NP), outer);
+  if (!launch_shape_ok(grid, NT, NP * lng::Shape<L, OWN>::BUF * sizeof(Cx<T>))) return;
+  if (mode == COL_PLAIN)
+    hipLaunchKernelGGL((lng::col_long<T, L, OWN, NP, COL_PLAIN>), grid, dim3(NT), 0, s, W, H, cg, tw, dg);
+  else if (mode == COL_STAGE_A)
+    hipLaunchKernelGGL((lng::col_long<T, L, OWN, NP, COL_STAGE_A>), grid, dim3(NT), 0, s, W, H, cg, tw, dg);
+  else if (mode == COL_STAGE_B)
+    hipLaunchKernelGGL((lng::col_long<T, L, OWN, NP, COL_STAGE_B>), grid, dim3(NT), 0, s, W, H, cg, tw, dg);
+  else
+    hipLaunchKernelGGL((lng::col_long<T, L, OWN, NP, COL_ETD1>), grid, dim3(NT), 0, s, W, H, cg, tw, dg);
 }
 
 template <typename T, int L>
 void col_long_launch(int mode, int pitch, int outer, hipStream_t s, T* W, T* H, const ColGeom& cg, const Cx<T>* tw,
                      const Diag& dg) {
-  constexpr int NT = lng::Shape<L>::NT;
-  if constexpr (2 * lng::Shape<L>::BUF * sizeof(Cx<T>) <= 160 * 1024) {
-    // two column pairs (a 16- or 32-byte row piece) per block of 2 NT threads (FP32, and FP64 up to
-    // 4096 points); the pitch is a multiple of 32
-    const dim3 grid(pitch / 4, outer);
-    if (!launch_shape_ok(grid, 2 * NT, 2 * lng::Shape<L>::BUF * sizeof(Cx<T>))) return;
-    if (mode == COL_PLAIN)
-      hipLaunchKernelGGL((lng::col_long4<T, L, COL_PLAIN>), grid, dim3(2 * NT), 0, s, W, H, cg, tw, dg);
-    else if (mode == COL_STAGE_A)
-      hipLaunchKernelGGL((lng::col_long4<T, L, COL_STAGE_A>), grid, dim3(2 * NT), 0, s, W, H, cg, tw, dg);
-    else if (mode == COL_STAGE_B)
-      hipLaunchKernelGGL((lng::col_long4<T, L, COL_STAGE_B>), grid, dim3(2 * NT), 0, s, W, H, cg, tw, dg);
-    else
-      hipLaunchKernelGGL((lng::col_long4<T, L, COL_ETD1>), grid, dim3(2 * NT), 0, s, W, H, cg, tw, dg);
+  // Wider row pieces (two pairs: 16 bytes FP32, 32 bytes FP64) cost fewer memory requests,
+  // narrower ones leave more blocks; the pitch is a multiple of 32.  Measured per step:
+  //  - 1024 intervals, at most two blocks of two pairs a compute unit: a short chain counts
+  //    (own wavefront for r = A / 2; 64 x 1024 FP32 36 -> 32 us); more: 64 x 64 x 1024 FP64
+  //    209 us with it, 184 without;
+  //  - 4096 FP64: two pairs leave one block a compute unit; 4096 x 4096 554 us, one pair
+  //    per block 810; 64 x 4096 (16 blocks) 95 us, one pair 73;
+  //  - FP32 1024 and 2048: four pairs from two blocks of two a compute unit on
+  //    (64 x 64 x 1024 153 -> 143 us, 2048 x 2048 104 -> 101); 2048 on less than one block
+  //    a compute unit: one pair (64 x 2048 47 -> 40 us).
+  const int64_t blocks = int64_t(pitch / 4) * outer;
+  if constexpr (L == 2048) {
+    if (blocks <= 2 * g_cus) return col_long_np<T, L, true, 2>(mode, pitch, outer, s, W, H, cg, tw, dg);
+  }
+  if constexpr (sizeof(T) == 8) {
+    if constexpr (L == 8192) {
+      if (blocks <= g_cus) return col_long_np<T, L, false, 1>(mode, pitch, outer, s, W, H, cg, tw, dg);
+    }
+    col_long_np<T, L, false, 2>(mode, pitch, outer, s, W, H, cg, tw, dg);
   } else {
-    const dim3 grid(pitch / 2, outer);
-    if (!launch_shape_ok(grid, NT, lng::Shape<L>::BUF * sizeof(Cx<T>))) return;
-    if (mode == COL_PLAIN)
-      hipLaunchKernelGGL((lng::col_long<T, L, COL_PLAIN>), grid, dim3(NT), 0, s, W, H, cg, tw, dg);
-    else if (mode == COL_STAGE_A)
-      hipLaunchKernelGGL((lng::col_long<T, L, COL_STAGE_A>), grid, dim3(NT), 0, s, W, H, cg, tw, dg);
-    else if (mode == COL_STAGE_B)
-      hipLaunchKernelGGL((lng::col_long<T, L, COL_STAGE_B>), grid, dim3(NT), 0, s, W, H, cg, tw, dg);
-    else
-      hipLaunchKernelGGL((lng::col_long<T, L, COL_ETD1>), grid, dim3(NT), 0, s, W, H, cg, tw, dg);
+    if constexpr (L == 4096) {
+      if (blocks < g_cus) return col_long_np<T, L, true, 1>(mode, pitch, outer, s, W, H, cg, tw, dg);
+    }
+    if constexpr (L < 8192) {
+      if (blocks >= 2 * g_cus) return col_long_np<T, L, false, 4>(mode, pitch, outer, s, W, H, cg, tw, dg);
+    }
+    col_long_np<T, L, false, 2>(mode, pitch, outer, s, W, H, cg, tw, dg);
   }
 }
 
