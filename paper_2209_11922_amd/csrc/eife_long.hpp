@@ -381,9 +381,24 @@ __global__ void __launch_bounds__((Shape<L, OWN>::NT), (LongWaves<T, L, OWN, 1>:
   }
   if constexpr (MODE == ROW_PHYS) {
     const fast::RowReaction<T, RK> fa(F, ra % g.ny, ra / g.ny), fb(F, rb % g.ny, rb / g.ny);
-    sine<T, L, OWN>(z, z, tw, t, [&](int k, Cx<T> Z) {
-      return Cx<T>{fa(F, -Z.im * scale, k - 1), fb(F, Z.re * scale, k - 1)};
-    });
+    if constexpr (RK == fast::RK_AC) {
+      sine<T, L, OWN>(z, z, tw, t, [&](int k, Cx<T> Z) {
+        return Cx<T>{fa(F, -Z.im * scale, k - 1), fb(F, Z.re * scale, k - 1)};
+      });
+    } else {
+      // in node order: the outputs' order steps by A through the forcing's tables
+      // (4096 x 2048 FP64, Example 5.1: 62 us a pass at the outputs, 58 here; the manufactured problem at 4096 x 4096 FP32 74 and 59)
+      sine<T, L, OWN>(z, z, tw, t, [&](int, Cx<T> Z) { return Cx<T>{-Z.im * scale, Z.re * scale}; });
+      const int tr = fresh(t);
+#pragma unroll
+      for (int i = 0; i < RIT; ++i) {
+        if (tr + NT * i < n) {
+          Cx<T>* const zp = z + node_pos(tr + NT * i + 1);
+          const Cx<T> u = *zp;
+          *zp = Cx<T>{fa(F, u.re, tr + NT * i), fb(F, u.im, tr + NT * i)};
+        }
+      }
+    }
   }
   sine<T, L, OWN>(z, z, tw, t, [&](int, Cx<T> Z) { return Cx<T>{-Z.im * scale, Z.re * scale}; });
   T* da = dst + int64_t(ra) * g.ld_dst + t;
