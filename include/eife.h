@@ -124,8 +124,7 @@ int eife_set_phi(eife_grid g, double tau, int stages);
  * EIFE2 node of eife_set_c2 is separate).  Its weights follow eq. (2.2): b_i
  * from the Lagrange polynomials of (0, c2, c3), a_3j from those of (0, c2)
  * (the reading that satisfies the consistency conditions, eq. (2.3)).  The
- * three-stage column passes are the generic kernels (no specialised or
- * split-BF16 variant: eife_step returns EIFE_EUNSUPPORTED with
+ * three-stage column passes have no split-BF16 variant (eife_step returns EIFE_EUNSUPPORTED with
  * EIFE_TX_GEMM_SPLITBF16); the scheme keeps a third array X = e^{c3 z} u^ +
  * tau a31 G_1 between its first and second stage.  If the grid is set to
  * 3 stages, eife_set_phi must be called again.  Errors: EIFE_EINVAL. */
