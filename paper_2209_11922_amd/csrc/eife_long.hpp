@@ -19,8 +19,8 @@
 // unit, one's memory accesses under the other's arithmetic.
 //
 // Against one block per pair with all L points in 16-point pieces per thread (8192 FP64
-// points fill LDS): 4096 x 2048 FP64 x pass 93 -> 49 us (134 MB), y stages 119 -> 94 and
-// 115 -> 90 us (268 MB); 4096 x 4096 FP32 x pass 72 -> 46 us, y stages 157 -> 146 us;
+// points fill LDS): 4096 x 2048 FP64 x pass 93 -> 49 us (134 MB), y stages 119 -> 88 and
+// 115 -> 84 us (268 MB); 4096 x 4096 FP32 x pass 72 -> 46 us, y stages 157 -> 146 us;
 // 1024 x 1024 FP64 23 -> 20.5 us; a single line of 4096 FP64 63 -> 37 us a step.
 #pragma once
 
@@ -470,8 +470,9 @@ __global__ void __launch_bounds__((NP * Shape<L, OWN>::NT), (LongWaves<T, L, OWN
   const int c = 2 * (NP * bx + p0);
   const int64_t base = int64_t(outer) * g.ld_outer + c;
   const T scale = T(1.0 / sqrt(double(L)));
-  // H ahead of the transform where the registers allow
-  constexpr bool AHEAD = MODE != COL_PLAIN && (sizeof(T) == 4 || Shape<L, OWN>::A < 16);
+  // H ahead of the transform where the registers allow (FP64 at 2048 intervals it spills
+  // eight of them: 4096 x 2048 260 us a step, read in the stage 247)
+  constexpr bool AHEAD = MODE != COL_PLAIN && (sizeof(T) == 4 || Shape<L, OWN>::A < 8);
   Cx<T> hv[AHEAD ? RIT : 1][V];
   {
     Cx<T> v[RIT][V];
