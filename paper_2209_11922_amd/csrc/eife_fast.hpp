@@ -643,7 +643,7 @@ __global__ void __launch_bounds__((PB / PPW * Line<T, L>::LP), (ColMinWaves<T, L
   constexpr int CIT = (n + MS - 1) / MS;
   const int tq = tid % PB;
   const int m0 = tid / PB;
-  const int ldl = int(g.ld_line);  // tile offsets stay below 2^31 elements
+  const int ldl = int(g.ld_line);  // a tile's offsets fit 32 bits (tile_fits_32)
   const Cx<T>* gsrc = reinterpret_cast<const Cx<T>*>(W + base + m0 * ldl + 2 * tq);
   Cx<T>* ltile = lds + tq * BUF + m0;
   // narrow tiles (small grids, one wave per block): the stage's H values are

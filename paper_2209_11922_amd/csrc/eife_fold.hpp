@@ -383,7 +383,7 @@ __global__ void __launch_bounds__(NT, (ColWaves<MODE>::value))
   const int tid = threadIdx.x;
   const int lane = tid & 63, wave = tid >> 6;
   const int gq = tid % GR, m0 = tid / GR;  // piece and first row (0-based node m = slot of m + 1)
-  const int ldl = int(g.ld_line);          // tile offsets stay below 2^31 elements
+  const int ldl = int(g.ld_line);          // a tile's offsets fit 32 bits (tile_fits_32)
   auto offset = [&](int t) -> int64_t {
     return int64_t(t / ntx) * g.ld_outer + (t % ntx) * 2 * TP + 4 * gq + int64_t(m0) * ldl;
   };

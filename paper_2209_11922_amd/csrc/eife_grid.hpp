@@ -85,6 +85,12 @@ bool fast_len(int N) {
   return N == 64 || N == 128 || N == 256 || N == 512 || N == 192 || (N == 384 && sizeof(T) == 4);
 }
 
+// Whether the offsets inside a line of a column pass fit 32 bits, in which the tiles of
+// eife_fast.hpp and eife_fold.hpp keep them.  False only along z, on grids of more than
+// 2^31 elements (4096 x 2560 x 256: 240 rows of 10.5 million elements): those lines take
+// the mixed-radix passes, whose offsets have 64 bits (as those of the long lines have).
+inline bool tile_fits_32(const ColGeom& cg) { return int64_t(cg.n) * cg.ld_line <= INT32_MAX; }
+
 // Launches of the kernels that are specialised to a line length (eife_f32.hip,
 // eife_f64.hip: eife_special.hpp compiled for one element type each); false where
 // no such kernel takes the pass, which then runs on the mixed-radix kernels.

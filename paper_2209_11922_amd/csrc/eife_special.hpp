@@ -442,9 +442,8 @@ bool try_row_fast(const eife_grid_s* g, int var, int mode, int count, hipStream_
 template <typename T>
 bool try_col_fast(const eife_grid_s* g, int var, int axis, int mode, int outer, int count, hipStream_t s, T* W, T* H,
                   const ColGeom& cg, const Cx<T>* tw, const Diag& dg, const ColInst<T>* ci) {
-  if (g->per[axis]) return try_col_fast_per<T>(g, axis, mode, outer, count, s, W, H, cg, tw, dg, ci);
   if (g->transform != EIFE_TX_FFT) return false;
-  if (long_len(g->N[axis])) {
+  if (!g->per[axis] && long_len(g->N[axis])) {
     if (count != 1 || ci || mode > COL_ETD1) return false;
     if (g->N[axis] == 1024)
       col_long_launch<T, 2048>(mode, g->pitch, outer, s, W, H, cg, tw, dg);
@@ -454,6 +453,8 @@ bool try_col_fast(const eife_grid_s* g, int var, int axis, int mode, int outer, 
       col_long_launch<T, 8192>(mode, g->pitch, outer, s, W, H, cg, tw, dg);
     return true;
   }
+  if (!tile_fits_32(cg)) return false;
+  if (g->per[axis]) return try_col_fast_per<T>(g, axis, mode, outer, count, s, W, H, cg, tw, dg, ci);
   if constexpr (sizeof(T) == 4) {
     if (!ci && fold_cols<T>(g, axis, outer)) {
       fold::col_launch(g_cus, mode, g->pitch, outer, s, W, H, cg, tw, dg);
