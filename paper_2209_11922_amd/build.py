@@ -7,8 +7,8 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 LIB = os.path.join(PKG, "libeife.so")
 CSRC = os.path.join(PKG, "csrc")
-SOURCES = ["eife_f64.hip", "eife_f32.hip", "eife_mix_f64.hip", "eife_mix_f32.hip", "eife.hip", "eife_corr.hip",
-           "eife_fold.hip", "eife_mix.hip"]
+SOURCES = ["eife_f64.hip", "eife_f32.hip", "eife_mix_f64.hip", "eife_mix_f32.hip", "eife_mix_prime_f64.hip",
+           "eife_mix_prime_f32.hip", "eife.hip", "eife_corr.hip", "eife_fold.hip", "eife_mix.hip"]
 
 HIPCC_FLAGS = [
     "--offload-arch=gfx950",

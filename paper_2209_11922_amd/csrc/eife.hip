@@ -74,15 +74,6 @@ thread_local const char* g_bad_launch = nullptr;
 
 namespace {
 
-template <typename T>
-void fill_twiddles(std::vector<Cx<T>>& v, int L) {
-  v.resize(L);
-  for (int j = 0; j < L; ++j) {
-    const double ang = -2.0 * M_PI * double(j) / double(L);
-    v[j] = Cx<T>{T(std::cos(ang)), T(std::sin(ang))};
-  }
-}
-
 // lambda_k = lamB_k / lamA_k = 6 (1 - cos t) / (h^2 (2 + cos t)), t = k pi / N
 // (Section 4, with the mass eigenvalue (h/6)(4 + 2 cos t)); 1 - cos t is
 // formed as 2 sin^2(t/2) to avoid cancellation for small k.
@@ -523,7 +514,8 @@ int launch_row(eife_grid_s* g, int mode, const T* src, int64_t ld_src, T* dst, i
       !try_row_fast<T>(g, B.var_row, mode, B.count, s, src, dst, dst2, rg, tw, F, ri)) {
     if (g->per[0] && (ri || mode == ROW_FWD_PHYS)) return fail(EIFE_EUNSUPPORTED, "periodic row pass variant");
     const int lp = mix_lp(B.prow, g->lp_row, [&](int q) { return int64_t((rg.nrows + (2 << q) - 1) / (2 << q)) * B.count; });
-    if (!mix::row_launch<T>(g->plan[0], lp, g->per[0], mode, B.count, s, src, dst, dst2, rg, tw, F, ri))
+    const auto launch = g->plan[0].np ? &mix::Kernels<T, true>::row_launch : &mix::Kernels<T, false>::row_launch;
+    if (!launch(g->plan[0], lp, g->per[0], mode, B.count, s, src, dst, dst2, rg, tw, F, ri))
       return fail(EIFE_EINVAL, "mixed-radix row pass shape");
   }
   if (g_bad_launch) return fail(EIFE_EINVAL, "%s", g_bad_launch);
@@ -569,7 +561,8 @@ int launch_col(eife_grid_s* g, int axis, int mode, T* W, T* H, const Diag& dg, h
       !try_col_fast<T>(g, B.var_col, axis, mode, outer, B.count, s, W, H, cg, tw, dg, ci)) {
     if (g->per[axis] && ci) return fail(EIFE_EUNSUPPORTED, "periodic batched column pass");
     const int lp = mix_lp(B.pcol, g->lp_col[axis], [&](int q) { return int64_t(g->pitch / (2 << q)) * outer * B.count; });
-    if (!mix::col_launch<T>(g->plan[axis], lp, g->per[axis], g->per[0], mode, g->pitch, outer, B.count, s, W, H, cg, tw, dg, ci))
+    const auto launch = g->plan[axis].np ? &mix::Kernels<T, true>::col_launch : &mix::Kernels<T, false>::col_launch;
+    if (!launch(g->plan[axis], lp, g->per[axis], g->per[0], mode, g->pitch, outer, B.count, s, W, H, cg, tw, dg, ci))
       return fail(EIFE_EINVAL, "mixed-radix column pass shape");
   }
   if (g_bad_launch) return fail(EIFE_EINVAL, "%s", g_bad_launch);
@@ -931,7 +924,9 @@ int eife_create_grid(int d, const int32_t* N, const double* h, double D, int bc,
     return fail(EIFE_EUNSUPPORTED, "a line of this grid needs %zu bytes of LDS, device allows %zu", need,
                 g->max_lds);
   }
-  if (dtype == EIFE_F32 ? mix::set_attrs<float>(need) : mix::set_attrs<double>(need)) {
+  const bool no_lds = dtype == EIFE_F32 ? mix::Kernels<float, false>::set_attrs(need) || mix::Kernels<float, true>::set_attrs(need)
+                                        : mix::Kernels<double, false>::set_attrs(need) || mix::Kernels<double, true>::set_attrs(need);
+  if (no_lds) {
     free_grid(g);
     return fail(EIFE_EHIP, "cannot allow %zu bytes of LDS per block", need);
   }
@@ -945,26 +940,13 @@ int eife_create_grid(int d, const int32_t* N, const double* h, double D, int bc,
     return fail(EIFE_EHIP, "hipMemset failed");
   }
   for (int a = 0; a < 3; ++a) {
-    const int L = g->plan[a].L;
-    size_t bytes;
-    if (dtype == EIFE_F32) {
-      std::vector<Cx<float>> v;
-      fill_twiddles(v, L);
-      bytes = v.size() * sizeof(v[0]);
-      if (hipMalloc(&g->tw[a], bytes) != hipSuccess ||
-          hipMemcpy(g->tw[a], v.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) {
-        free_grid(g);
-        return fail(EIFE_ENOMEM, "twiddle table allocation failed");
-      }
-    } else {
-      std::vector<Cx<double>> v;
-      fill_twiddles(v, L);
-      bytes = v.size() * sizeof(v[0]);
-      if (hipMalloc(&g->tw[a], bytes) != hipSuccess ||
-          hipMemcpy(g->tw[a], v.data(), bytes, hipMemcpyHostToDevice) != hipSuccess) {
-        free_grid(g);
-        return fail(EIFE_ENOMEM, "twiddle table allocation failed");
-      }
+    auto upload = [&](const auto& v) {
+      const size_t bytes = v.size() * sizeof(v[0]);
+      return hipMalloc(&g->tw[a], bytes) == hipSuccess && hipMemcpy(g->tw[a], v.data(), bytes, hipMemcpyHostToDevice) == hipSuccess;
+    };
+    if (!(dtype == EIFE_F32 ? upload(mix::twiddle_values<float>(g->plan[a])) : upload(mix::twiddle_values<double>(g->plan[a])))) {
+      free_grid(g);
+      return fail(EIFE_ENOMEM, "twiddle table allocation failed");
     }
     g->tablen[a] = (a == 0) ? g->pitch : g->n[a];
     if (hipMalloc(reinterpret_cast<void**>(&g->tab[a]), kTabArrays * size_t(g->tablen[a]) * sizeof(double)) != hipSuccess ||

@@ -1,5 +1,7 @@
 // Plans of the mixed-radix passes (eife_mix.hpp).
 #include <algorithm>
+#include <cmath>
+#include <cstring>
 #include <vector>
 
 #include "eife_mix.hpp"
@@ -74,13 +76,13 @@ bool make_plan(int L, Plan* pl) {
   int smooth = L;
   for (int p : primes) smooth /= p;
   std::vector<int> seq = best_radices(smooth);
-  // large prime stages last: their twiddle sweep is the same anywhere, and the first
-  // stage, without twiddles, is the cheapest of the others
+  // prime stages first: each forms its outputs in double with the next stage's twiddles
   std::sort(seq.begin(), seq.end(), [](int a, int b) { return a > b; });
-  seq.insert(seq.end(), primes.begin(), primes.end());
+  seq.insert(seq.begin(), primes.begin(), primes.end());
   if (seq.size() > size_t(kMaxStages)) return false;
   pl->L = L;
   pl->ns = int(seq.size());
+  pl->np = int(primes.size());
   int Ns = 1;
   for (int i = 0; i < pl->ns; ++i) {
     Stage& s = pl->st[i];
@@ -88,12 +90,38 @@ bool make_plan(int L, Plan* pl) {
     s.Ns = Ns;
     s.nbf = L / s.R;
     s.tws = L / (Ns * s.R);
+    s.roots = i == 0 ? L : pl->st[i - 1].roots + pl->st[i - 1].R;
+    s.twiddle = i > pl->np;
     s.inv_ns = inv32(Ns);
     s.inv_nbf = inv32(s.nbf);
     Ns *= s.R;
   }
   return true;
 }
+
+template <typename T>
+std::vector<Cx<T>> twiddle_values(const Plan& pl) {
+  auto root = [](int j, int n) {
+    const double ang = -2.0 * M_PI * double(j) / double(n);
+    return Cx<double>{std::cos(ang), std::sin(ang)};
+  };
+  const int L = pl.L;
+  std::vector<Cx<double>> w(L);
+  for (int j = 0; j < L; ++j) w[j] = root(j, L);
+  std::vector<Cx<T>> v(L);
+  for (int j = 0; j < L; ++j) v[j] = Cx<T>{T(w[j].re), T(w[j].im)};
+  for (int i = 0; i < pl.np; ++i)
+    for (int e = 0; e < pl.st[i].R; ++e) w.push_back(root(e, pl.st[i].R));
+  if (pl.np > 0) {
+    // FP32: all of w, from a multiple of 16 bytes on; FP64: the roots
+    const size_t from = sizeof(T) == 8 ? size_t(L) : 0, at = sizeof(T) == 8 ? size_t(L) : size_t(L + 1) & ~size_t(1);
+    v.resize(at + (w.size() - from) * sizeof(w[0]) / sizeof(v[0]));
+    std::memcpy(static_cast<void*>(&v[at]), &w[from], (w.size() - from) * sizeof(w[0]));
+  }
+  return v;
+}
+template std::vector<Cx<float>> twiddle_values<float>(const Plan&);
+template std::vector<Cx<double>> twiddle_values<double>(const Plan&);
 
 size_t lds_bytes(const Plan& pl, int lp, int esz) { return (size_t(pl.L) << lp) * 2 * esz; }
 
@@ -103,7 +131,7 @@ bool block_shape(const Plan& pl, int lp, int esz, int* JT, int* pts) {
     int jt = 1;
     for (int i = 0; i < pl.ns; ++i) {
       const Stage& s = pl.st[i];
-      const bool prime = s.R > 7 && s.R != 8 && s.R != 9 && s.R != 10 && s.R != 12 && s.R != 15 && s.R != 16;
+      const bool prime = i < pl.np;
       const int work = prime ? s.nbf * ((s.R + 1) / 2) : s.nbf;  // tasks of the stage
       const int per = prime ? v / 2 : v / s.R;                   // tasks per thread
       jt = std::max(jt, (work + per - 1) / per);

@@ -20,6 +20,8 @@
 // pass 110 -> 38 us.
 #pragma once
 
+#include <vector>
+
 #include "eife_fast.hpp"
 
 namespace eife {
@@ -30,11 +32,13 @@ constexpr int kMaxThreads = 512;
 
 struct Stage {
   int R, Ns, nbf, tws;    // radix, product of the radices before it, L / R, L / (Ns R)
+  int roots;              // prime radix: place of exp(-2 pi i e / R), e < R, behind the twiddles in double
+  int twiddle;            // the inputs still need their twiddles (not in the first stage, nor after a prime one)
   uint32_t inv_ns, inv_nbf;  // ceil(2^32 / Ns), ceil(2^32 / nbf) (unused for 1)
 };
 
 struct Plan {
-  int L, ns;
+  int L, ns, np;  // length, stages, how many of them (the first) have a prime radix above 7
   Stage st[kMaxStages];
 };
 
@@ -143,9 +147,9 @@ __device__ __forceinline__ void stage(Cx<T>* lds, const Stage& st, int lp, int p
     if (j < nbf) {
 #pragma unroll
       for (int q = 0; q < R; ++q) v[s][q] = line[(j + q * nbf) << lp];
-      if (Ns > 1) {
+      if (st.twiddle) {
         const int k = j - quot(j, Ns, st.inv_ns) * Ns;
-        twiddle_powers<T, R>(v[s], tw[k * st.tws]);
+        twiddle_powers<T, R>(v[s], tw, k * st.tws);
       }
       Rdx<T, R>::run(v[s]);
     }
@@ -165,25 +169,34 @@ __device__ __forceinline__ void stage(Cx<T>* lds, const Stage& st, int lp, int p
   __syncthreads();
 }
 
-// A stage of a prime radix R > 7: the inputs times their twiddles in place, then per
-// butterfly j the outputs m and R - m together from a_r = x_r + x_{R-r}, b_r = x_r - x_{R-r}:
+// The twiddles in double, the roots of the prime radices behind them; FP32: behind those in T (twiddle_values).
+template <typename T>
+__device__ __forceinline__ const Cx<double>* twiddles64(const Cx<T>* __restrict__ tw, int L) {
+  if constexpr (sizeof(T) == 8)
+    return tw;
+  else
+    return reinterpret_cast<const Cx<double>*>(tw + ((L + 1) & ~1));
+}
+
+// A stage of a prime radix R > 7: per butterfly j the outputs m and R - m together from
+// a_r = x_r + x_{R-r}, b_r = x_r - x_{R-r}:
 //   X_m, X_{R-m} = x_0 + sum_r a_r cos(2 pi r m / R) -+ i sum_r b_r sin(2 pi r m / R),
-// sums in double.
+// sums and factors in double.  Prime stages are the first of a plan and multiply their
+// outputs by the twiddles of the next stage (nx, null in the last) before they round to
+// T: no rounding and no LDS sweep for the twiddles alone.
 template <typename T, int PTS>
-__device__ __forceinline__ void stage_prime(Cx<T>* lds, const Stage& st, int L, int lp, int p, int jt, int JT,
-                                            const Cx<T>* __restrict__ tw, int lim) {
+__device__ __forceinline__ void stage_prime(Cx<T>* lds, const Stage& st, const Stage* nx, int lp, int p, int jt, int JT,
+                                            const Cx<double>* __restrict__ tw, int lim) {
   constexpr int B = PTS / 2;
   const int R = st.R, nbf = st.nbf, Ns = st.Ns, H = (R - 1) / 2;
+  const Cx<double>* __restrict__ roots = tw + st.roots;
   Cx<T>* const line = lds + p;
-  if (Ns > 1) {
-    for (int i = jt + nbf; i < L; i += JT) {
-      const int q = quot(i, nbf, st.inv_nbf);
-      const int j = i - q * nbf;
-      const int k = j - quot(j, Ns, st.inv_ns) * Ns;
-      line[i << lp] = cmul(line[i << lp], tw[q * k * st.tws]);
-    }
-    __syncthreads();
-  }
+  // twiddle of the next stage's input i
+  auto next = [&](int i) -> Cx<double> {
+    const int q = quot(i, nx->nbf, nx->inv_nbf);
+    const int j = i - q * nx->nbf;
+    return tw[q * (j - quot(j, nx->Ns, nx->inv_ns) * nx->Ns) * nx->tws];
+  };
   Cx<T> o1[B], o2[B];
 #pragma unroll
   for (int s = 0; s < B; ++s) {
@@ -191,6 +204,13 @@ __device__ __forceinline__ void stage_prime(Cx<T>* lds, const Stage& st, int L, 
     if (u < nbf * (H + 1)) {
       const int m = quot(u, nbf, st.inv_nbf);
       const int j = u - m * nbf;
+      const int k = j - quot(j, Ns, st.inv_ns) * Ns;
+      const int base = (j - k) * R + k;
+      Cx<double> w1 = {1.0, 0.0}, w2 = w1;
+      if (nx) {  // ahead of the sums: their latency hides behind them
+        w1 = next(base + m * Ns);
+        w2 = next(base + (m ? R - m : 0) * Ns);
+      }
       const Cx<T> x0 = line[j << lp];
       double cr = x0.re, ci = x0.im, sr = 0.0, si = 0.0;
       int e = 0;
@@ -198,15 +218,15 @@ __device__ __forceinline__ void stage_prime(Cx<T>* lds, const Stage& st, int L, 
         const Cx<T> x = line[(j + r * nbf) << lp], y = line[(j + (R - r) * nbf) << lp];
         e += m;
         if (e >= R) e -= R;
-        const Cx<T> w = tw[e * nbf];
-        const double c = w.re, sn = -double(w.im);
-        cr = fma(c, double(x.re) + double(y.re), cr);
-        ci = fma(c, double(x.im) + double(y.im), ci);
-        sr = fma(sn, double(x.re) - double(y.re), sr);
-        si = fma(sn, double(x.im) - double(y.im), si);
+        const Cx<double> w = roots[e];
+        cr = fma(w.re, double(x.re) + double(y.re), cr);
+        ci = fma(w.re, double(x.im) + double(y.im), ci);
+        sr = fma(-w.im, double(x.re) - double(y.re), sr);
+        si = fma(-w.im, double(x.im) - double(y.im), si);
       }
-      o1[s] = Cx<T>{T(cr + si), T(ci - sr)};
-      o2[s] = Cx<T>{T(cr - si), T(ci + sr)};
+      const Cx<double> X1 = cmul(Cx<double>{cr + si, ci - sr}, w1), X2 = cmul(Cx<double>{cr - si, ci + sr}, w2);
+      o1[s] = Cx<T>{T(X1.re), T(X1.im)};
+      o2[s] = Cx<T>{T(X2.re), T(X2.im)};
     }
   }
   __syncthreads();
@@ -226,13 +246,19 @@ __device__ __forceinline__ void stage_prime(Cx<T>* lds, const Stage& st, int L, 
 }
 
 // Forward FFT of the block's pairs (natural order in and out; outputs at slots below
-// keep).  The caller has synchronised after writing the inputs.
-template <typename T, int PTS>
+// keep).  The caller has synchronised after writing the inputs.  PRIME: the plan may have
+// prime stages (kernels of their own: the stage's registers and code cost the others up
+// to 4%).
+template <typename T, int PTS, bool PRIME>
 __device__ __forceinline__ void fft(Cx<T>* lds, const Plan& pl, int lp, int p, int jt, int JT,
                                     const Cx<T>* __restrict__ tw, int keep) {
   for (int i = 0; i < pl.ns; ++i) {
     const Stage st = pl.st[i];
     const int lim = i == pl.ns - 1 ? keep : pl.L;
+    if (PRIME && i < pl.np) {
+      stage_prime<T, PTS>(lds, st, i + 1 < pl.ns ? &pl.st[i + 1] : nullptr, lp, p, jt, JT, twiddles64(tw, pl.L), lim);
+      continue;
+    }
     switch (st.R) {
       case 16: stage<T, 16, PTS>(lds, st, lp, p, jt, JT, tw, lim); break;
       case 15: stage<T, 15, PTS>(lds, st, lp, p, jt, JT, tw, lim); break;
@@ -245,14 +271,13 @@ __device__ __forceinline__ void fft(Cx<T>* lds, const Plan& pl, int lp, int p, i
       case 5: stage<T, 5, PTS>(lds, st, lp, p, jt, JT, tw, lim); break;
       case 4: stage<T, 4, PTS>(lds, st, lp, p, jt, JT, tw, lim); break;
       case 3: stage<T, 3, PTS>(lds, st, lp, p, jt, JT, tw, lim); break;
-      case 2: stage<T, 2, PTS>(lds, st, lp, p, jt, JT, tw, lim); break;
-      default: stage_prime<T, PTS>(lds, st, pl.L, lp, p, jt, JT, tw, lim); break;
+      default: stage<T, 2, PTS>(lds, st, lp, p, jt, JT, tw, lim); break;
     }
   }
 }
 
 // The lines of a block and this thread's place in them.
-template <typename T, int PTS>
+template <typename T, int PTS, bool PRIME>
 struct Lines {
   Cx<T>* lds;
   const Shape& sh;
@@ -274,7 +299,7 @@ struct Lines {
   // The caller has synchronised.  Forward: coefficient m by coef(m); inverse: node
   // values by node(m) (the sine transform is its own inverse).
   __device__ __forceinline__ void run() const {
-    fft<T, PTS>(lds, sh.pl, sh.lp, p, jt, sh.JT, tw, sh.per ? sh.pl.L : sh.pl.L / 2);
+    fft<T, PTS, PRIME>(lds, sh.pl, sh.lp, p, jt, sh.JT, tw, sh.per ? sh.pl.L : sh.pl.L / 2);
   }
   __device__ __forceinline__ void forward() const {
     run();
@@ -339,7 +364,7 @@ struct Waves {
 };
 
 // Row pass (x lines, contiguous): rows 2 (P bx + p), + 1 are pair p.
-template <typename T, int PTS, int RK>
+template <typename T, int PTS, bool PRIME, int RK>
 __global__ void __launch_bounds__(kMaxThreads, (Waves<T, PTS>::value))
     row_mix(const T* src, T* dst, T* dst2, RowGeom g, Shape sh, const Cx<T>* __restrict__ tw, Forcing F,
             const RowInst<T>* __restrict__ insts, int mode) {
@@ -352,7 +377,7 @@ __global__ void __launch_bounds__(kMaxThreads, (Waves<T, PTS>::value))
       row_inst_ptrs<T, ROW_PHYS>(insts, src, dst, dst2, F);
   }
   extern __shared__ unsigned char smem_raw[];
-  const Lines<T, PTS> ln(reinterpret_cast<Cx<T>*>(smem_raw), sh, tw, g.n);
+  const Lines<T, PTS, PRIME> ln(reinterpret_cast<Cx<T>*>(smem_raw), sh, tw, g.n);
   const int n = g.n, JT = sh.JT;
   const int ra = 2 * ((int(blockIdx.x) << sh.lp) + ln.p), rb = ra + 1;
   const bool hasa = ra < g.nrows, hasb = rb < g.nrows;
@@ -456,8 +481,8 @@ __device__ __forceinline__ void diag_any(const Sep& s, double D, double tau, dou
 
 // The diagonal stage over the block's lines: coefficient m -> the value to inverse
 // transform, H updated; four H values in flight.
-template <typename T, int PTS, int MODE, bool ZERO>
-__device__ __forceinline__ void diag_lines(const Lines<T, PTS>& ln, T scale, T* H, int64_t base, int ldl, int col,
+template <int MODE, bool ZERO, typename T, typename Ln>
+__device__ __forceinline__ void diag_lines(const Ln& ln, T scale, T* H, int64_t base, int ldl, int col,
                                            int outer, const ColGeom& g, const AxisTab& t0, const AxisTab& t1,
                                            const AxisTab& t2, double D, const Diag& dg) {
   const double tau = dg.tau, rtc2 = 1.0 / (tau * dg.c2);
@@ -496,7 +521,7 @@ __device__ __forceinline__ void diag_lines(const Lines<T, PTS>& ln, T scale, T* 
 // Blocks in XCD-contiguous order, so that the tiles of a 128-byte line share an L2.
 // MODE: COL_PLAIN (forward), COL_PLAIN_INV (inverse, periodic lines), a stage of one or
 // two stages (COL_ETD1, COL_STAGE_A, COL_STAGE_B) or of three (COL_S3_*).
-template <typename T, int PTS, int MODE>
+template <typename T, int PTS, bool PRIME, int MODE>
 __global__ void __launch_bounds__(kMaxThreads, (Waves<T, PTS>::value))
     col_mix(T* W, T* H, ColGeom g, Shape sh, const Cx<T>* __restrict__ tw, Diag dg, const ColInst<T>* __restrict__ insts) {
   AxisTab t0 = dg.ax[0], t1 = dg.ax[1], t2 = dg.ax[2];
@@ -511,7 +536,7 @@ __global__ void __launch_bounds__(kMaxThreads, (Waves<T, PTS>::value))
     D = I.D;
   }
   extern __shared__ unsigned char smem_raw[];
-  const Lines<T, PTS> ln(reinterpret_cast<Cx<T>*>(smem_raw), sh, tw, g.n);
+  const Lines<T, PTS, PRIME> ln(reinterpret_cast<Cx<T>*>(smem_raw), sh, tw, g.n);
   const int n = g.n, JT = sh.JT;
   int bx, outer;
   xcd_block(bx, outer);
@@ -550,9 +575,9 @@ __global__ void __launch_bounds__(kMaxThreads, (Waves<T, PTS>::value))
           ln.put(m, Cx<T>{outv[0], outv[1]});
         }
       } else if (sh.zero) {
-        diag_lines<T, PTS, MODE, true>(ln, scale, H, base, ldl, col, outer, g, t0, t1, t2, D, dg);
+        diag_lines<MODE, true>(ln, scale, H, base, ldl, col, outer, g, t0, t1, t2, D, dg);
       } else {
-        diag_lines<T, PTS, MODE, false>(ln, scale, H, base, ldl, col, outer, g, t0, t1, t2, D, dg);
+        diag_lines<MODE, false>(ln, scale, H, base, ldl, col, outer, g, t0, t1, t2, D, dg);
       }
     }
     __syncthreads();
@@ -567,6 +592,10 @@ __global__ void __launch_bounds__(kMaxThreads, (Waves<T, PTS>::value))
 // Host side (eife_mix.hip).
 // Plan of an FFT of length L <= 8192; false when it needs more than kMaxStages.
 bool make_plan(int L, Plan* pl);
+// The twiddle table of a plan as the passes read it: exp(-2 pi i k / L), k < L, in T; for
+// prime stages behind it the same in double (FP32) and the roots of each radix in double.
+template <typename T>
+std::vector<Cx<T>> twiddle_values(const Plan& pl);
 // Threads per pair of a block of P = 2^lp pairs and the values per thread (16, or 32
 // where 16 would need more than kMaxThreads); false when no block of that size fits.
 bool block_shape(const Plan& pl, int lp, int esz, int* JT, int* pts);
@@ -576,15 +605,17 @@ size_t lds_bytes(const Plan& pl, int lp, int esz);
 // 16 pairs per block against 8: FP32 stage passes 52 -> 41 us, FP64 88 -> 58 us; against
 // 4: 46, 63 us).
 int pick_lp(const Plan& pl, int esz, int cap);
-// Allow dynamic LDS up to `bytes` for every kernel of the element type.
-template <typename T>
-int set_attrs(size_t bytes);
-template <typename T>
-bool row_launch(const Plan& pl, int lp, bool per, int mode, int count, hipStream_t s, const T* src, T* dst, T* dst2,
-                const RowGeom& rg, const Cx<T>* tw, const Forcing& F, const RowInst<T>* ri);
-template <typename T>
-bool col_launch(const Plan& pl, int lp, bool per, bool zero, int mode, int pitch, int outer, int count, hipStream_t s, T* W, T* H,
-                const ColGeom& cg, const Cx<T>* tw, const Diag& dg, const ColInst<T>* ci);
+// The kernels of one element type, without or with prime stages (each combination is a
+// translation unit of its own).
+template <typename T, bool PRIME>
+struct Kernels {
+  // Allow dynamic LDS up to `bytes` for every kernel.
+  static int set_attrs(size_t bytes);
+  static bool row_launch(const Plan& pl, int lp, bool per, int mode, int count, hipStream_t s, const T* src, T* dst, T* dst2,
+                         const RowGeom& rg, const Cx<T>* tw, const Forcing& F, const RowInst<T>* ri);
+  static bool col_launch(const Plan& pl, int lp, bool per, bool zero, int mode, int pitch, int outer, int count, hipStream_t s,
+                         T* W, T* H, const ColGeom& cg, const Cx<T>* tw, const Diag& dg, const ColInst<T>* ci);
+};
 
 }  // namespace mix
 }  // namespace eife
