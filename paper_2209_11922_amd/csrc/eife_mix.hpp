@@ -276,6 +276,25 @@ __device__ __forceinline__ void fft(Cx<T>* lds, const Plan& pl, int lp, int p, i
   }
 }
 
+// x / sqrt(n) by the factor's value in T and what that leaves out: the same rounded factor
+// in every transform of a step adds its error up (periodic FP64 48^3, two steps: 1.0e-15
+// from exact with the rounded factors, 4.9e-16 so).
+template <typename T>
+struct RootScale {
+  T hi, lo;
+  __device__ __forceinline__ explicit RootScale(int n) {
+    const double s = 1.0 / sqrt(double(n));
+    hi = T(s);
+    if constexpr (sizeof(T) == 4) {
+      lo = T(s - double(hi));
+    } else {  // s (1 - n s^2) / 2
+      const double q = s * s;
+      lo = 0.5 * s * (fma(-double(n), q, 1.0) - double(n) * fma(s, s, -q));
+    }
+  }
+  __device__ __forceinline__ T operator()(T x) const { return fma(x, hi, x * lo); }
+};
+
 // The lines of a block and this thread's place in them.
 template <typename T, int PTS, bool PRIME>
 struct Lines {
@@ -306,15 +325,15 @@ struct Lines {
     if (sh.per) {
       // (Z_k, Z_{N-k}) -> the coefficients at k and N - k, in place
       const int N = n;
-      const T s1 = T(1.0 / sqrt(double(N))), s2 = T(1.0 / sqrt(2.0 * double(N)));
+      const RootScale<T> s1(N), s2(2 * N);
       for (int k = jt; k <= N / 2; k += sh.JT) {
         const Cx<T> zp = at(k);
         if (k == 0 || 2 * k == N) {
-          at(k) = Cx<T>{zp.re * s1, zp.im * s1};
+          at(k) = Cx<T>{s1(zp.re), s1(zp.im)};
         } else {
           const Cx<T> zm = at(N - k);
-          at(k) = Cx<T>{(zp.re + zm.re) * s2, (zp.im + zm.im) * s2};
-          at(N - k) = Cx<T>{(zm.im - zp.im) * s2, (zp.re - zm.re) * s2};
+          at(k) = Cx<T>{s2(zp.re + zm.re), s2(zp.im + zm.im)};
+          at(N - k) = Cx<T>{s2(zm.im - zp.im), s2(zp.re - zm.re)};
         }
       }
       __syncthreads();
@@ -324,15 +343,15 @@ struct Lines {
     if (sh.per) {
       // the coefficients at k and N - k -> conj(Z^), in place
       const int N = n;
-      const T r2 = T(0.70710678118654752440);
+      const RootScale<T> r2(2);
       for (int k = jt; k <= N / 2; k += sh.JT) {
         const Cx<T> ck = at(k);
         if (k == 0 || 2 * k == N) {
           at(k) = Cx<T>{ck.re, -ck.im};
         } else {
           const Cx<T> cm = at(N - k);
-          at(k) = Cx<T>{(ck.re + cm.im) * r2, (cm.re - ck.im) * r2};
-          at(N - k) = Cx<T>{(ck.re - cm.im) * r2, -(ck.im + cm.re) * r2};
+          at(k) = Cx<T>{r2(ck.re + cm.im), r2(cm.re - ck.im)};
+          at(N - k) = Cx<T>{r2(ck.re - cm.im), -r2(ck.im + cm.re)};
         }
       }
       __syncthreads();
@@ -340,19 +359,19 @@ struct Lines {
     run();
   }
   // after forward()
-  __device__ __forceinline__ Cx<T> coef(int m, T scale) const {
+  __device__ __forceinline__ Cx<T> coef(int m, const RootScale<T>& scale) const {
     if (sh.per) return at(m);
     const Cx<T> Z = at(m + 1);
-    return Cx<T>{-Z.im * scale, Z.re * scale};
+    return Cx<T>{scale(-Z.im), scale(Z.re)};
   }
   // after inverse()
-  __device__ __forceinline__ Cx<T> node(int m, T scale) const {
+  __device__ __forceinline__ Cx<T> node(int m, const RootScale<T>& scale) const {
     if (sh.per) {
       const Cx<T> X = at(m);
-      return Cx<T>{X.re * scale, -X.im * scale};
+      return Cx<T>{scale(X.re), scale(-X.im)};
     }
     const Cx<T> Z = at(m + 1);
-    return Cx<T>{-Z.im * scale, Z.re * scale};
+    return Cx<T>{scale(-Z.im), scale(Z.re)};
   }
 };
 
@@ -381,7 +400,7 @@ __global__ void __launch_bounds__(kMaxThreads, (Waves<T, PTS>::value))
   const int n = g.n, JT = sh.JT;
   const int ra = 2 * ((int(blockIdx.x) << sh.lp) + ln.p), rb = ra + 1;
   const bool hasa = ra < g.nrows, hasb = rb < g.nrows;
-  const T scale = T(1.0 / sqrt(double(sh.pl.L)));
+  const RootScale<T> scale(sh.pl.L);
   constexpr int PV = 2;  // values per piece: 16 lanes of a pair read 128 bytes or more of a row, two slots apart in LDS
   const T* sa = src + int64_t(ra) * g.ld_src;
   const T* sb = sa + g.ld_src;
@@ -482,7 +501,7 @@ __device__ __forceinline__ void diag_any(const Sep& s, double D, double tau, dou
 // The diagonal stage over the block's lines: coefficient m -> the value to inverse
 // transform, H updated; four H values in flight.
 template <int MODE, bool ZERO, typename T, typename Ln>
-__device__ __forceinline__ void diag_lines(const Ln& ln, T scale, T* H, int64_t base, int ldl, int col,
+__device__ __forceinline__ void diag_lines(const Ln& ln, const RootScale<T>& scale, T* H, int64_t base, int ldl, int col,
                                            int outer, const ColGeom& g, const AxisTab& t0, const AxisTab& t1,
                                            const AxisTab& t2, double D, const Diag& dg) {
   const double tau = dg.tau, rtc2 = 1.0 / (tau * dg.c2);
@@ -543,7 +562,7 @@ __global__ void __launch_bounds__(kMaxThreads, (Waves<T, PTS>::value))
   const int col = (bx << (sh.lp + 1)) + 2 * ln.p;
   const int64_t base = int64_t(outer) * g.ld_outer + col;
   const int ldl = int(g.ld_line);
-  const T scale = T(1.0 / sqrt(double(sh.pl.L)));
+  const RootScale<T> scale(sh.pl.L);
   {
     constexpr int UB = 8;
     for (int m0 = ln.jt; m0 < n; m0 += UB * JT) {
