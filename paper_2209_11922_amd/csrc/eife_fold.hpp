@@ -10,7 +10,10 @@
 // sub-transforms r = 5, 6, 7 mirrors of r = 3, 2, 1, so five M-point
 // sub-transforms remain of eight (M = 64 = 4 x 4 x 4).  Against the plain L-point
 // FFT of eife_fast.hpp that is about two thirds of the butterflies, with no
-// prefix sums and no added rounding.  The columns j = 0 and j = M/2 are their own
+// prefix sums.  It has one set of twiddles more; with every twiddle from the table and
+// an exact scale its rounding error is the smaller all the same (255^3, four steps:
+// 3.4e-7 from 64 bits against 3.6e-7; 3.75e-7 with twiddles 3 and 4 as products and a
+// rounded scale).  The columns j = 0 and j = M/2 are their own
 // mirrors and are formed from the short sine sums they reduce to.
 //
 // Work split: a line pair takes LP = 16 lanes with 5 x 4 values each (the
@@ -75,10 +78,19 @@ __device__ __forceinline__ Cf mul_nconj(Cf x, Cf w) {
   return {-(x.re * w.re + x.im * w.im), x.re * w.im - x.im * w.re};
 }
 
+// x / sqrt(L) by the factor's FP32 value and what that leaves out (1.7e-8 of it, which
+// the transforms of a step would add up).
+__device__ __forceinline__ float scaled(float x) {
+  constexpr double s = 0.04419417382415922028;
+  constexpr float hi = float(s), lo = float(s - double(hi));
+  static_assert(L == 512, "1 / sqrt(L)");
+  return fmaf(x, hi, x * lo);
+}
+
 // The lane's place and twiddles in the transforms of its wavefront.
 struct Lane {
   int l, p;     // columns j = l mod LP of pair p
-  Cf w1[2][2];  // W_L^{j r}, j = l + LP t, r = 1, 2
+  Cf w1[2][4];  // W_L^{j r}, j = l + LP t, r = 1 .. 4
   Cf w2[4];     // i W_M^{l k} / sqrt(L)
   Cf w3[4];     // W_LP^{c k}, c = l mod 4
   __device__ __forceinline__ Lane(const Cf* __restrict__ tw, int lane) {
@@ -87,12 +99,11 @@ struct Lane {
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int r = 1; r <= 2; ++r) w1[t][r - 1] = tw[(l + LP * t) * r];
-    const float sc = float(1.0 / sqrt(double(L)));
+      for (int r = 1; r <= 4; ++r) w1[t][r - 1] = tw[(l + LP * t) * r];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const Cf w = tw[8 * l * k];
-      w2[k] = Cf{-w.im * sc, w.re * sc};
+      w2[k] = Cf{scaled(-w.im), scaled(w.re)};
       w3[k] = tw[32 * (l % 4) * k];
     }
   }
@@ -114,7 +125,7 @@ __device__ __forceinline__ void sub_transforms(Regs& R, Cf* col, const Lane& ln,
     for (int i = 0; i < RN; ++i) {
       Cf* v = R.v[R0 + RS * i];
       Dft<float, 4>::run(v);
-      v[0] = Cf{-v[0].im * ln.w2[0].im, v[0].re * ln.w2[0].im};  // W = 1: i / sqrt(L)
+      v[0] = Cf{scaled(-v[0].im), scaled(v[0].re)};  // W = 1
 #pragma unroll
       for (int k = 1; k < 4; ++k) v[k] = cmul(v[k], ln.w2[k]);
 #pragma unroll
@@ -197,7 +208,7 @@ __device__ __forceinline__ void transform(Regs& R, Cf* reg, const Lane& ln) {
     o[3] = Cf{(o[3].im - o[3].re) * h, -(o[3].re + o[3].im) * h};
     Dft<float, 4>::run(e);  // X[0], X[2], X[4], X[6]
     Dft<float, 4>::run(o);  // X[1], X[3], X[5], X[7]
-    const Cf w[4] = {ln.w1[t][0], ln.w1[t][1], cmul(ln.w1[t][0], ln.w1[t][1]), cmul(ln.w1[t][1], ln.w1[t][1])};
+    const Cf* const w = ln.w1[t];
     Cf own[5] = {e[0], cmul(o[0], w[0]), cmul(e[1], w[1]), cmul(o[1], w[2]), cmul(e[2], w[3])};
     Cf mir[5] = {Cf{-e[0].re, -e[0].im}, mul_nconj(o[3], w[0]), mul_nconj(e[3], w[1]), mul_nconj(o[2], w[2]),
                  mul_nconj(e[2], w[3])};
