@@ -402,11 +402,17 @@ struct Line<T, L, false> {
 // Reaction kinds that get their own code path (everything else is generic).
 enum { RK_GENERIC = 0, RK_AC = 1, RK_WAVE = 2 };
 
+// The row whose reaction a line takes: the last one for lines past the end.  Their results
+// are not stored, but the forcing's tables end with the last row, and the packed
+// transform carries whatever is read there into the line's partner.
+__host__ __device__ __forceinline__ int reaction_row(const RowGeom& g, int row) { return row < g.nrows ? row : g.nrows - 1; }
+
 // The reaction along one row (y, z index iy, iz).
 template <typename T, int RK>
 struct RowReaction {
   int iy, iz;
-  __device__ __forceinline__ RowReaction(const Forcing&, int y, int z) : iy(y), iz(z) {}
+  __host__ __device__ __forceinline__ RowReaction(const Forcing&, const RowGeom& g, int row)
+      : iy(reaction_row(g, row) % g.ny), iz(reaction_row(g, row) / g.ny) {}
   __device__ __forceinline__ T operator()(const Forcing& F, T u, int ix) const {
     if (RK == RK_AC) return u - u * u * u;
     return reaction<T>(F, u, ix, iy, iz);
@@ -415,7 +421,8 @@ struct RowReaction {
 template <typename T>
 struct RowReaction<T, RK_WAVE> {
   ShellRow r;
-  __device__ __forceinline__ RowReaction(const Forcing& F, int y, int z) : r(shell_row(F, y, z)) {}
+  __device__ __forceinline__ RowReaction(const Forcing& F, const RowGeom& g, int row)
+      : r(shell_row(F, reaction_row(g, row) % g.ny, reaction_row(g, row) / g.ny)) {}
   __device__ __forceinline__ T operator()(const Forcing& F, T u, int ix) const { return reaction_wave<T>(F, r, u, ix); }
 };
 
@@ -483,7 +490,7 @@ __global__ void __launch_bounds__((PB * Line<T, L>::LP), (MinWaves<T, L>::value)
       }
     }
     wave_sync();
-    const RowReaction<T, RK> fa(F, ra % g.ny, ra / g.ny), fb(F, rb % g.ny, rb / g.ny);
+    const RowReaction<T, RK> fa(F, g, ra), fb(F, g, rb);
 #pragma unroll
     for (int t = 0; t < RIT; ++t) {
       const int m = lane + LP * t;
@@ -494,7 +501,7 @@ __global__ void __launch_bounds__((PB * Line<T, L>::LP), (MinWaves<T, L>::value)
   }
 
   if (MODE == ROW_PHYS) {
-    const RowReaction<T, RK> fa(F, ra % g.ny, ra / g.ny), fb(F, rb % g.ny, rb / g.ny);
+    const RowReaction<T, RK> fa(F, g, ra), fb(F, g, rb);
     Ln::outputs(v, lane, tw, [&](int k, Cx<T> Z) {
       my[k - 1] = Cx<T>{fa(F, -Z.im * scale, k - 1), fb(F, Z.re * scale, k - 1)};
     });

@@ -310,7 +310,7 @@ __global__ void __launch_bounds__(64, 4) row_fold(float* W, RowGeom g, const Cf*
   transform(R, lds, ln);
   {
     const int ta = blockIdx.x * 2 * PW + 2 * ln.p, tb = ta + 1;
-    const fast::RowReaction<float, RK> fa(F, ta % g.ny, ta / g.ny), fb(F, tb % g.ny, tb / g.ny);
+    const fast::RowReaction<float, RK> fa(F, g, ta), fb(F, g, tb);
     const bool ina = ta < g.nrows, inb = tb < g.nrows;  // rows past the end stay zero
     outputs(R, ln, [&](int k, int s, Cf u) {
       lds[s * PW + ln.p] = Cf{ina ? fa(F, u.re, k - 1) : 0.f, inb ? fb(F, u.im, k - 1) : 0.f};

@@ -380,7 +380,7 @@ __global__ void __launch_bounds__((Shape<L, OWN>::NT), (LongWaves<T, L, OWN, 1>:
     if (t == 0) z[0] = Cx<T>{T(0), T(0)};
   }
   if constexpr (MODE == ROW_PHYS) {
-    const fast::RowReaction<T, RK> fa(F, ra % g.ny, ra / g.ny), fb(F, rb % g.ny, rb / g.ny);
+    const fast::RowReaction<T, RK> fa(F, g, ra), fb(F, g, rb);
     if constexpr (RK == fast::RK_AC) {
       sine<T, L, OWN>(z, z, tw, t, [&](int k, Cx<T> Z) {
         return Cx<T>{fa(F, -Z.im * scale, k - 1), fb(F, Z.re * scale, k - 1)};

@@ -433,7 +433,7 @@ __global__ void __launch_bounds__(kMaxThreads, (Waves<T, PTS>::value))
   } else {
     ln.inverse();
     if (mode == ROW_PHYS) {
-      const fast::RowReaction<T, RK> rfa(F, ra % g.ny, ra / g.ny), rfb(F, rb % g.ny, rb / g.ny);
+      const fast::RowReaction<T, RK> rfa(F, g, ra), rfb(F, g, rb);
       const int off = sh.per ? -1 : 0;  // the reaction counts interior nodes
       for (int m = ln.jt; m < n; m += JT) {
         const Cx<T> u = ln.node(m, scale);

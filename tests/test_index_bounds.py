@@ -48,3 +48,25 @@ def test_32_bit_tiles_only_where_the_offsets_fit(tmp_path):
   cg.ld_line = int64_t(4096) * 2559;
   if (tile_fits_32(cg) || refused == 0) return 3;
 """)
+
+
+def test_reactions_of_lines_past_the_end_stay_in_the_tables(tmp_path):
+    """A row pass forms the reaction of every line of its blocks, up to 63 rows past the last one on
+    odd row counts; the y and z indices it reads the forcing's tables at are those of rows."""
+    _run(tmp_path, """
+  Forcing F{};
+  for (int ny : {1, 2, 63, 64, 511})
+    for (int nz : {1, 3, 64, 255}) {
+      RowGeom g{};
+      g.ny = ny;
+      g.nrows = ny * nz;
+      for (int row = 0; row < g.nrows + 64; ++row) {
+        const fast::RowReaction<float, fast::RK_GENERIC> r(F, g, row);
+        if (r.iy < 0 || r.iy >= ny || r.iz < 0 || r.iz >= nz) {
+          printf("row %d of %d x %d: %d, %d\\n", row, ny, nz, r.iy, r.iz);
+          return 1;
+        }
+        if (row < g.nrows && r.iz * ny + r.iy != row) return 2;
+      }
+    }
+""")
