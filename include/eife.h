@@ -307,8 +307,8 @@ int eife_batch_step(eife_batch b, void* u, int64_t n_steps, int f_kind, double t
  * specialised line lengths two row tile widths and, for columns, two tile
  * widths with one tile per block plus (FP32) both widths in a persistent
  * stage pass that prefetches each next tile across instances; for the other
- * lengths the line pairs per block of both passes.  Every choice gives the
- * same results bit for bit.  Before tuning, FP32 classes of 512-interval
+ * lengths the line pairs per block of either pass, 1 to 16, the untuned
+ * shape first.  Every choice gives the same results bit for bit.  Before tuning, FP32 classes of 512-interval
  * columns use the persistent stage pass, the others the widest tiles.  With a
  * non-null cache_path, choices recorded there for this device, dtype and
  * class are reused, and new ones are added to the file (JSON).  Blocks the

@@ -477,17 +477,23 @@ struct Batchlet {
   int prow = 0, pcol = 0;        // mixed-radix passes: pairs per block (0 = the grid's default)
 };
 
-// Pairs per block (log2) of a mixed-radix launch: the tuned number, else the grid's
-// widest block, halved while the launch has fewer blocks than compute units (blocks(q)
-// for 2^q pairs); the results do not depend on it.
-template <typename F>
-int mix_lp(int tuned, int widest, F blocks) {
-  int lp = widest;
-  if (tuned > 0) {
-    for (lp = 0; (2 << lp) <= tuned;) ++lp;
-    return lp;
-  }
-  while (lp > 0 && blocks(lp) < g_cus) --lp;
+// Pairs per block (log2) of a mixed-radix pass over `count` grids: the grid's widest block,
+// halved while the launch has fewer blocks than compute units; the results do not depend
+// on it.
+int mix_lp_row(const eife_grid_s* g, int count) {
+  int lp = g->lp_row;
+  while (lp > 0 && int64_t((g->nlines_total() + (2 << lp) - 1) / (2 << lp)) * count < g_cus) --lp;
+  return lp;
+}
+int mix_lp_col(const eife_grid_s* g, int axis, int outer, int count) {
+  int lp = g->lp_col[axis];
+  while (lp > 0 && int64_t(g->pitch / (2 << lp)) * outer * count < g_cus) --lp;
+  return lp;
+}
+// log2 of a tuned number of pairs.
+int log2_pairs(int P) {
+  int lp = 0;
+  while ((2 << lp) <= P) ++lp;
   return lp;
 }
 
@@ -513,7 +519,7 @@ int launch_row(eife_grid_s* g, int mode, const T* src, int64_t ld_src, T* dst, i
   if (!(B.count == 1 && !ri && try_row_gemm<T>(g, mode, s, src, dst, dst2, rg, F)) &&
       !try_row_fast<T>(g, B.var_row, mode, B.count, s, src, dst, dst2, rg, tw, F, ri)) {
     if (g->per[0] && (ri || mode == ROW_FWD_PHYS)) return fail(EIFE_EUNSUPPORTED, "periodic row pass variant");
-    const int lp = mix_lp(B.prow, g->lp_row, [&](int q) { return int64_t((rg.nrows + (2 << q) - 1) / (2 << q)) * B.count; });
+    const int lp = B.prow > 0 ? log2_pairs(B.prow) : mix_lp_row(g, B.count);
     const auto launch = g->plan[0].np ? &mix::Kernels<T, true>::row_launch : &mix::Kernels<T, false>::row_launch;
     if (!launch(g->plan[0], lp, g->per[0], mode, B.count, s, src, dst, dst2, rg, tw, F, ri))
       return fail(EIFE_EINVAL, "mixed-radix row pass shape");
@@ -560,7 +566,7 @@ int launch_col(eife_grid_s* g, int axis, int mode, T* W, T* H, const Diag& dg, h
   if ((s3 || !(B.count == 1 && !ci && try_col_gemm<T>(g, axis, mode, outer, s, W, H, cg, dg))) &&
       !try_col_fast<T>(g, B.var_col, axis, mode, outer, B.count, s, W, H, cg, tw, dg, ci)) {
     if (g->per[axis] && ci) return fail(EIFE_EUNSUPPORTED, "periodic batched column pass");
-    const int lp = mix_lp(B.pcol, g->lp_col[axis], [&](int q) { return int64_t(g->pitch / (2 << q)) * outer * B.count; });
+    const int lp = B.pcol > 0 ? log2_pairs(B.pcol) : mix_lp_col(g, axis, outer, B.count);
     const auto launch = g->plan[axis].np ? &mix::Kernels<T, true>::col_launch : &mix::Kernels<T, false>::col_launch;
     if (!launch(g->plan[axis], lp, g->per[axis], g->per[0], mode, g->pitch, outer, B.count, s, W, H, cg, tw, dg, ci))
       return fail(EIFE_EINVAL, "mixed-radix column pass shape");
@@ -1422,6 +1428,12 @@ void tune_store(const char* path, const std::string& key, const int v[4], double
   fclose(f);
 }
 
+// Column variant before any tuning: FP32 classes of 512-interval columns take the
+// pipelined stage pass (measured faster).
+int default_var_col(const eife_grid_s* g) {
+  return g->dtype == EIFE_F32 && g->N[1] == 512 && g->transform == EIFE_TX_FFT ? 2 : 0;
+}
+
 template <typename T>
 int tune_class(eife_batch_s* b, eife_batch_s::Class& c, const char* path, hipStream_t s) {
   const std::string key = tune_key(b, c);
@@ -1432,14 +1444,17 @@ int tune_class(eife_batch_s* b, eife_batch_s::Class& c, const char* path, hipStr
   // line pairs per block whose LDS regions fit and whose tiles divide the pitch
   auto valid = [&](const std::array<int, 4>& cd) {
     if (fast) return cd[0] >= 0 && cd[0] < 2 && cd[1] >= 0 && cd[1] < ncol && cd[2] == 0 && cd[3] == 0;
-    // pairs per block: a power of two whose block fits and whose tiles divide the pitch
-    auto fits = [&](int a, int P) {
-      int jt, pts, lp = 0;
-      while ((2 << lp) <= P) ++lp;
-      return P >= 1 && P <= 16 && (1 << lp) == P && mix::lds_bytes(g->plan[a], lp, int(g->esz)) <= 65536 &&
+    // pairs per block: a power of two whose block fits (64 KB of LDS, or the default's) and
+    // whose tiles divide the pitch
+    auto fits = [&](int a, int P, int widest) {
+      int jt, pts;
+      const int lp = log2_pairs(P);
+      return P >= 1 && P <= 16 && (1 << lp) == P &&
+             (lp <= widest || mix::lds_bytes(g->plan[a], lp, int(g->esz)) <= 65536) &&
              mix::block_shape(g->plan[a], lp, int(g->esz), &jt, &pts);
     };
-    return cd[0] == 0 && cd[1] == 0 && fits(0, cd[2]) && fits(1, cd[3]) && g->pitch % (2 * cd[3]) == 0;
+    return cd[0] == 0 && (cd[1] == 0 || cd[1] == default_var_col(g)) && fits(0, cd[2], g->lp_row) && fits(1, cd[3], g->lp_col[1]) &&
+           g->pitch % (2 * cd[3]) == 0;
   };
   int v[4];
   if (tune_lookup(path, key, v) && valid({v[0], v[1], v[2], v[3]})) {
@@ -1449,22 +1464,12 @@ int tune_class(eife_batch_s* b, eife_batch_s::Class& c, const char* path, hipStr
     c.pcol = v[3];
     return EIFE_OK;
   }
-  std::vector<std::array<int, 4>> cands;
-  if (fast) {
-    for (int r = 0; r < 2; ++r)
-      for (int cc = 0; cc < ncol; ++cc) cands.push_back({r, cc, 0, 0});
-  } else {
-    for (int pr : {4, 8, 16})
-      for (int pc : {4, 8, 16})
-        if (valid({0, 0, pr, pc})) cands.push_back({0, 0, pr, pc});
-  }
-  if (cands.empty()) return EIFE_OK;  // no candidate fits: keep the defaults
   hipEvent_t e0, e1;
   HIP_TRY(hipEventCreate(&e0));
   HIP_TRY(hipEventCreate(&e1));
   double best = 1e30;
-  std::array<int, 4> bestc = cands[0];
-  for (const auto& cd : cands) {
+  std::array<int, 4> bestc{};
+  auto try_shape = [&](const std::array<int, 4>& cd) -> int {
     c.var_row = cd[0];
     c.var_col = cd[1];
     c.prow = cd[2];
@@ -1479,6 +1484,23 @@ int tune_class(eife_batch_s* b, eife_batch_s::Class& c, const char* path, hipStr
     if (ms < best) {
       best = ms;
       bestc = cd;
+    }
+    return EIFE_OK;
+  };
+  if (fast) {
+    for (int r = 0; r < 2; ++r)
+      for (int cc = 0; cc < ncol; ++cc) RET_IF(try_shape({r, cc, 0, 0}));
+  } else {
+    // the shape of an untuned launch first, then each pass by itself
+    const int count = int(c.members.size());
+    RET_IF(try_shape({0, default_var_col(g), 1 << mix_lp_row(g, count), 1 << mix_lp_col(g, 1, 1, count)}));
+    for (int k : {2, 3}) {
+      const std::array<int, 4> from = bestc;
+      for (int P : {1, 2, 4, 8, 16}) {
+        std::array<int, 4> cd = from;
+        cd[k] = P;
+        if (P != from[k] && valid(cd)) RET_IF(try_shape(cd));
+      }
     }
   }
   (void)hipEventDestroy(e0);
@@ -1526,12 +1548,7 @@ int eife_create_batch(int B, const int32_t* N, const double* h, const double* D,
     }
     b->classes[found].members.push_back(i);
   }
-  // default column variant before any tuning: FP32 classes of 512-interval
-  // columns take the pipelined stage pass (measured faster)
-  for (auto& c : b->classes) {
-    const eife_grid_s* g0 = b->inst[c.members[0]];
-    if (dtype == EIFE_F32 && g0->N[1] == 512 && g0->transform == EIFE_TX_FFT) c.var_col = 2;
-  }
+  for (auto& c : b->classes) c.var_col = default_var_col(b->inst[c.members[0]]);
   const int r = dtype == EIFE_F32 ? build_batch_tables<float>(b) : build_batch_tables<double>(b);
   if (r != EIFE_OK) {
     free_batch(b);

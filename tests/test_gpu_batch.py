@@ -132,6 +132,25 @@ def test_autotune_ignores_invalid_cache_entries(tmp_path):
     b.close()
 
 
+def test_autotune_of_mixed_radix_classes_includes_the_untuned_shape(tmp_path):
+    """Classes whose untuned launches take one or two pairs per block (1000 and 384 intervals
+    in FP64: 32 and 12 KB a pair) are tuned too, from that shape on; the bits stay."""
+    inst = [(1000, 20, 1e-3), (384, 384, 9e-4), (40, 1000, 1e-3), (4000, 6, 1e-3), (40, 40, 1e-3)]
+    u0s = _inputs(inst, 600)
+    cache = tmp_path / "tune.json"
+    b0, ref = _batch_run(inst, u0s, 0.01, 2, 2, "f64")
+    b0.close()
+    for _ in range(2):  # tuned, then read back
+        b, outs = _batch_run(inst, u0s, 0.01, 2, 2, "f64", autotune=cache)
+        rec = json.loads(cache.read_text())
+        assert len(rec) == len(inst)
+        for info in b.class_info():
+            assert info[3] in (1, 2, 4, 8, 16) and info[4] in (1, 2, 4, 8, 16), info
+        for a, c in zip(ref, outs):
+            assert np.array_equal(a, c)
+        b.close()
+
+
 def test_batch_matches_oracle():
     inst = _mixed_instances()
     u0s = _inputs(inst, 7)
