@@ -69,3 +69,18 @@ def test_blocks_of_tables_match_single_steps(stages, variable):
         t += dt
     assert _rel(u.cpu().numpy(), v.cpu().numpy()) <= TOL["f64"]
     g.close()
+
+
+def test_large_grid_of_256_interval_rows_matches_generic():
+    """FP32 256-interval rows enough for the folded row pass, which has no traveling wave:
+    these rows stay on the wave-local pass.  Against the generic passes."""
+    N, tau = [256, 184, 184], T_END / 256
+    assert 183 * 183 >= 16 * 8 * torch.cuda.get_device_properties(0).multi_processor_count
+    out = []
+    for transform in ("TX_FFT", "TX_FFT_GENERIC"):
+        eife, g, _, _, u = _setup(N, "f32", 2, tau)
+        g.set_transform(getattr(eife.binding, transform))
+        g.step(u, 2, eife.F_TRAVELING_WAVE, 0.0)
+        out.append(u.double().cpu().numpy())
+        g.close()
+    assert _rel(out[0], out[1]) <= TOL["f32"]
