@@ -896,7 +896,7 @@ int eife_create_grid(int d, const int32_t* N, const double* h, double D, int bc,
     if (!mix::make_plan(g->per[a] ? g->N[a] : 2 * g->N[a], &g->plan[a])) {
       const int bad = g->N[a];
       delete g;
-      return fail(EIFE_EUNSUPPORTED, "N = %d: FFT length has more than three prime factors above 7", bad);
+      return fail(EIFE_EUNSUPPORTED, "N = %d: no plan for its FFT length", bad);
     }
   }
   g->pitch = ((g->n[0] + 31) / 32) * 32;

@@ -74,28 +74,6 @@ struct Dft<T, 4> {
   }
 };
 
-// 8 points: two 4-point transforms of the even and odd inputs, then
-// X_k = E_k + W^k O_k, X_{k+4} = E_k - W^k O_k with W = exp(-i pi/4).
-template <typename T>
-struct Dft<T, 8> {
-  static __device__ __forceinline__ void run(Cx<T>* v) {
-    const T s = T(0.70710678118654752440);
-    Cx<T> e[4] = {v[0], v[2], v[4], v[6]};
-    Cx<T> o[4] = {v[1], v[3], v[5], v[7]};
-    Dft<T, 4>::run(e);
-    Dft<T, 4>::run(o);
-    const Cx<T> t[4] = {o[0],
-                        Cx<T>{s * (o[1].re + o[1].im), s * (o[1].im - o[1].re)},
-                        cmnegi(o[2]),
-                        Cx<T>{s * (o[3].im - o[3].re), -s * (o[3].re + o[3].im)}};
-#pragma unroll
-    for (int k = 0; k < 4; ++k) {
-      v[k] = cadd(e[k], t[k]);
-      v[k + 4] = csub(e[k], t[k]);
-    }
-  }
-};
-
 // Odd prime P: with a_r = v_r + v_{P-r}, b_r = v_r - v_{P-r} (r = 1 .. (P-1)/2)
 // and theta = 2 pi r k / P,
 //   X_k     = v_0 + sum_r a_r cos(theta) - i sum_r b_r sin(theta),

@@ -10,8 +10,8 @@
 // PTS values at a time in registers; every division left (by the Stockham stride) is
 // a multiplication by a 32-bit reciprocal from the host's plan.  Radices 2 ... 16
 // (composites of coprime factors by the prime-factor mapping, without twiddles
-// inside) keep the number of LDS sweeps down: N = 240 runs 16 x 6 x 5, three sweeps.
-// Prime factors above 7 run as symmetric direct DFTs of the stage.
+// inside) keep the number of LDS sweeps down: N = 240 (480 points) runs 12 x 10 x 4,
+// three sweeps.  Prime factors above 7 run as symmetric direct DFTs of the stage.
 //
 // Bound by vector instructions and barrier latency (28% VALU, 20% LDS, 57% of the wave
 // time waiting, at 16 pairs per block).  239 x 149 x 99 nodes (28 MB per FP32 array and

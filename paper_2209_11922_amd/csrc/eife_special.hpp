@@ -233,7 +233,9 @@ void col_fast_launch(int var, int mode, int pitch, int outer, int count, hipStre
 // or 16 wavefronts of eight rows per compute unit.  Smaller launches last as
 // long as one wavefront's work, and the folded wavefront holds four line pairs
 // against one (255^2: x pass 9 against 4 us, stage passes 14 against 6.5 us; at
-// 255^3: x pass 39 against 43 us, stage passes 61-66 against 72-78 us).
+// 255^3: x pass 39 against 43 us, stage passes 61-66 against 72-78 us).  Batched and 2D
+// grids keep the wave-local passes for another reason too: an instance of a batch has the
+// bits of its single grid, and the two forms of the transform round differently.
 template <typename T>
 bool fold_cols(const eife_grid_s* g, int axis, int outer) {
   return sizeof(T) == 4 && g->d == 3 && g->N[axis] == 256 && (g->pitch / 32) * int64_t(outer) >= 2 * g_cus;
