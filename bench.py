@@ -50,15 +50,15 @@ def measured_traffic(pass_name):
     """HBM bytes per launch from the committed rocprofv3 counter summary, or None.
 
     The record is only used while the kernel sources are byte-identical to the
-    ones the counters were taken on (sha256 over the two kernel headers).
+    ones the counters were taken on (sha256 over the kernel headers).
     """
     import hashlib
     rec_path = os.path.join(ROOT, "profiles", "traffic_255cubed_f32.json")
     csrc = os.path.join(ROOT, "paper_2209_11922_amd", "csrc")
     try:
         rec = json.load(open(rec_path))
-        src = open(os.path.join(csrc, "eife_fast.hpp"), "rb").read() + \
-            open(os.path.join(csrc, "eife_kernels.hpp"), "rb").read()
+        src = b"".join(open(os.path.join(csrc, f), "rb").read()
+                       for f in ("eife_fast.hpp", "eife_kernels.hpp", "eife_fold.hpp"))
     except OSError:
         return None
     if hashlib.sha256(src).hexdigest() != rec.get("source_sha256"):

@@ -10,10 +10,10 @@
 // sub-transforms r = 5, 6, 7 mirrors of r = 3, 2, 1, so five M-point
 // sub-transforms remain of eight (M = 64 = 4 x 4 x 4).  Against the plain L-point
 // FFT of eife_fast.hpp that is about two thirds of the butterflies, with no
-// prefix sums.  It has one set of twiddles more; with every twiddle from the table and
-// an exact scale its rounding error is the smaller all the same (255^3, four steps:
-// 3.4e-7 from 64 bits against 3.6e-7; 3.75e-7 with twiddles 3 and 4 as products and a
-// rounded scale).  The columns j = 0 and j = M/2 are their own
+// prefix sums.  It has one set of twiddles more; with an exact scale its rounding error
+// is the smaller all the same (255^3, four steps: 3.49e-7 from 64 bits against 3.58e-7;
+// 3.75e-7 with a rounded scale; 3.42e-7 with the twiddles 3 and 4 from the table too, which
+// costs up to 0.6% of the step).  The columns j = 0 and j = M/2 are their own
 // mirrors and are formed from the short sine sums they reduce to.
 //
 // Work split: a line pair takes LP = 16 lanes with 5 x 4 values each (the
@@ -31,8 +31,10 @@
 //
 // Measured at 255^3 (66 MB arrays, mean of a step's launches): y pass 32 -> 24 us
 // (5.6 TB/s, 82% of a device copy), stage passes 77 / 71 -> 64 / 58 us, x pass 41 ->
-// 39 us.  The x pass is bound by its two transforms' LDS and vector instructions
-// (skipping them leaves 21 us), the y pass by memory (20 us without its transform).
+// 39 us, 1.005 times the algorithmic bytes.  No unit is saturated: the x pass has the
+// vector ALU 57% and the LDS 43% busy and its waves 39% of their time in memory waits
+// (without the transforms it takes 21 us), the y pass 45 and 38% at 5.1 TB/s (20 us
+// without its transform), the stages 50 and 30% with 42% of the wave time in waits.
 // The same split for other lengths or FP64 (32-byte LDS regions per node, two
 // wavefronts per SIMD) measured no faster than eife_fast.hpp.
 #pragma once
@@ -90,7 +92,7 @@ __device__ __forceinline__ float scaled(float x) {
 // The lane's place and twiddles in the transforms of its wavefront.
 struct Lane {
   int l, p;     // columns j = l mod LP of pair p
-  Cf w1[2][4];  // W_L^{j r}, j = l + LP t, r = 1 .. 4
+  Cf w1[2][2];  // W_L^{j r}, j = l + LP t, r = 1, 2
   Cf w2[4];     // i W_M^{l k} / sqrt(L)
   Cf w3[4];     // W_LP^{c k}, c = l mod 4
   __device__ __forceinline__ Lane(const Cf* __restrict__ tw, int lane) {
@@ -99,7 +101,7 @@ struct Lane {
 #pragma unroll
     for (int t = 0; t < 2; ++t)
 #pragma unroll
-      for (int r = 1; r <= 4; ++r) w1[t][r - 1] = tw[(l + LP * t) * r];
+      for (int r = 1; r <= 2; ++r) w1[t][r - 1] = tw[(l + LP * t) * r];
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const Cf w = tw[8 * l * k];
@@ -208,7 +210,7 @@ __device__ __forceinline__ void transform(Regs& R, Cf* reg, const Lane& ln) {
     o[3] = Cf{(o[3].im - o[3].re) * h, -(o[3].re + o[3].im) * h};
     Dft<float, 4>::run(e);  // X[0], X[2], X[4], X[6]
     Dft<float, 4>::run(o);  // X[1], X[3], X[5], X[7]
-    const Cf* const w = ln.w1[t];
+    const Cf w[4] = {ln.w1[t][0], ln.w1[t][1], cmul(ln.w1[t][0], ln.w1[t][1]), cmul(ln.w1[t][1], ln.w1[t][1])};
     Cf own[5] = {e[0], cmul(o[0], w[0]), cmul(e[1], w[1]), cmul(o[1], w[2]), cmul(e[2], w[3])};
     Cf mir[5] = {Cf{-e[0].re, -e[0].im}, mul_nconj(o[3], w[0]), mul_nconj(e[3], w[1]), mul_nconj(o[2], w[2]),
                  mul_nconj(e[2], w[3])};

@@ -13,11 +13,11 @@
 // inside) keep the number of LDS sweeps down: N = 240 (480 points) runs 12 x 10 x 4,
 // three sweeps.  Prime factors above 7 run as symmetric direct DFTs of the stage.
 //
-// Bound by vector instructions and barrier latency (28% VALU, 20% LDS, 57% of the wave
-// time waiting, at 16 pairs per block).  239 x 149 x 99 nodes (28 MB per FP32 array and
-// pass), against one LDS sweep per radix 8, 4, 3, 5 with a zero fill and divisions by
-// runtime lengths: FP32 y / z pass 67-78 -> 18-21 us, stage passes 146-155 -> 40 us, x
-// pass 110 -> 38 us.
+// No unit is saturated (239 x 149 x 99 nodes, FP32: vector ALU 39 to 49% busy, LDS 30 to
+// 44%, half of the wave time in the waits at the barriers between the sweeps; 1.01 times
+// the algorithmic bytes).  There, 28 MB per array and pass, against one LDS sweep per radix
+// 8, 4, 3, 5 with a zero fill and divisions by runtime lengths: y / z pass 67-78 -> 19-21
+// us, stage passes 146-155 -> 40-43 us, x pass 110 -> 39 us.
 #pragma once
 
 #include <vector>
